@@ -97,9 +97,13 @@ __device__ __forceinline__ void store_tile_through(const GemvParams& p, int out0
   }
 }
 
-__device__ __forceinline__ void store_out(const GemvParams& p, int col, float v) {
+// What store_out adds to column `col`; fetched by its callers before they wait for the sums.
+__device__ __forceinline__ float residual_of(const GemvParams& p, int col) {
+  return p.residual ? (float)p.residual[col] : 0.f;
+}
+__device__ __forceinline__ void store_out(const GemvParams& p, int col, float v, float residual) {
   if (p.y_scale) v *= *p.y_scale;
-  if (p.residual) v += (float)p.residual[col];
+  if (p.residual) v += residual;
   if (!p.f32_out())
     reinterpret_cast<half_t*>(p.y)[col] = (half_t)v;
   else
@@ -310,14 +314,9 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   __syncthreads();  // s_scratch changes its role: histograms -> wave sums
 
   // lane groups -> one row of sums per wave
+  const int first = af_sum_lane_groups<LX>(acc);
 #pragma unroll
-  for (int off = LX; off < AF_WAVE; off <<= 1)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] += __shfl_xor(acc[c], off, AF_WAVE);
-  if (ly == 0) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) s_red[wave][lx * 8 + c] = acc[c];
-  }
+  for (int c = 0; c < LX / 8; ++c) s_red[wave][lx * 8 + first + c] = acc[c];
   __syncthreads();
 
   const int tile0 = vb.bx * TW;                      // in the padded column space
@@ -334,10 +333,11 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       gemv_phase_signal(p);
     } else {
       for (int c = tid; c < valid; c += GEMV_THREADS) {
+        const float res = residual_of(p, out0 + c);
         float v = 0.f;
 #pragma unroll
         for (int w = 0; w < GEMV_WAVES; ++w) v += s_red[w][c];
-        store_out(p, out0 + c, v);
+        store_out(p, out0 + c, v, res);
       }
     }
     af_prof_end(p.prof);
@@ -367,8 +367,10 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       return af_sum_partials(p.partials + tile0 + c, p.out_pad, S);
     });
   } else {
-    for (int c = tid; c < valid; c += GEMV_THREADS)
-      store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S));
+    for (int c = tid; c < valid; c += GEMV_THREADS) {
+      const float res = residual_of(p, out0 + c);
+      store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S), res);
+    }
   }
   if (tid == 0) af_ticket_reset(&p.tickets[vb.bx]);  // ready for the next launch
   if constexpr (PHASE) gemv_phase_signal(p);

@@ -45,9 +45,13 @@ struct Q4Params {
   long long* prof;  // time stamps of this launch (af_profile_set), or null
 };
 
-__device__ __forceinline__ void q4_store_out(const Q4Params& p, int col, float v) {
+// What q4_store_out adds to column `col`; fetched by its callers before they wait for the sums.
+__device__ __forceinline__ float q4_residual_of(const Q4Params& p, int col) {
+  return p.residual ? (float)p.residual[col] : 0.f;
+}
+__device__ __forceinline__ void q4_store_out(const Q4Params& p, int col, float v, float residual) {
   if (p.y_scale) v *= *p.y_scale;
-  if (p.residual) v += (float)p.residual[col];
+  if (p.residual) v += residual;
   if (p.y_kind == AF_F16)
     reinterpret_cast<half_t*>(p.y)[col] = (half_t)v;
   else
@@ -284,14 +288,9 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
   }
   __syncthreads();  // s_scratch changes its role: histograms -> wave sums
 
+  const int first = af_sum_lane_groups<LX>(yacc);
 #pragma unroll
-  for (int off = LX; off < AF_WAVE; off <<= 1)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) yacc[c] += __shfl_xor(yacc[c], off, AF_WAVE);
-  if (ly == 0) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) s_red[wave][lx * 8 + c] = yacc[c];
-  }
+  for (int c = 0; c < LX / 8; ++c) s_red[wave][lx * 8 + first + c] = yacc[c];
   __syncthreads();
 
   const int tile0 = blockIdx.x * TW;                        // in the padded column space
@@ -299,10 +298,11 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
   const int valid = min(TW, p.cols_per_slot - tile_in * TW);
   if (S == 1) {
     for (int c = tid; c < valid; c += THREADS) {
+      const float res = q4_residual_of(p, out0 + c);
       float v = 0.f;
 #pragma unroll
       for (int w = 0; w < NW; ++w) v += s_red[w][c];
-      q4_store_out(p, out0 + c, v);
+      q4_store_out(p, out0 + c, v, res);
     }
     af_prof_end(p.prof);
     return;
@@ -325,8 +325,10 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
     af_prof_end(p.prof);
     return;
   }
-  for (int c = tid; c < valid; c += THREADS)
-    q4_store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S));
+  for (int c = tid; c < valid; c += THREADS) {
+    const float res = q4_residual_of(p, out0 + c);
+    q4_store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S), res);
+  }
   if (tid == 0) af_ticket_reset(&p.tickets[blockIdx.x]);
   af_prof_end(p.prof);
 }
