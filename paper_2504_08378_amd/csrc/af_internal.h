@@ -101,7 +101,7 @@ struct af_row_src {
 #define AF_GEMV_LDS_BUDGET (120u * 1024u)  // leaves room for the kernels' static LDS in 160 KB
 static inline bool af_plan_gemv_lds(const af_row_src& r, int max_rows, bool use_lds_x,
                                     bool range_sel, int chunk, int* S, size_t* xs_bytes,
-                                    int* list_cap, bool full_x = false) {
+                                    int* list_cap, bool full_x = false, bool by_range = false) {
   for (int s = *S < 1 ? 1 : *S; s <= 4096; ++s) {
     size_t xb;
     int cap;
@@ -110,6 +110,10 @@ static inline bool af_plan_gemv_lds(const af_row_src& r, int max_rows, bool use_
       xb = full_x ? (size_t)r.n * 2 : (size_t)cap * 2;  // an in-kernel router wants all of x
     } else if (r.sel != AF_ROWS_GIVEN) {
       cap = (max_rows + s - 1) / s;
+      if (by_range) {  // all kept channels may lie in one range
+        const int range = 8 * ((r.n / 8 + s - 1) / s);
+        cap = range < max_rows ? range : max_rows;
+      }
       xb = (size_t)r.n * 2;
     } else {
       cap = chunk;
@@ -292,6 +296,14 @@ __device__ __forceinline__ unsigned af_wave_incl_scan(unsigned v) {
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
   v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+// The same within each row of 16 lanes.
+__device__ __forceinline__ unsigned af_row_incl_scan(unsigned v) {
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
   return v;
 }
 __device__ __forceinline__ float af_wave_incl_scan(float v) {

@@ -93,7 +93,7 @@ static void launch_one(dim3 grid, size_t lds, hipStream_t st, const GemvParams& 
 // The 1024-thread launches that build or select their input come in one instantiation per
 // (producer, selection) pair of a decoder layer; anything else runs the generic kernel.
 template <int LX>
-static void launch_lx(int nw, dim3 grid, size_t lds, hipStream_t st, const GemvParams& p) {
+static void launch_lx(int nw, int early, dim3 grid, size_t lds, hipStream_t st, const GemvParams& p) {
   if (p.router_Wr != nullptr) {  // the launcher has made sure of nw == 16 and of an RMSNorm producer
     const int mode = gemv_mode_of(p);
     if (mode == GEMV_MODE(AF_PRO_RMSNORM, 1))
@@ -103,14 +103,18 @@ static void launch_lx(int nw, dim3 grid, size_t lds, hipStream_t st, const GemvP
     else
       launch_one<LX, 16, true, -1>(grid, lds, st, p);
   } else if (nw == 16) {
-    switch (gemv_mode_of(p)) {
+    const int mode = gemv_mode_of(p);
+    switch (mode | ((mode >> 2) == 1 ? early << 4 : 0)) {
 #define AF_MODE_CASE(pro, kind) \
   case GEMV_MODE(pro, kind):    \
     launch_one<LX, 16, false, GEMV_MODE(pro, kind)>(grid, lds, st, p); \
     break;
-      AF_MODE_CASE(AF_PRO_RMSNORM, 1)
-      AF_MODE_CASE(AF_PRO_NONE, 1)
-      AF_MODE_CASE(AF_PRO_SILUMUL, 1)
+#define AF_MODE_CASES(pro) AF_MODE_CASE(pro, 1) AF_MODE_CASE(pro, 1 | 1 << 2) AF_MODE_CASE(pro, 1 | 2 << 2) \
+                           AF_MODE_CASE(pro, 1 | GEMV_EARLY_NONE << 2)
+      AF_MODE_CASES(AF_PRO_RMSNORM)
+      AF_MODE_CASES(AF_PRO_NONE)
+      AF_MODE_CASES(AF_PRO_SILUMUL)
+#undef AF_MODE_CASES
       AF_MODE_CASE(AF_PRO_RMSNORM, 3)
       AF_MODE_CASE(AF_PRO_NONE, 3)
       AF_MODE_CASE(AF_PRO_SILUMUL, 3)
@@ -159,8 +163,20 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   while (S > 1 && (size_t)S * out_pad > ctx->lay.partial_floats) --S;
   if (a.router_Wr && (r.pro != AF_PRO_RMSNORM || a.router_E > 8 || r.n > 8192 || nw != 16 || !use_lds_x))
     return AF_EINVAL;  // the in-kernel router's preconditions (the caller falls back to the router kernel)
-  if (!af_plan_gemv_lds(r, max_rows, use_lds_x, range_sel, GEMV_LIST, &S, &xs_bytes, &list_cap,
-                        a.router_Wr != nullptr))
+  // Early rows split by channel range, and a range lists more rows than an even share of the list
+  // can have: they are used where that fits the LDS with this S, and the launch stays as it is
+  // without them where it does not.
+  int early = GEMV_EARLY_NONE;
+  if (r.sel == AF_SEL_TOPK && nw == 16 && !whole_layer && !a.router_Wr) {
+    int s_early = S;
+    early = gemv_early_class(r.n, (long long)r.k / S * tw * 2);
+    if (early != GEMV_EARLY_NONE &&
+        (!af_plan_gemv_lds(r, max_rows, use_lds_x, false, GEMV_LIST, &s_early, &xs_bytes, &list_cap, false, true) ||
+         s_early != S))
+      early = GEMV_EARLY_NONE;
+  }
+  if (early == GEMV_EARLY_NONE && !af_plan_gemv_lds(r, max_rows, use_lds_x, range_sel, GEMV_LIST, &S, &xs_bytes,
+                                                    &list_cap, a.router_Wr != nullptr))
     return AF_EWORKSPACE;
   if (S > 1 && (size_t)S * out_pad > ctx->lay.partial_floats) return AF_EWORKSPACE;
   GemvParams& p = plan->p;
@@ -192,6 +208,7 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   plan->S = S;
   plan->lx = lx;
   plan->nw = nw;
+  plan->early = early;
   plan->lds = xs_bytes + (size_t)list_cap * 4;
   return AF_OK;
 }
@@ -203,11 +220,11 @@ int af_launch_gemv_f16(af_ctx* ctx, const af_gemv_args& a) {
   plan.p.prof = af_prof_take(ctx);
   dim3 grid(plan.tiles, plan.S);
   if (plan.lx == 64)
-    launch_lx<64>(plan.nw, grid, plan.lds, ctx->stream, plan.p);
+    launch_lx<64>(plan.nw, plan.early, grid, plan.lds, ctx->stream, plan.p);
   else if (plan.lx == 32)
-    launch_lx<32>(plan.nw, grid, plan.lds, ctx->stream, plan.p);
+    launch_lx<32>(plan.nw, plan.early, grid, plan.lds, ctx->stream, plan.p);
   else
-    launch_lx<16>(plan.nw, grid, plan.lds, ctx->stream, plan.p);
+    launch_lx<16>(plan.nw, plan.early, grid, plan.lds, ctx->stream, plan.p);
   AF_LAUNCH_CHECK();
   return AF_OK;
 }

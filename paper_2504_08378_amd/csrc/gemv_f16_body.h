@@ -2,6 +2,8 @@
 // operation C), shared by the stand-alone kernel (gemv_f16.hip) and the whole-layer kernel
 // (layer.hip).  See gemv_f16.hip for the decomposition.
 #pragma once
+#include <type_traits>
+
 #include "af_internal.h"
 #include "row_prologue.h"
 
@@ -115,6 +117,7 @@ __device__ __forceinline__ void store_out(const GemvParams& p, int col, float v,
 struct GemvPlan {
   GemvParams p;
   int tiles, S, lx, nw;
+  int early;  // gemv_early_class of the launch
   size_t lds;
 };
 // whole_layer: the operator runs as a phase of the whole-layer kernel (1024-thread workgroups,
@@ -135,9 +138,18 @@ struct GemvLds {
   typename RowPrologue<NW * AF_WAVE>::Smem rp;
   int last;
 };
+// ... and the kernels that request rows early
+template <int NW, int TWMAX, int CAP>
+struct GemvEarlyLds : GemvLds<NW, TWMAX> {
+  typename RowPrologue<NW * AF_WAVE>::Early early;
+  unsigned early_row[NW][CAP];
+};
 
 // PHASE: the operator is a phase of the whole-layer kernel (p.done is set).
-template <int LX, int U, int NW, bool ROUTED, bool PHASE, typename LDS_T>
+// EARLY (top-k launches of 1024-thread workgroups): the rows whose selection is obvious are
+// requested before the front end runs (RowPrologue, "early rows").  EARLY is the number of
+// vectors of the operator's source that one thread holds (1, 4 or 8; 0: no early rows).
+template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, typename LDS_T>
 __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos vb,
                                               unsigned short* xs, LDS_T& lds) {
   constexpr int GEMV_THREADS = NW * AF_WAVE;
@@ -192,9 +204,11 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
         wr[e] = *reinterpret_cast<const half8*>(p.router_Wr + (size_t)e * r.n + (size_t)tid * 8);
     }
   }
+  if constexpr (!EARLY) {
   if (p.use_lds_x() && (!p.range_sel() || routed))
     RP::produce(r, xs, s_rp, s == 0, vb.bx, vb.gx,
                 r.sel == AF_SEL_TOPK ? s_scratch : nullptr);
+  }
   if constexpr (routed) {
     RP::template router_in_lds<RE>(xs, r.n, s_rp, wr, p.router_E, p.router_top);
     if (vb.bx == 0 && s == 0) {
@@ -215,6 +229,72 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   else if (p.w_sel)
     wcol += (size_t)p.w_sel[slot] * (size_t)p.w_stride;
 
+  // Early rows: UE batches of LY rows per wave, half of them requested behind the loads of the
+  // operator's source and before anything waits for the front end, half once x is in LDS.  Four
+  // batches are 64 KB per compute unit, about what it can have in flight: with all eight at the
+  // head the waves stalled on the requests themselves (q|k|v of the 7B shape: the last wave got
+  // its eighth request out 2.3 us after its first) and held up the front end.
+  // The narrowest tiles (four rows a batch) get by with four.
+  constexpr int UE = EARLY ? (LX == 16 ? 4 : 8) : 1;
+  half8 ew[UE];
+#pragma unroll
+  for (int u = 0; u < UE; ++u)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) ew[u][c] = (half_t)0;
+  int early_n = 0;
+  bool early_pending = false;
+  typename RP::EarlyWave early;
+  if constexpr (EARLY) {
+    early = RP::early_block(r.n, S, s);
+    half_t ea, eb;
+    RP::early_load(r, early, &ea, &eb);
+    typename RP::template Raw<EARLY> raw;
+    RP::template load_raw<EARLY>(r, raw);
+    RP::zero_hist(s_scratch);
+    // The source is in registers before the first row load goes out: otherwise the compiler,
+    // which tracks the masked loads above with one counter, would make the front end wait for
+    // the rows as well.  (For the same reason the number of vectors is a template argument and
+    // not a branch.)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    unsigned* row = lds.early_row[wave];
+    early_n = RP::template early_pick<UE * LY>(r, early, row, ea, eb);
+    // A missing row is read as the wave's last one, or as row 0: no branch around the loads.
+    auto request = [&](auto from) __attribute__((always_inline)) {
+      constexpr int U0 = decltype(from)::value;
+      unsigned e[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) e[u] = row[max(min((U0 + u) * LY + ly, early_n - 1), 0)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned j = early_n > 0 ? e[u] : 0u;
+        ew[U0 + u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)j * p.ld));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    request(std::integral_constant<int, 0>{});
+    RP::template produce_raw<EARLY>(r, raw, xs, s_rp, s == 0, vb.bx, vb.gx, s_scratch);
+    if constexpr (UE == 8) {
+      if (early_n > 4 * LY) request(std::integral_constant<int, 4>{});
+    }
+    early_pending = true;
+  }
+  // products of the early rows; called with the first batch of listed rows already requested
+  auto take_early = [&]() __attribute__((always_inline)) {
+    if constexpr (EARLY) {
+      early_pending = false;
+#pragma unroll
+      for (int u = 0; u < UE; ++u) {
+        const int i = u * LY + ly;
+        const unsigned e = lds.early_row[wave][max(min(i, early_n - 1), 0)];
+        if (i < early_n && (early.kept >> (e - (unsigned)early.lo)) & 1ull) {
+          const float xv = (float)__builtin_bit_cast(half_t, xs[e]);
+#pragma unroll
+          for (int c = 0; c < 8; ++c) acc[c] += (float)ew[u][c] * xv;
+        }
+      }
+    }
+  };
+
   // One pass over `cnt` staged rows of s_list.
   auto stream = [&](int cnt) {
     int i = wave * LY + ly;
@@ -230,6 +310,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       // scheduler has, in some instantiations, paired every load with its own wait (one row in
       // flight instead of U), which halves the streaming rate.
       __builtin_amdgcn_sched_barrier(0);
+      if (EARLY && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -254,6 +335,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
           for (int c = 0; c < 8; ++c) w[u][c] = (half_t)0;
         }
       }
+      if (EARLY && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -263,7 +345,10 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     }
   };
 
-  if (p.range_sel()) {
+  if constexpr (EARLY) {
+    stream(RP::select_range(r, xs, s_scratch, s_rp, lds.early, early, s_list, vb.bx == 0, vb.bx == 0 && s == 0));
+    if (early_pending) take_early();
+  } else if (p.range_sel()) {
     stream(routed ? RP::threshold_range_of_full(r, xs, s_rp, s_list, S, s)
                   : RP::threshold_range(r, xs, s_rp, s_list, S, s, vb.bx == 0));
   } else if (r.sel != AF_ROWS_GIVEN) {
@@ -381,13 +466,14 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
 // (kind: 0 rows given, 1 top-k, 2 threshold with an index list, 3 threshold per channel range).
 // A kernel instantiated for one mode carries none of the other modes' code and branches, which
 // measured 0.4-0.5 us per launch (q|k|v 16.7 -> 16.3 us, gate|up 23.5 -> 23.0 us); mode -1 is
-// the generic kernel that reads both from its arguments.
+// the generic kernel that reads both from its arguments.  Top-k modes carry the width class of
+// their input (gemv_early_class) in bits 4 and 5.
 #define GEMV_MODE(pro, kind) ((pro) | ((kind) << 2))
 template <int MODE>
 __device__ __forceinline__ GemvParams gemv_fix_mode(const GemvParams& p) {
   GemvParams q = p;
   if constexpr (MODE >= 0) {
-    constexpr int pro = MODE & 3, kind = MODE >> 2;
+    constexpr int pro = MODE & 3, kind = (MODE >> 2) & 3;
     q.rows.pro = pro;
     q.rows.sel = kind == 0 ? (int)AF_ROWS_GIVEN : (kind == 1 ? (int)AF_SEL_TOPK : (int)AF_SEL_THRESHOLD);
     q.flags = (p.flags & ~(GEMV_F_LDS_X | GEMV_F_RANGE_SEL)) |
@@ -401,17 +487,40 @@ static inline int gemv_mode_of(const GemvParams& p) {
   return GEMV_MODE(p.rows.pro, kind);
 }
 
+// Do the launches of this instantiation request rows early?  (A router's launch does not know its
+// matrix before its front end has run.)
+constexpr int gemv_early(int mode, int nw, bool routed) {
+  constexpr int vectors[4] = {1, 4, 8, 0};
+  return mode >= 0 && ((mode >> 2) & 3) == 1 && nw == 16 && !routed ? vectors[mode >> 4] : 0;
+}
+enum { GEMV_EARLY_NONE = 3 };
+// Which of them: inputs of up to 4096, 16384 and AF_MAX_N channels; none where the
+// `bytes` that a workgroup streams are few: looking for the rows costs 0.4-0.5 us, which a short
+// stream does not give back.  Measured at 50 % without / with early rows: 2048 -> 2048 (22 KB a
+// workgroup) 9.27 / 9.73 us, 4096 -> 4096 (87 KB) 9.83 / 10.02, 4096 -> 12288 (210 KB) 14.86 /
+// 14.46, 4096 -> 22016 (520 KB) 20.60 / 19.61; wider inputs have a longer front end to hide behind:
+// 12000 -> 504 (85 KB) 13.06 / 12.22, 11008 -> 4096 at 80 % (70 KB) 12.56 / 11.86 and at 50 % (200 KB)
+// 16.53 / 14.81, 8192 -> 10240 (350 KB) 21.71 / 18.91.  (The splits are channel ranges then: a vector
+// whose kept channels all lie together loads one split's workgroups with most of the rows, as it
+// does in the threshold form.)
+static inline int gemv_early_class(int n, long long bytes) {
+  if (bytes < (n <= 4096 ? 96 : 64) * 1024) return GEMV_EARLY_NONE;
+  return n <= RP_EV * 1024 ? 0 : (n <= 4 * RP_EV * 1024 ? 1 : 2);
+}
+static_assert(8 * RP_EV * 1024 >= AF_MAX_N, "the widest input fits the largest class");
+
 // ROUTED: the instantiation that runs a mixture-of-experts router in its front end (kept apart
 // so that the plain launches do not carry its registers).
 template <int LX, int U, int NW, bool ROUTED, int MODE = -1>
 __global__ __launch_bounds__(NW * AF_WAVE) void gemv_f16_kernel(GemvParams p) {
   extern __shared__ __align__(16) unsigned short xs[];  // the operator input, when built here
-  __shared__ GemvLds<NW, LX * 8> lds;
+  constexpr int EARLY = gemv_early(MODE, NW, ROUTED);
+  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, (LX == 16 ? 4 : 8) * AF_WAVE / LX>, GemvLds<NW, LX * 8>> lds;
   const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y};
   if constexpr (MODE >= 0) {
     const GemvParams q = gemv_fix_mode<MODE>(p);
-    gemv_f16_body<LX, U, NW, ROUTED, false>(q, vb, xs, lds);
+    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(q, vb, xs, lds);
   } else {
-    gemv_f16_body<LX, U, NW, ROUTED, false>(p, vb, xs, lds);
+    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(p, vb, xs, lds);
   }
 }

@@ -686,7 +686,7 @@ __device__ __forceinline__ bool layer_gemv_phase(const LayerParams& P, int w, un
   }
   const GemvPos vb = {w % tiles, w / tiles, tiles, S};
   const GemvParams g = P.g[OP];  // a copy of its own: the fields settle in scalar registers
-  gemv_f16_body<LX, 8, LAYER_WAVES, false, true>(g, vb, xs, lds);
+  gemv_f16_body<LX, 8, LAYER_WAVES, false, true, false>(g, vb, xs, lds);
   __syncthreads();  // the next phase reuses the workgroup's LDS
   return true;
 }

@@ -468,6 +468,261 @@ struct RowPrologue {
     __syncthreads();
   }
 
+  // ---- early rows ---------------------------------------------------------------------------
+  // A top-k front end is some 4 us in which memory is idle.  Most of the rows it will keep are
+  // obvious before it has run: a wave looks at (up to 64, one per lane) channels of its own, takes
+  // the largest of them and requests their rows before the front end starts, so that they arrive
+  // behind it.  A row taken early that the exact selection then does not keep is dropped (its
+  // products are not formed); the selection lists the rows that were not taken.  Splits are
+  // contiguous channel ranges here (as in threshold_range), because a wave has to know its rows'
+  // owner beforehand, and a wave lists the channels that it looked at, so what was taken and what
+  // is dropped stays in its own registers.
+  struct Early {
+    uint4 tot[WAVES];  // per-wave counts of the selection
+    unsigned ties[WAVES];
+  };
+  struct EarlyWave {            // uniform over the wave
+    int lo, width;              // first channel and number of channels of this wave's block
+    int n_below;                // channels below the workgroup's range
+    unsigned long long taken;   // bit l: channel lo + l was taken
+    unsigned long long kept;    // bit l: channel lo + l is kept by the selection
+  };
+  template <int B>
+  struct Raw {  // one thread's share of the operator's source: NONE x; RMSNORM hidden, gain; SILUMUL gate, up
+    rp_half a[B], b[B];
+  };
+
+  // The block of this wave: range of split s, cut evenly over the waves.
+  static __device__ __forceinline__ EarlyWave early_block(int n, int S, int s) {
+    const int nvec = n / RP_EV, V = af_ceil_div_small(nvec, S);
+    const int c0 = min(s * V, nvec) * RP_EV, c1 = min(c0 + V * RP_EV, n);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int bw = (c1 - c0 + WAVES - 1) / WAVES;
+    EarlyWave ew;
+    ew.n_below = c0;
+    ew.lo = min(c0 + wave * bw, c1);
+    ew.width = min(ew.lo + bw, c1) - ew.lo;
+    ew.taken = ew.kept = 0;
+    return ew;
+  }
+
+  static __device__ __forceinline__ float silu_mul(float g, float u) {
+    return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+  }
+
+  // All of the thread's source loads, in flight together (n <= RP_EV * B * THREADS).
+  template <int B>
+  static __device__ __forceinline__ void load_raw(const af_row_src& r, Raw<B>& raw) {
+    const int nvec = r.n / RP_EV;
+    const rp_half* a = reinterpret_cast<const rp_half*>(r.src);
+    const rp_half* b = reinterpret_cast<const rp_half*>(r.pro == AF_PRO_RMSNORM ? r.gain : r.src + r.n);
+    rp_half zero;
+#pragma unroll
+    for (int c = 0; c < RP_EV; ++c) zero[c] = (half_t)0;
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int v = threadIdx.x + u * THREADS;
+      raw.a[u] = v < nvec ? a[v] : zero;
+      if (r.pro != AF_PRO_NONE) raw.b[u] = v < nvec ? b[v] : zero;
+    }
+  }
+
+  // x into xs and the first digit's histogram into `hist` (zeroed by the caller), from the loaded
+  // source; the arithmetic is produce()'s.  The caller barriers between zeroing and this call.
+  template <int B>
+  static __device__ __forceinline__ void produce_raw(const af_row_src& r, Raw<B>& raw, unsigned short* xs,
+                                                     Smem& sm, bool store_x, int store_phase,
+                                                     int store_stride, unsigned* hist) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nvec = r.n / RP_EV;
+    rp_half* xv = reinterpret_cast<rp_half*>(xs);
+    float scale = 1.f;
+    if (r.pro == AF_PRO_RMSNORM) {
+      float ss = 0.f;
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+#pragma unroll
+        for (int c = 0; c < RP_EV; ++c) ss += (float)raw.a[u][c] * (float)raw.a[u][c];
+      ss = af_wave_sum(ss);
+      if (lane == 0) sm.red[wave] = ss;
+    }
+    __syncthreads();  // the norm's partial sums, and the zeroed histogram
+    if (r.pro == AF_PRO_RMSNORM) {
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) tot += sm.red[w];
+      scale = 1.0f / sqrtf(tot / (float)r.n + r.eps);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int v = tid + u * THREADS;
+      if (v < nvec) {
+        rp_half h = raw.a[u];
+#pragma unroll
+        for (int c = 0; c < RP_EV; ++c) {
+          if (r.pro == AF_PRO_RMSNORM) h[c] = (half_t)((float)h[c] * scale * (float)raw.b[u][c]);
+          if (r.pro == AF_PRO_SILUMUL) h[c] = (half_t)silu_mul((float)h[c], (float)raw.b[u][c]);
+        }
+        xv[v] = h;
+        count_digit1(hist, h);
+      }
+    }
+    __syncthreads();
+    if (store_x && r.x_out != nullptr) {
+      rp_half* dst = reinterpret_cast<rp_half*>(r.x_out);
+      for (int v = store_phase * THREADS + tid; v < nvec; v += store_stride * THREADS) dst[v] = xv[v];
+    }
+  }
+
+  // The two source values of this lane's channel.
+  static __device__ __forceinline__ void early_load(const af_row_src& r, const EarlyWave& ew, half_t* a,
+                                                    half_t* b) {
+    const int lane = threadIdx.x & 63;
+    const int j = min(ew.lo + min(lane, max(ew.width - 1, 0)), r.n - 1);
+    *a = r.src[j];
+    *b = r.pro == AF_PRO_NONE ? (half_t)1 : (r.pro == AF_PRO_RMSNORM ? r.gain[j] : r.src[r.n + j]);
+  }
+
+  // Choose at most CAP of the wave's first 64 channels; row[0..count) gets their numbers.  The
+  // magnitude is the producer's up to the norm's common factor.  The cut is the largest value of
+  // the key's exponent and first mantissa bit that at least `want` of the channels reach: one
+  // compare, ballot and population count per bit.  want is at most 3/4 of the channels that are
+  // kept on average, so that what the cut lets in lies above the k-th magnitude almost always.
+  template <int CAP>
+  static __device__ __forceinline__ int early_pick(const af_row_src& r, EarlyWave& ew, unsigned* row, half_t a,
+                                                   half_t b) {
+    const int lane = threadIdx.x & 63;
+    const float x = r.pro == AF_PRO_SILUMUL ? silu_mul((float)a, (float)b) : (float)a * (float)b;
+    const int looked = min(ew.width, AF_WAVE);
+    const unsigned key = lane < looked ? __builtin_bit_cast(unsigned short, (half_t)x) & 0x7FFFu : 0u;
+    const int share = (int)((float)looked * 0.75f * (float)r.k * __builtin_amdgcn_rcpf((float)r.n));
+    const int want = min(CAP, share);
+    unsigned T = 0;
+#pragma unroll
+    for (int bit = 14; bit >= 9; --bit) {
+      const unsigned t = T | (1u << bit);
+      if (__popcll(__ballot(key >= t)) >= want) T = t;
+    }
+    const unsigned long long cand = want > 0 ? __ballot(key >= T && lane < looked) : 0ull;
+    const int rank = (int)lanes_below(cand);
+    const bool mine = ((cand >> lane) & 1ull) && rank < CAP;
+    ew.taken = __ballot(mine);
+    if (mine) row[rank] = (unsigned)(ew.lo + lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // row[] is read by the other lanes of this wave
+    __builtin_amdgcn_wave_barrier();
+    return __popcll(ew.taken);
+  }
+
+  // Exact top-k over xs (first digit already counted in `hist`), restricted to this split's
+  // range: list[] gets the range's kept channels that were not taken early, first those above
+  // the k-th magnitude, then the ties, each in ascending order; returns their number.  ew.kept
+  // tells which of the wave's first 64 channels are kept.  store_idx: the range's part of the
+  // ascending index list goes to r.idx_out.
+  static __device__ __forceinline__ int select_range(const af_row_src& r, const unsigned short* xs,
+                                                     unsigned* hist, Smem& sm, Early& el, EarlyWave& ew,
+                                                     unsigned* list, bool store_idx, bool store_count) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nvec = r.n / RP_EV;
+    const rp_u16* xv = reinterpret_cast<const rp_u16*>(xs);
+    const int rep = lane & (RP_HIST_COPIES - 1);
+    int T = 0x8000;
+    unsigned quota = 0;
+    if (r.k > 0) {
+      find_digit(hist + H1, sm, 256, (unsigned)r.k);
+      const unsigned d1 = sm.digit, above1 = sm.above;
+      for (int v = tid; v < nvec; v += THREADS) {
+        const rp_u16 b = xv[v];
+#pragma unroll
+        for (int c = 0; c < RP_EV; ++c) {
+          const unsigned key = b[c] & 0x7FFFu;
+          if ((key >> 7) == d1) atomicAdd(&hist[H2 + rep * 128 + (key & 127u)], 1u);
+        }
+      }
+      __syncthreads();
+      find_digit(hist + H2, sm, 128, (unsigned)r.k - above1);
+      T = (int)((d1 << 7) | sm.digit);
+      quota = (unsigned)r.k - above1 - sm.above;
+    }
+    // counts below the range (above T | at T << 16)
+    unsigned below = 0;
+    for (int v = tid; v < ew.n_below / RP_EV; v += THREADS) {
+      const rp_u16 b = xv[v];
+#pragma unroll
+      for (int c = 0; c < RP_EV; ++c) {
+        const int key = b[c] & 0x7FFFu;
+        below += (unsigned)(key > T) + ((unsigned)(key == T) << 16);
+      }
+    }
+    below = af_wave_sum(below);
+    // ... of the wave's block, and of its channels that are still open (not taken)
+    const int passes = (ew.width + AF_WAVE - 1) / AF_WAVE;
+    unsigned run = 0, open = 0;
+    auto look = [&](int i, unsigned* bits, unsigned long long* gt, unsigned long long* eq) {
+      const int l = i * AF_WAVE + lane;
+      *bits = l < ew.width ? xs[ew.lo + l] : 0u;
+      const int key = (int)(*bits & 0x7FFFu);
+      *gt = __ballot(l < ew.width && key > T);
+      *eq = __ballot(l < ew.width && key == T);
+    };
+    for (int i = 0; i < passes; ++i) {
+      unsigned bits;
+      unsigned long long gt, eq;
+      look(i, &bits, &gt, &eq);
+      const unsigned long long free = i == 0 ? ~ew.taken : ~0ull;
+      run += (unsigned)__popcll(gt) + ((unsigned)__popcll(eq) << 16);
+      open += (unsigned)__popcll(gt & free) + ((unsigned)__popcll(eq & free) << 16);
+    }
+    if (lane == 0) el.tot[wave] = make_uint4(run, open, below, 0u);
+    __syncthreads();
+    // every wave scans the (at most 16) wave counts on its own lanes
+    static_assert(WAVES <= 16, "one row of lanes");
+    const uint4 wt = el.tot[lane % WAVES];
+    const unsigned run_s = af_row_incl_scan(wt.x), open_s = af_row_incl_scan(wt.y), below_s = af_row_incl_scan(wt.z);
+    const unsigned run_pre = (unsigned)__builtin_amdgcn_readlane((int)run_s, wave) - run;
+    const unsigned open_pre = (unsigned)__builtin_amdgcn_readlane((int)open_s, wave) - open;
+    const unsigned open_all = (unsigned)__builtin_amdgcn_readlane((int)open_s, WAVES - 1);
+    const unsigned below_all = (unsigned)__builtin_amdgcn_readlane((int)below_s, WAVES - 1);
+    const unsigned eq_below = min(below_all >> 16, quota), gt_below = below_all & 0xFFFFu;
+    const unsigned quota_r = quota - eq_below;  // ties this range may keep
+    const unsigned n_gt = open_all & 0xFFFFu;   // ties are listed behind these
+    const bool to_mem = store_idx && r.idx_out != nullptr;
+    unsigned gt_rank = run_pre & 0xFFFFu, eq_rank = run_pre >> 16;
+    unsigned gt_pos = open_pre & 0xFFFFu, eq_pos = open_pre >> 16, ties = 0;
+    for (int i = 0; i < passes; ++i) {
+      unsigned bits;
+      unsigned long long gt, eq;
+      look(i, &bits, &gt, &eq);
+      const unsigned long long free = i == 0 ? ~ew.taken : ~0ull;
+      // the first quota_r ties of the range are kept
+      const unsigned my_eq = eq_rank + lanes_below(eq);
+      const unsigned long long keq = __ballot(((eq >> lane) & 1ull) && my_eq < quota_r);
+      if (i == 0) ew.kept = gt | keq;
+      const unsigned entry = ((unsigned)(ew.lo + i * AF_WAVE + lane) << 16) | bits;
+      if (((gt & free) >> lane) & 1ull) list[gt_pos + lanes_below(gt & free)] = entry;
+      if (((keq & free) >> lane) & 1ull) list[n_gt + eq_pos + lanes_below(keq & free)] = entry;
+      if (to_mem && (((gt | keq) >> lane) & 1ull))
+        r.idx_out[gt_below + eq_below + gt_rank + lanes_below(gt) + min(my_eq, quota_r)] =
+            ew.lo + i * AF_WAVE + lane;
+      gt_rank += (unsigned)__popcll(gt);
+      eq_rank += (unsigned)__popcll(eq);
+      gt_pos += (unsigned)__popcll(gt & free);
+      eq_pos += (unsigned)__popcll(eq & free);
+      ties += (unsigned)__popcll(keq & free);
+    }
+    if (lane == 0) el.ties[wave] = ties;
+    if (store_count && r.count_out != nullptr && tid == 0) *r.count_out = r.k;
+    __syncthreads();
+    const unsigned all_ties = (unsigned)__builtin_amdgcn_readlane(
+        (int)af_row_incl_scan(el.ties[lane % WAVES]), WAVES - 1);
+    return (int)(n_gt + all_ties);
+  }
+
+  // number of set bits of m below this lane
+  static __device__ __forceinline__ unsigned lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+  }
+
   // Select on xs[0..n) (n % 8 == 0) and keep the entries of split s of S in list[] as
   // (index << 16 | fp16 bits).  Returns the number of entries kept by this workgroup;
   // *nidx_total is the size of the whole index set.  `hist` is RP_SCRATCH_WORDS words of LDS.

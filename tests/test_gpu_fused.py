@@ -288,3 +288,47 @@ def test_random_shapes_every_form(ctx, out, n, pro, keep, form):
     if pro == "none":
         assert np.array_equal(x_gpu.view(np.uint16), x_ref.view(np.uint16))
     assert O.rel_err(y, O.sparse_gemv(W, x_gpu, idx)) <= 1e-4
+
+
+# ---- rows requested before the selection has run (long top-k streams) ------------------------
+def _pattern(kind, n, rng):
+    x = rng.laplace(size=n)
+    if kind == "equal":            # every channel ties with the k-th: the first k are kept
+        x = np.where(rng.random(n) < 0.5, 1.5, -1.5)
+    elif kind == "few":            # three magnitudes, ties across all ranges
+        x = rng.choice([0.5, -1.0, 2.0], size=n)
+    elif kind == "ascending":      # everything that is kept lies in the last ranges
+        x = np.sort(np.abs(x))
+    elif kind == "descending":
+        x = -np.sort(-np.abs(x))
+    elif kind == "sparse":         # fewer non-zero channels than k
+        x = np.where(rng.random(n) < 0.2, x, 0.0)
+    return x.astype(np.float16)
+
+
+# width classes of the source (4096 / 16384 / above, and one past each), tile widths 128 / 256 / 512,
+# ragged tiles, ranges that do not divide
+@pytest.mark.parametrize("n,out,share", [(4096, 4096, 0.9), (4096, 12288, 0.5), (4096, 22016, 0.3), (4104, 8184, 0.5),
+                                         (4040, 6152, 0.97), (11008, 4096, 0.5), (16384, 2056, 0.4),
+                                         (16392, 4096, 0.5), (32768, 1032, 0.99), (8192, 10240, 1.0)])
+@pytest.mark.parametrize("kind", ["random", "equal", "few", "ascending", "descending", "sparse"])
+def test_early_rows_are_exactly_the_kept_ones(ctx, n, out, share, kind):
+    rng = np.random.default_rng(n + out)
+    x, k = _pattern(kind, n, rng), int(n * share)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Wt = (torch.randn((n, out), generator=g, device="cuda") * 0.02).half()
+    ref_idx = O.select_topk(x, k)
+    # a channel that is not kept must not be touched by its weights either
+    dropped = np.setdiff1d(np.arange(n), ref_idx)
+    if len(dropped):
+        Wt[torch.from_numpy(dropped).cuda()] = float("inf")
+    y, xo, idx, c = _run(ctx, Wt, to_dev(x), n, sel_mode=B.AF_SEL_TOPK, k=k, y_kind=B.AF_F32)
+    assert c == k and np.array_equal(idx, ref_idx)
+    assert np.array_equal(xo.view(np.uint16), x.view(np.uint16))
+    rows = torch.from_numpy(ref_idx.astype(np.int64)).cuda()
+    xs = torch.from_numpy(x[ref_idx].astype(np.float64)).cuda()
+    ref = (Wt[rows].double() * xs[:, None]).sum(0).cpu().numpy()
+    assert O.rel_err(y, ref) <= 1e-4  # the bound of the fp32 results above
+    y2, *_ = _run(ctx, Wt, to_dev(x), n, sel_mode=B.AF_SEL_TOPK, k=k, y_kind=B.AF_F32)
+    assert np.array_equal(y, y2)      # the order of the sums is fixed
