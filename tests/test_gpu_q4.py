@@ -176,3 +176,48 @@ def test_q4_random_shapes_both_layouts(ctx, out, n, k, cl):
         ref = O.sparse_gemv_q4(nib, s, x, idx)
     ctx.synchronize()
     assert O.rel_err(to_host(y), ref) <= 1e-4
+
+
+def _pack_reference(W, axis_groups):
+    """codes (out, in) as the quantiser's definition gives them for any fp16 value: fp32 quotient, ties
+    to even, NaN to -7; groups of 32 along the given axis."""
+    w = W.astype(np.float32)
+    g = w.reshape(w.shape[0], -1, 32) if axis_groups == 1 else w.reshape(-1, 32, w.shape[1])
+    ax = 2 if axis_groups == 1 else 1
+    amax = np.nanmax(np.where(np.isnan(g), 0.0, np.abs(g)), axis=ax, keepdims=True)
+    s = (amax / np.float32(7)).astype(np.float16)
+    with np.errstate(all="ignore"):
+        q = np.rint((g / s.astype(np.float32)).astype(np.float32))
+    q = np.where(np.isnan(q), -7, np.clip(q, -7, 7))
+    q = np.where(s == 0, 0, q)
+    return q.reshape(w.shape).astype(np.int64), np.squeeze(s, ax)
+
+
+# ragged tiles of both axes, pointers that allow the wide accesses and pointers that do not
+@pytest.mark.parametrize("out,n,shift", [(8, 32, 0), (256, 64, 0), (264, 96, 0), (520, 4064, 0), (264, 96, 1), (1032, 160, 1)])
+@pytest.mark.parametrize("layout", ["g32", "cl"])
+def test_pack_edges_ties_and_special_values(ctx, out, n, shift, layout):
+    import torch
+    if layout == "cl":
+        out = (out + 31) // 32 * 32
+    rng = np.random.default_rng(out + n)
+    W = (rng.integers(-14, 15, (out, n)) * 0.5).astype(np.float16)      # quotients k + 1/2 at scale 1
+    W[:, ::32] = 7
+    W[: out // 2] = (rng.standard_normal((out // 2, n)) * 0.02).astype(np.float16)
+    W[1, 3], W[2, 5], W[4, 8] = np.inf, np.nan, -np.inf
+    W[5] = 0
+    W[6, :32] = np.float16(6e-8)
+    flat = torch.zeros(out * n + shift, dtype=torch.float16, device="cuda")
+    Wd = flat[shift:].view(out, n)
+    Wd.copy_(to_dev(W))
+    packed = torch.zeros(n * (out // 2) + shift, dtype=torch.uint8, device="cuda")[shift:].view(n, out // 2)
+    rows = (n, out // 32) if layout == "cl" else (n // 32, out)
+    scales = torch.zeros(rows[0] * rows[1] + shift, dtype=torch.float16, device="cuda")[shift:].view(*rows)
+    torch.cuda.synchronize()
+    (ctx.pack_q4_cl if layout == "cl" else ctx.pack_q4_g32)(Wd, packed, scales)
+    ctx.synchronize()
+    q, s = _pack_reference(W, 0 if layout == "cl" else 1)
+    b = to_host(packed)
+    got = np.stack([b & 15, b >> 4], axis=2).reshape(n, out).T.astype(np.int64) - 8
+    assert np.array_equal(got, q)
+    assert np.array_equal(to_host(scales).view(np.uint16), s.T.view(np.uint16))
