@@ -92,6 +92,9 @@ extern "C" int af_set_option(af_ctx* ctx, int option, int value) {
     case AF_OPT_TUNE_ATTN_SPLITS:
       ctx->tune_attn_splits = value;
       return AF_OK;
+    case AF_OPT_TUNE_EARLY_ROWS:
+      ctx->tune_early_rows = value;
+      return AF_OK;
     default:
       return AF_EINVAL;
   }

@@ -169,12 +169,15 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   int early = GEMV_EARLY_NONE;
   if (r.sel == AF_SEL_TOPK && nw == 16 && !whole_layer && !a.router_Wr) {
     int s_early = S;
-    early = gemv_early_class(r.n, (long long)r.k / S * tw * 2);
+    early = ctx->tune_early_rows == 1   ? (int)GEMV_EARLY_NONE
+            : ctx->tune_early_rows == 2 ? gemv_width_class(r.n)
+                                        : gemv_early_class(r.n, (long long)r.k / S * tw * 2);
     if (early != GEMV_EARLY_NONE &&
         (!af_plan_gemv_lds(r, max_rows, use_lds_x, false, GEMV_LIST, &s_early, &xs_bytes, &list_cap, false, true) ||
          s_early != S))
       early = GEMV_EARLY_NONE;
   }
+  if (ctx->tune_early_rows == 2 && r.sel == AF_SEL_TOPK && early == GEMV_EARLY_NONE) return AF_EINVAL;
   if (early == GEMV_EARLY_NONE && !af_plan_gemv_lds(r, max_rows, use_lds_x, range_sel, GEMV_LIST, &S, &xs_bytes,
                                                     &list_cap, a.router_Wr != nullptr))
     return AF_EWORKSPACE;

@@ -332,3 +332,29 @@ def test_early_rows_are_exactly_the_kept_ones(ctx, n, out, share, kind):
     assert O.rel_err(y, ref) <= 1e-4  # the bound of the fp32 results above
     y2, *_ = _run(ctx, Wt, to_dev(x), n, sel_mode=B.AF_SEL_TOPK, k=k, y_kind=B.AF_F32)
     assert np.array_equal(y, y2)      # the order of the sums is fixed
+
+
+@pytest.mark.parametrize("n,out,share", [(4096, 12288, 0.5), (4096, 22016, 0.7), (8192, 10240, 0.5)])
+def test_early_rows_lose_no_precision(ctx, n, out, share):
+    """fp32 results against 64 bits, with and without early rows.  Different orders of the same sums:
+    the mean over eight inputs of thousands of columns each settles to about 1 %; the early rows in
+    the same running sum as the rest measured 4 to 15 % worse."""
+    k = int(n * share)
+    err = {1: [], 2: []}
+    g = torch.Generator(device="cuda")
+    for seed in range(8):
+        g.manual_seed(seed)
+        W = (torch.randn((n, out), generator=g, device="cuda") * 0.02).half()
+        x = to_dev(S.activation(seed, S.channel_scales(seed, n, "fused"), "fused", 0))
+        kept = torch.sort(x.float().abs(), descending=True, stable=True).indices[:k]
+        ref = (W[kept].double() * x[kept].double()[:, None]).sum(0)
+        torch.cuda.synchronize()
+        for early in err:
+            ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, early)
+            try:
+                y = ctx.select_gemv_f16(W, x, sel_mode=B.AF_SEL_TOPK, k=k, y_kind=B.AF_F32)
+            finally:
+                ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
+            ctx.synchronize()
+            err[early].append(float((y.double() - ref).norm() / ref.norm()))
+    assert np.mean(err[2]) <= 1.02 * np.mean(err[1]), err
