@@ -98,10 +98,13 @@ struct af_row_src {
 // selects keeps its whole share of the rows staged, so the share has to fit: *S (the number
 // of row splits) is raised until it does.  Rows given by the caller are staged `chunk` at a
 // time instead.  Returns false if nothing fits.
+#ifndef AF_DEAL
+#define AF_DEAL 16  // channels dealt together (af_dealt_channel)
+#endif
 #define AF_GEMV_LDS_BUDGET (120u * 1024u)  // leaves room for the kernels' static LDS in 160 KB
 static inline bool af_plan_gemv_lds(const af_row_src& r, int max_rows, bool use_lds_x,
                                     bool range_sel, int chunk, int* S, size_t* xs_bytes,
-                                    int* list_cap, bool full_x = false, bool by_range = false) {
+                                    int* list_cap, bool full_x = false, bool dealt = false) {
   for (int s = *S < 1 ? 1 : *S; s <= 4096; ++s) {
     size_t xb;
     int cap;
@@ -110,8 +113,8 @@ static inline bool af_plan_gemv_lds(const af_row_src& r, int max_rows, bool use_
       xb = full_x ? (size_t)r.n * 2 : (size_t)cap * 2;  // an in-kernel router wants all of x
     } else if (r.sel != AF_ROWS_GIVEN) {
       cap = (max_rows + s - 1) / s;
-      if (by_range) {  // all kept channels may lie in one range
-        const int range = 8 * ((r.n / 8 + s - 1) / s);
+      if (dealt) {  // all of the split's channels may be kept
+        const int range = AF_DEAL * (((r.n + AF_DEAL - 1) / AF_DEAL + s - 1) / s);
         cap = range < max_rows ? range : max_rows;
       }
       xb = (size_t)r.n * 2;
@@ -264,6 +267,26 @@ __device__ __forceinline__ int af_ceil_div_small(int a, int s) {
   q += (r >= s) - (r < 0);
   return q;
 }
+
+// Channels dealt to the splits of a launch: groups of AF_DEAL channels, in cycles of S groups, of
+// which every split has one.  Wave w takes the cycles from af_dealt_cycle(w) to that of w + 1, so
+// that wave w of every split lies in the same stretch of the vector; this is channel l of the wave
+// of split s that starts with cycle q0 (ascending in l and w; may lie past the vector's end in the
+// last cycle).  The deal is turned from cycle to cycle by the golden ratio and from 64 channels of a
+// wave to the next by sqrt(3), so that neither a stretch of the vector nor a pattern that repeats
+// with it (the same dimensions of every head) goes to few splits.  The masks tell the compiler
+// that it may multiply in 24 bits.
+__host__ __device__ __forceinline__ int af_dealt_channel(int q0, int S, int s, int w, int l) {
+  const unsigned su = (unsigned)S & 0xFFFFu, q = (unsigned)(l / AF_DEAL) & 0xFFFFu;
+  const unsigned block = (unsigned)(w * 7 + l / 64);
+  int o = s + (int)(((block * 47974u & 0xFFFFu) * su) >> 16);
+  o -= o >= S ? S : 0;
+  o += (int)((((q & (64u / AF_DEAL - 1)) * 40503u & 0xFFFFu) * su) >> 16);
+  o -= o >= S ? S : 0;
+  return (q0 * S + (int)(q * su) + o) * AF_DEAL + l % AF_DEAL;
+}
+__host__ __device__ __forceinline__ int af_dealt_cycles(int n, int S) { return ((n + AF_DEAL - 1) / AF_DEAL + S - 1) / S; }
+__host__ __device__ __forceinline__ int af_dealt_cycle(int cycles, int w, int waves) { return w * cycles / waves; }
 
 // A load of data that is used once (weight rows): marked non-temporal so that it does not
 // displace lines that are used again; a plain streaming read of HBM measured about 10 % faster

@@ -163,8 +163,8 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   while (S > 1 && (size_t)S * out_pad > ctx->lay.partial_floats) --S;
   if (a.router_Wr && (r.pro != AF_PRO_RMSNORM || a.router_E > 8 || r.n > 8192 || nw != 16 || !use_lds_x))
     return AF_EINVAL;  // the in-kernel router's preconditions (the caller falls back to the router kernel)
-  // Early rows split by channel range, and a range lists more rows than an even share of the list
-  // can have: they are used where that fits the LDS with this S, and the launch stays as it is
+  // Early rows split by channel, and a split's channels can be more rows than an even share of the
+  // list: they are used where that fits the LDS with this S, and the launch stays as it is
   // without them where it does not.
   int early = GEMV_EARLY_NONE;
   if (r.sel == AF_SEL_TOPK && nw == 16 && !whole_layer && !a.router_Wr) {
@@ -212,6 +212,7 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   plan->lx = lx;
   plan->nw = nw;
   plan->early = early;
+  if (early != GEMV_EARLY_NONE) p.early_cycles = af_dealt_cycles(r.n, S);
   plan->lds = xs_bytes + (size_t)list_cap * 4;
   return AF_OK;
 }

@@ -29,7 +29,10 @@ struct GemvParams {
   // device are reached without a host round trip.  y_scale (device, one float) scales the
   // product before the residual is added.
   int cols_per_slot, tiles_per_slot;
-  int done_total;  // see `done` below
+  union {
+    int done_total;    // see `done` below
+    int early_cycles;  // launches with early rows (never part of a whole layer): af_dealt_cycles
+  };
   const int* w_sel;
   long long w_stride;
   const float* y_scale;
@@ -245,12 +248,13 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   bool early_pending = false;
   typename RP::EarlyWave early;
   if constexpr (EARLY) {
-    early = RP::early_block(r.n, S, s);
+    early = RP::early_block(r.n, S, s, p.early_cycles);
     half_t ea, eb;
     RP::early_load(r, early, &ea, &eb);
     typename RP::template Raw<EARLY> raw;
     RP::template load_raw<EARLY>(r, raw);
     RP::zero_hist(s_scratch);
+    if (RP::own_channels(early) > AF_WAVE) early.ch1 = RP::early_channel(early, 1, r.n);
     // The source is in registers before the first row load goes out: otherwise the compiler,
     // which tracks the masked loads above with one counter, would make the front end wait for
     // the rows as well.  (For the same reason the number of vectors is a template argument and
@@ -266,7 +270,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       for (int u = 0; u < 4; ++u) e[u] = row[max(min((U0 + u) * LY + ly, early_n - 1), 0)];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const unsigned j = early_n > 0 ? e[u] : 0u;
+        const unsigned j = early_n > 0 ? e[u] & 0xFFFFu : 0u;
         ew[U0 + u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)j * p.ld));
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -289,9 +293,9 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
 #pragma unroll
       for (int u = 0; u < UE; ++u) {
         const int i = u * LY + ly;
-        const unsigned e = lds.early_row[wave][max(min(i, early_n - 1), 0)];
-        if (i < early_n && (early.kept >> (e - (unsigned)early.lo)) & 1ull) {
-          const float xv = (float)__builtin_bit_cast(half_t, xs[e]);
+        const unsigned e = early_n > 0 ? lds.early_row[wave][min(i, early_n - 1)] : 0u;
+        if (i < early_n && (early.kept >> (e >> 16)) & 1ull) {
+          const float xv = (float)__builtin_bit_cast(half_t, xs[e & 0xFFFFu]);
 #pragma unroll
           for (int c = 0; c < 8; ++c) early_acc[c] += (float)ew[u][c] * xv;
         }
@@ -350,7 +354,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   };
 
   if constexpr (EARLY) {
-    stream(RP::select_range(r, xs, s_scratch, s_rp, lds.early, early, s_list, vb.bx == 0, vb.bx == 0 && s == 0));
+    stream(RP::select_dealt(r, xs, s_scratch, s_rp, lds.early, early, s_list, s * vb.gx + vb.bx));
     if (early_pending) take_early();
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] += early_acc[c];
@@ -431,6 +435,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
         store_out(p, out0 + c, v, res);
       }
     }
+    if constexpr (EARLY) RP::early_write_list(r, xs, early, vb.bx, vb.gx);
     af_prof_end(p.prof);
     return;
   }
@@ -442,6 +447,9 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     for (int w = 0; w < GEMV_WAVES; ++w) v += s_red[w][c];
     af_store_agent(mine + tile0 + c, v);  // out_pad covers whole tiles
   }
+  // Nothing in this launch waits for the index list: it is written while the partial sums are on
+  // their way (7B step 2.218 ms; ahead of the stream 2.222, behind it 2.226, beside the ticket 2.225).
+  if constexpr (EARLY) RP::early_write_list(r, xs, early, s * vb.gx + vb.bx, vb.gx * S);
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
@@ -506,9 +514,7 @@ enum { GEMV_EARLY_NONE = 3 };
 // workgroup) 9.27 / 9.73 us, 4096 -> 4096 (87 KB) 9.83 / 10.02, 4096 -> 12288 (210 KB) 14.86 /
 // 14.46, 4096 -> 22016 (520 KB) 20.60 / 19.61; wider inputs have a longer front end to hide behind:
 // 12000 -> 504 (85 KB) 13.06 / 12.22, 11008 -> 4096 at 80 % (70 KB) 12.56 / 11.86 and at 50 % (200 KB)
-// 16.53 / 14.81, 8192 -> 10240 (350 KB) 21.71 / 18.91.  (The splits are channel ranges then: a vector
-// whose kept channels all lie together loads one split's workgroups with most of the rows, as it
-// does in the threshold form.)
+// 16.53 / 14.81, 8192 -> 10240 (350 KB) 21.71 / 18.91.
 static inline int gemv_width_class(int n) { return n <= RP_EV * 1024 ? 0 : (n <= 4 * RP_EV * 1024 ? 1 : 2); }
 static inline int gemv_early_class(int n, long long bytes) {
   return bytes < (n <= 4096 ? 96 : 64) * 1024 ? (int)GEMV_EARLY_NONE : gemv_width_class(n);

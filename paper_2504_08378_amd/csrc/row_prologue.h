@@ -473,37 +473,86 @@ struct RowPrologue {
   // obvious before it has run: a wave looks at (up to 64, one per lane) channels of its own, takes
   // the largest of them and requests their rows before the front end starts, so that they arrive
   // behind it.  A row taken early that the exact selection then does not keep is dropped (its
-  // products are not formed); the selection lists the rows that were not taken.  Splits are
-  // contiguous channel ranges here (as in threshold_range), because a wave has to know its rows'
-  // owner beforehand, and a wave lists the channels that it looked at, so what was taken and what
-  // is dropped stays in its own registers.
+  // products are not formed); the selection lists the rows that were not taken.  A wave has to know
+  // its channels beforehand, so the channels and not the list are cut into splits: they are dealt
+  // out in small groups (af_dealt_channel), because what is kept may lie together (whole heads
+  // at the o projection).  With one contiguous range per split, half of the vector 6 times the other
+  // took 26.1 us for 4096 -> 22016 and 59.5 for 28672 -> 8192, where even inputs take 21.2 and 50.5.
+  // Wave w of every split has its groups in the same sixteenth of the vector, its stretch; it counts
+  // the ties of all of that for their ranks, so what it took stays in its own registers.
   struct Early {
-    uint4 tot[WAVES];  // per-wave counts of the selection
+    uint2 tot[WAVES];  // per-wave counts of the selection
     unsigned ties[WAVES];
   };
-  struct EarlyWave {            // uniform over the wave
-    int lo, width;              // first channel and number of channels of this wave's block
-    int n_below;                // channels below the workgroup's range
-    unsigned long long taken;   // bit l: channel lo + l was taken
-    unsigned long long kept;    // bit l: channel lo + l is kept by the selection
+  struct EarlyWave {            // uniform over the wave, but for ch
+    int cycles, q0, q1;         // of the deal, and the wave's
+    int S, s;                   // splits, and the workgroup's own
+    int ch, ch1;                // this lane's channels of the wave's first 64 and of its next, -1: none
+    unsigned long long taken;   // bit l: lane l's channel was taken
+    unsigned long long kept;    // bit l: lane l's channel is kept by the selection
+    int T, last_tie;            // kept in this wave's stretch: keys above T, at T up to this channel
+    unsigned pos, ties;         // position of the stretch in the index list, ties that may be kept in it
   };
   template <int B>
   struct Raw {  // one thread's share of the operator's source: NONE x; RMSNORM hidden, gain; SILUMUL gate, up
     rp_half a[B], b[B];
   };
 
-  // The block of this wave: range of split s, cut evenly over the waves.
-  static __device__ __forceinline__ EarlyWave early_block(int n, int S, int s) {
-    const int nvec = n / RP_EV, V = af_ceil_div_small(nvec, S);
-    const int c0 = min(s * V, nvec) * RP_EV, c1 = min(c0 + V * RP_EV, n);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int bw = (c1 - c0 + WAVES - 1) / WAVES;
+  static __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+  // This lane's channel of pass i over the wave's channels, -1: none.
+  static __device__ __forceinline__ int early_channel(const EarlyWave& ew, int i, int n) {
+    const int l = i << 6 | (int)(threadIdx.x & 63);
+    const int j = af_dealt_channel(ew.q0, ew.S, ew.s, wave_id(), l);
+    return l < own_channels(ew) && j < n ? j : -1;
+  }
+  static __device__ __forceinline__ int own_channels(const EarlyWave& ew) { return (ew.q1 - ew.q0) * AF_DEAL; }
+  // cycles: af_dealt_cycles(n, S)
+  static __device__ __forceinline__ EarlyWave early_block(int n, int S, int s, int cycles) {
     EarlyWave ew;
-    ew.n_below = c0;
-    ew.lo = min(c0 + wave * bw, c1);
-    ew.width = min(ew.lo + bw, c1) - ew.lo;
+    ew.cycles = cycles;
+    ew.q0 = af_dealt_cycle(cycles, wave_id(), WAVES);
+    ew.q1 = af_dealt_cycle(cycles, wave_id() + 1, WAVES);
+    ew.S = S;
+    ew.s = s;
+    ew.ch = early_channel(ew, 0, n);
+    ew.ch1 = -1;
     ew.taken = ew.kept = 0;
     return ew;
+  }
+  // The wave's stretch in groups of 8 channels (n % 8 == 0), and the pieces (of 32
+  // groups) of the longest stretch.
+  static constexpr int GROUP = 8;
+  static __device__ __forceinline__ int stretch_begin(const EarlyWave& ew, int n) {
+    return min(ew.q0 * ew.S * (AF_DEAL / GROUP), n / GROUP);
+  }
+  static __device__ __forceinline__ int stretch_end(const EarlyWave& ew, int n) {
+    return min(ew.q1 * ew.S * (AF_DEAL / GROUP), n / GROUP);
+  }
+  static __device__ __forceinline__ int stretch_pieces(const EarlyWave& ew) {
+    return ((ew.cycles + WAVES - 1) / WAVES * ew.S * (AF_DEAL / GROUP) + 31) / 32;
+  }
+  // Does workgroup j of the launch write any piece of the index list?
+  static __device__ __forceinline__ bool early_lists(const af_row_src& r, const EarlyWave& ew, int j) {
+    return r.idx_out != nullptr && j < stretch_pieces(ew) * WAVES;
+  }
+  // Of a group's magnitude keys, how many are T / lie above T: two keys to a word, whose sums with
+  // what is missing to 0x8000 carry into the sign bits (a compare and an addition for every key made
+  // the look at the stretch the longest part of the selection).
+  typedef unsigned group_keys __attribute__((ext_vector_type(GROUP / 2)));
+  static __device__ __forceinline__ unsigned group_at(const group_keys b, int T) {
+    const unsigned t2 = (unsigned)T | (unsigned)T << 16;
+    unsigned other = 0;
+#pragma unroll
+    for (int c = 0; c < GROUP / 2; ++c)
+      other += (unsigned)__popc((((b[c] ^ t2) & 0x7FFF7FFFu) + 0x7FFF7FFFu) & 0x80008000u);
+    return GROUP - other;
+  }
+  static __device__ __forceinline__ unsigned group_above(const group_keys b, int T) {
+    const unsigned m = 0x7FFFu - (unsigned)min(T, 0x7FFF), m2 = m | m << 16;
+    unsigned n = 0;
+#pragma unroll
+    for (int c = 0; c < GROUP / 2; ++c) n += (unsigned)__popc(((b[c] & 0x7FFF7FFFu) + m2) & 0x80008000u);
+    return n;
   }
 
   static __device__ __forceinline__ float silu_mul(float g, float u) {
@@ -577,13 +626,12 @@ struct RowPrologue {
   // The two source values of this lane's channel.
   static __device__ __forceinline__ void early_load(const af_row_src& r, const EarlyWave& ew, half_t* a,
                                                     half_t* b) {
-    const int lane = threadIdx.x & 63;
-    const int j = min(ew.lo + min(lane, max(ew.width - 1, 0)), r.n - 1);
+    const int j = max(ew.ch, 0);
     *a = r.src[j];
     *b = r.pro == AF_PRO_NONE ? (half_t)1 : (r.pro == AF_PRO_RMSNORM ? r.gain[j] : r.src[r.n + j]);
   }
 
-  // Choose at most CAP of the wave's first 64 channels; row[0..count) gets their numbers.  The
+  // Choose at most CAP of the wave's first 64 channels; row[0..count) gets (lane << 16 | channel).  The
   // magnitude is the producer's up to the norm's common factor.  The cut is the largest value of
   // the key's exponent and first mantissa bit that at least `want` of the channels reach: one
   // compare, ballot and population count per bit.  want is at most 3/4 of the channels that are
@@ -593,8 +641,8 @@ struct RowPrologue {
                                                    half_t b) {
     const int lane = threadIdx.x & 63;
     const float x = r.pro == AF_PRO_SILUMUL ? silu_mul((float)a, (float)b) : (float)a * (float)b;
-    const int looked = min(ew.width, AF_WAVE);
-    const unsigned key = lane < looked ? __builtin_bit_cast(unsigned short, (half_t)x) & 0x7FFFu : 0u;
+    const int looked = __popcll(__ballot(ew.ch >= 0));
+    const unsigned key = ew.ch >= 0 ? __builtin_bit_cast(unsigned short, (half_t)x) & 0x7FFFu : 0u;
     const int share = (int)((float)looked * 0.75f * (float)r.k * __builtin_amdgcn_rcpf((float)r.n));
     const int want = min(CAP, share);
     unsigned T = 0;
@@ -603,26 +651,25 @@ struct RowPrologue {
       const unsigned t = T | (1u << bit);
       if (__popcll(__ballot(key >= t)) >= want) T = t;
     }
-    const unsigned long long cand = want > 0 ? __ballot(key >= T && lane < looked) : 0ull;
+    const unsigned long long cand = want > 0 ? __ballot(key >= T && ew.ch >= 0) : 0ull;
     const int rank = (int)lanes_below(cand);
     const bool mine = ((cand >> lane) & 1ull) && rank < CAP;
     ew.taken = __ballot(mine);
-    if (mine) row[rank] = (unsigned)(ew.lo + lane);
+    if (mine) row[rank] = (unsigned)(lane << 16 | ew.ch);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // row[] is read by the other lanes of this wave
     __builtin_amdgcn_wave_barrier();
     return __popcll(ew.taken);
   }
 
-  // Exact top-k over xs (first digit already counted in `hist`), restricted to this split's
-  // range: list[] gets the range's kept channels that were not taken early, first those above
-  // the k-th magnitude, then the ties, each in ascending order; returns their number.  ew.kept
-  // tells which of the wave's first 64 channels are kept.  store_idx: the range's part of the
-  // ascending index list goes to r.idx_out.
-  static __device__ __forceinline__ int select_range(const af_row_src& r, const unsigned short* xs,
+  // Exact top-k over xs (first digit already counted in `hist`), restricted to the channels dealt to
+  // this split: list[] gets those that are kept and were not taken early, first those above the
+  // k-th magnitude, then the ties, each in ascending order; returns their number.  ew.kept tells
+  // which of the wave's first 64 channels are kept.  j: the workgroup's number in the launch.
+  static __device__ __forceinline__ int select_dealt(const af_row_src& r, const unsigned short* xs,
                                                      unsigned* hist, Smem& sm, Early& el, EarlyWave& ew,
-                                                     unsigned* list, bool store_idx, bool store_count) {
+                                                     unsigned* list, int j) {
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_id();
     const int nvec = r.n / RP_EV;
     const rp_u16* xv = reinterpret_cast<const rp_u16*>(xs);
     const int rep = lane & (RP_HIST_COPIES - 1);
@@ -644,80 +691,148 @@ struct RowPrologue {
       T = (int)((d1 << 7) | sm.digit);
       quota = (unsigned)r.k - above1 - sm.above;
     }
-    // counts below the range (above T | at T << 16)
-    unsigned below = 0;
-    for (int v = tid; v < ew.n_below / RP_EV; v += THREADS) {
-      const rp_u16 b = xv[v];
-#pragma unroll
-      for (int c = 0; c < RP_EV; ++c) {
-        const int key = b[c] & 0x7FFFu;
-        below += (unsigned)(key > T) + ((unsigned)(key == T) << 16);
-      }
-    }
-    below = af_wave_sum(below);
-    // ... of the wave's block, and of its channels that are still open (not taken)
-    const int passes = (ew.width + AF_WAVE - 1) / AF_WAVE;
-    unsigned run = 0, open = 0;
-    auto look = [&](int i, unsigned* bits, unsigned long long* gt, unsigned long long* eq) {
-      const int l = i * AF_WAVE + lane;
-      *bits = l < ew.width ? xs[ew.lo + l] : 0u;
-      const int key = (int)(*bits & 0x7FFFu);
-      *gt = __ballot(l < ew.width && key > T);
-      *eq = __ballot(l < ew.width && key == T);
+    // Everything that is looked at comes into registers together: the wave's own channels (up to
+    // 128 of them; wider shares go on in loops) and its stretch.
+    const int passes = (own_channels(ew) + AF_WAVE - 1) / AF_WAVE;
+    const int g_lo = stretch_begin(ew, r.n), g_hi = stretch_end(ew, r.n);
+    const group_keys* xg = reinterpret_cast<const group_keys*>(xs);
+    const unsigned bits0 = xs[max(ew.ch, 0)], bits1 = xs[max(ew.ch1, 0)];
+    const group_keys b0 = xg[max(min(g_lo + lane, g_hi - 1), 0)], b1 = xg[max(min(g_lo + AF_WAVE + lane, g_hi - 1), 0)];
+    __builtin_amdgcn_sched_barrier(0);
+    const bool lists = early_lists(r, ew, j);
+    struct Look {
+      unsigned long long gt, eq;  // lanes above T / at T
     };
-    for (int i = 0; i < passes; ++i) {
-      unsigned bits;
-      unsigned long long gt, eq;
-      look(i, &bits, &gt, &eq);
-      const unsigned long long free = i == 0 ? ~ew.taken : ~0ull;
-      run += (unsigned)__popcll(gt) + ((unsigned)__popcll(eq) << 16);
-      open += (unsigned)__popcll(gt & free) + ((unsigned)__popcll(eq & free) << 16);
+    auto look = [&](int ch, unsigned bits) {
+      const int key = ch >= 0 ? (int)(bits & 0x7FFFu) : -1;
+      return Look{__ballot(key > T), __ballot(key == T)};
+    };
+    const Look l0 = look(ew.ch, bits0);
+    Look l1 = {0ull, 0ull};
+    unsigned open_n = counts(l0.gt & ~ew.taken, l0.eq & ~ew.taken);  // as (above T | at T << 16)
+    if (passes > 1) {
+      l1 = look(ew.ch1, bits1);
+      open_n += counts(l1.gt, l1.eq);
     }
-    if (lane == 0) el.tot[wave] = make_uint4(run, open, below, 0u);
+    for (int i = 2; i < passes; ++i) {
+      const int ch = early_channel(ew, i, r.n);
+      const Look l = look(ch, xs[max(ch, 0)]);
+      open_n += counts(l.gt, l.eq);
+    }
+    // of the stretch: its ties, and where the index list is written also what lies above T
+    auto stretch = [&](int g, const group_keys& b) {
+      unsigned c = group_at(b, T) << 16;
+      if (lists) c += group_above(b, T);
+      return g < g_hi ? c : 0u;
+    };
+    unsigned all_n = stretch(g_lo + lane, b0);
+    if (g_lo + AF_WAVE < g_hi) all_n += stretch(g_lo + AF_WAVE + lane, b1);
+    for (int g0 = g_lo + 2 * AF_WAVE; g0 < g_hi; g0 += AF_WAVE) all_n += stretch(g0 + lane, xg[min(g0 + lane, g_hi - 1)]);
+    all_n = __ballot(all_n != 0) != 0 ? af_wave_sum(all_n) : 0u;
+    if (lane == 0) el.tot[wave] = make_uint2(all_n, open_n);
     __syncthreads();
     // every wave scans the (at most 16) wave counts on its own lanes
     static_assert(WAVES <= 16, "one row of lanes");
-    const uint4 wt = el.tot[lane % WAVES];
-    const unsigned run_s = af_row_incl_scan(wt.x), open_s = af_row_incl_scan(wt.y), below_s = af_row_incl_scan(wt.z);
-    const unsigned run_pre = (unsigned)__builtin_amdgcn_readlane((int)run_s, wave) - run;
-    const unsigned open_pre = (unsigned)__builtin_amdgcn_readlane((int)open_s, wave) - open;
-    const unsigned open_all = (unsigned)__builtin_amdgcn_readlane((int)open_s, WAVES - 1);
-    const unsigned below_all = (unsigned)__builtin_amdgcn_readlane((int)below_s, WAVES - 1);
-    const unsigned eq_below = min(below_all >> 16, quota), gt_below = below_all & 0xFFFFu;
-    const unsigned quota_r = quota - eq_below;  // ties this range may keep
-    const unsigned n_gt = open_all & 0xFFFFu;   // ties are listed behind these
-    const bool to_mem = store_idx && r.idx_out != nullptr;
-    unsigned gt_rank = run_pre & 0xFFFFu, eq_rank = run_pre >> 16;
-    unsigned gt_pos = open_pre & 0xFFFFu, eq_pos = open_pre >> 16, ties = 0;
-    for (int i = 0; i < passes; ++i) {
-      unsigned bits;
-      unsigned long long gt, eq;
-      look(i, &bits, &gt, &eq);
-      const unsigned long long free = i == 0 ? ~ew.taken : ~0ull;
-      // the first quota_r ties of the range are kept
-      const unsigned my_eq = eq_rank + lanes_below(eq);
-      const unsigned long long keq = __ballot(((eq >> lane) & 1ull) && my_eq < quota_r);
-      if (i == 0) ew.kept = gt | keq;
-      const unsigned entry = ((unsigned)(ew.lo + i * AF_WAVE + lane) << 16) | bits;
-      if (((gt & free) >> lane) & 1ull) list[gt_pos + lanes_below(gt & free)] = entry;
-      if (((keq & free) >> lane) & 1ull) list[n_gt + eq_pos + lanes_below(keq & free)] = entry;
-      if (to_mem && (((gt | keq) >> lane) & 1ull))
-        r.idx_out[gt_below + eq_below + gt_rank + lanes_below(gt) + min(my_eq, quota_r)] =
-            ew.lo + i * AF_WAVE + lane;
-      gt_rank += (unsigned)__popcll(gt);
-      eq_rank += (unsigned)__popcll(eq);
-      gt_pos += (unsigned)__popcll(gt & free);
-      eq_pos += (unsigned)__popcll(eq & free);
-      ties += (unsigned)__popcll(keq & free);
+    const uint2 wt = el.tot[lane % WAVES];
+    const unsigned all_s = af_row_incl_scan(wt.x), open_s = af_row_incl_scan(wt.y);
+    const unsigned all_pre = (unsigned)__builtin_amdgcn_readlane((int)all_s, wave) - all_n;
+    const unsigned open_pre = (unsigned)__builtin_amdgcn_readlane((int)open_s, wave) - open_n;
+    const unsigned n_gt = (unsigned)__builtin_amdgcn_readlane((int)open_s, WAVES - 1) & 0xFFFFu;  // ties are listed behind these
+    // The first `quota` ties of the whole vector are kept; the one stretch in which they run out
+    // looks up the last of them.
+    const unsigned eq_pre = all_pre >> 16;
+    int last_tie = eq_pre < quota ? r.n : -1;
+    if (eq_pre < quota && eq_pre + (all_n >> 16) > quota) {
+      unsigned seen = eq_pre;
+      for (int g0 = g_lo; g0 < g_hi && last_tie == r.n; g0 += AF_WAVE) {
+        const group_keys b = xg[min(g0 + lane, g_hi - 1)];
+        const unsigned mine_n = g0 + lane < g_hi ? group_at(b, T) : 0u;
+        const unsigned up_to = af_wave_incl_scan(mine_n);
+        unsigned rank = seen + up_to - mine_n;
+        const unsigned long long found = __ballot(rank < quota && rank + mine_n >= quota);
+        if (found != 0) {
+          int mine = 0;
+#pragma unroll
+          for (int c = 0; c < GROUP; ++c)
+            if ((int)(b[c / 2] >> (c % 2 * 16) & 0x7FFFu) == T && ++rank == quota) mine = (g0 + lane) * GROUP + c;
+          last_tie = __builtin_amdgcn_readlane(mine, (int)__builtin_ctzll(found));
+        }
+        seen += (unsigned)__builtin_amdgcn_readlane((int)up_to, AF_WAVE - 1);
+      }
+    }
+    unsigned gt_pos = open_pre & 0xFFFFu, eq_pos = n_gt + (open_pre >> 16), ties = 0;
+    auto put = [&](int ch, unsigned bits, const Look& l, unsigned long long free) {
+      const unsigned long long keq = l.eq != 0 ? l.eq & __ballot(ch <= last_tie) : 0ull;
+      const unsigned entry = ((unsigned)ch << 16) | bits;
+      if (((l.gt & free) >> lane) & 1ull) list[gt_pos + lanes_below(l.gt & free)] = entry;
+      gt_pos += (unsigned)__popcll(l.gt & free);
+      if (keq != 0) {
+        if (((keq & free) >> lane) & 1ull) list[eq_pos + lanes_below(keq & free)] = entry;
+        eq_pos += (unsigned)__popcll(keq & free);
+        ties += (unsigned)__popcll(keq & free);
+      }
+      return l.gt | keq;
+    };
+    ew.kept = put(ew.ch, bits0, l0, ~ew.taken);
+    if (passes > 1) put(ew.ch1, bits1, l1, ~0ull);
+    for (int i = 2; i < passes; ++i) {
+      const int ch = early_channel(ew, i, r.n);
+      const unsigned bits = xs[max(ch, 0)];
+      put(ch, bits, look(ch, bits), ~0ull);
     }
     if (lane == 0) el.ties[wave] = ties;
-    if (store_count && r.count_out != nullptr && tid == 0) *r.count_out = r.k;
+    if (j == 0 && r.count_out != nullptr && tid == 0) *r.count_out = r.k;
     __syncthreads();
+    ew.T = T;
+    ew.last_tie = last_tie;
+    ew.pos = (all_pre & 0xFFFFu) + min(eq_pre, quota);
+    ew.ties = quota - min(eq_pre, quota);
     const unsigned all_ties = (unsigned)__builtin_amdgcn_readlane(
         (int)af_row_incl_scan(el.ties[lane % WAVES]), WAVES - 1);
     return (int)(n_gt + all_ties);
   }
 
+  // Workgroup j's part of the ascending index list of the whole vector: piece i of stretch w is
+  // written by wave w of workgroup w + i * WAVES of the launch's J (modulo J where there are fewer).
+  static __device__ __forceinline__ void early_write_list(const af_row_src& r, const unsigned short* xs,
+                                                          const EarlyWave& ew, int j, int J) {
+    const int g_lo = stretch_begin(ew, r.n), g_hi = stretch_end(ew, r.n);
+    if (!early_lists(r, ew, j) || g_lo >= g_hi) return;
+    const int lane = threadIdx.x & 63, wave = wave_id(), pieces = stretch_pieces(ew);
+    typedef unsigned short half_group __attribute__((ext_vector_type(GROUP / 2)));
+    const half_group* xh = reinterpret_cast<const half_group*>(xs);
+    for (int i = 0; i < pieces; ++i) {
+      int writer = wave + i * WAVES;
+      while (writer >= J) writer -= J;
+      if (writer != j) continue;
+      // the kept channels of the stretch in front of the piece
+      unsigned front = 0;
+      for (int g0 = g_lo; g0 < g_lo + i * 32; g0 += AF_WAVE) {
+        const int g = g0 + lane;
+        const group_keys b = reinterpret_cast<const group_keys*>(xs)[min(g, g_hi - 1)];
+        const unsigned c = group_above(b, ew.T) + (group_at(b, ew.T) << 16);
+        front += g < min(g_lo + i * 32, g_hi) ? c : 0u;
+      }
+      if (i > 0) front = af_wave_sum(front);
+      const unsigned base = ew.pos + (front & 0xFFFFu) + min(front >> 16, ew.ties);
+      const int h = (g_lo + i * 32) * 2 + lane;  // half a group per lane
+      const half_group b = xh[min(h, g_hi * 2 - 1)];
+      unsigned keep = 0;
+#pragma unroll
+      for (int c = 0; c < GROUP / 2; ++c) {
+        const int key = (int)(b[c] & 0x7FFFu);
+        keep |= (unsigned)(h < g_hi * 2 && (key > ew.T || (key == ew.T && h * (GROUP / 2) + c <= ew.last_tie))) << c;
+      }
+      unsigned pos = base + af_wave_incl_scan((unsigned)__popc(keep)) - (unsigned)__popc(keep);
+#pragma unroll
+      for (int c = 0; c < GROUP / 2; ++c)
+        if ((keep >> c) & 1u) r.idx_out[pos++] = h * (GROUP / 2) + c;
+    }
+  }
+
+  static __device__ __forceinline__ unsigned counts(unsigned long long gt, unsigned long long eq) {
+    return (unsigned)__popcll(gt) + ((unsigned)__popcll(eq) << 16);
+  }
   // number of set bits of m below this lane
   static __device__ __forceinline__ unsigned lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
