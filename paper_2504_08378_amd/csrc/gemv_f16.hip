@@ -171,7 +171,7 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
     int s_early = S;
     early = ctx->tune_early_rows == 1   ? (int)GEMV_EARLY_NONE
             : ctx->tune_early_rows == 2 ? gemv_width_class(r.n)
-                                        : gemv_early_class(r.n, (long long)r.k / S * tw * 2);
+                                        : gemv_early_class(r.pro, r.n, r.k, S, lx);
     if (early != GEMV_EARLY_NONE &&
         (!af_plan_gemv_lds(r, max_rows, use_lds_x, false, GEMV_LIST, &s_early, &xs_bytes, &list_cap, false, true) ||
          s_early != S))

@@ -508,16 +508,35 @@ constexpr int gemv_early(int mode, int nw, bool routed) {
   return mode >= 0 && ((mode >> 2) & 3) == 1 && nw == 16 && !routed ? vectors[mode >> 4] : 0;
 }
 enum { GEMV_EARLY_NONE = 3 };
-// Which of them: inputs of up to 4096, 16384 and AF_MAX_N channels; none where the
-// `bytes` that a workgroup streams are few: looking for the rows costs 0.4-0.5 us, which a short
-// stream does not give back.  Measured at 50 % without / with early rows: 2048 -> 2048 (22 KB a
-// workgroup) 9.27 / 9.73 us, 4096 -> 4096 (87 KB) 9.83 / 10.02, 4096 -> 12288 (210 KB) 14.86 /
-// 14.46, 4096 -> 22016 (520 KB) 20.60 / 19.61; wider inputs have a longer front end to hide behind:
-// 12000 -> 504 (85 KB) 13.06 / 12.22, 11008 -> 4096 at 80 % (70 KB) 12.56 / 11.86 and at 50 % (200 KB)
-// 16.53 / 14.81, 8192 -> 10240 (350 KB) 21.71 / 18.91.
+// Rows that a wave of a launch with LX lanes across a tile can take.
+constexpr int gemv_early_cap(int lx) { return (lx == 16 ? 4 : 8) * AF_WAVE / lx; }
+// Which of them: inputs of up to 4096, 16384 and AF_MAX_N channels.
 static inline int gemv_width_class(int n) { return n <= RP_EV * 1024 ? 0 : (n <= 4 * RP_EV * 1024 ? 1 : 2); }
-static inline int gemv_early_class(int n, long long bytes) {
-  return bytes < (n <= 4096 ? 96 : 64) * 1024 ? (int)GEMV_EARLY_NONE : gemv_width_class(n);
+// ... and whether at all: not where early rows cost more than they hide.  The look for the rows is
+// 0.5-1 us of front end.  Up to 4096 channels it pays from a stream of 160 KB a workgroup on (us
+// without / with, index list written; 50 % unless stated):
+//   2048 -> 12288 (128 KB) 10.54 / 11.59    4096 -> 4096 (85 KB) 9.89 / 10.41    2048 -> 16384 (170 KB) 12.31 / 12.37
+//   4096 -> 8192 (170 KB) 12.61 / 12.19     4096 -> 12288 (256 KB) 15.24 / 14.35, at 80 % (102 KB) 10.75 / 12.01
+//   3072 -> 12288 (192 KB) 13.00 / 12.63    4096 -> 22016 (512 KB) 22.13 / 21.68, at 80 % (205 KB) 14.68 / 14.84
+// Wider inputs have a longer front end to hide behind: from 48 KB on, or from 72 KB where few
+// channels are kept and so less than 48 KB can be taken early,
+//   10672 -> 920 (55 KB) 12.82 / 12.36      12632 -> 616 at 30 % (58 KB) 15.33 / 14.36    14456 -> 1536 at 70 % (67 KB) 13.83 / 12.89
+//   5120 -> 4096 at 80 % (42 KB) 9.75 / 9.69    8192 -> 4096 at 80 % (68 KB) 10.91 / 11.16    11008 -> 4096 at 80 % (91 KB) 13.21 / 13.05
+// but there the look also grows with the channels that a wave owns, of which it takes from the first
+// 64 only, so what is taken has to be worth it: 1 KB for the workgroup to 6 of a wave's channels, to
+// 3.5 behind the SiLU producer (channels : KB; * SiLU):
+//   17856 -> 3408 at 80 % (124 : 36) 18.91 / 16.87    28304 -> 3152 at 80 % (177 : 36) 23.50 / 21.87
+//   19888 -> 6472 at 90 % (178 : 32) 19.36 / 18.80    28672 -> 8192 at 90 % (298 : 32) 24.11 / 24.46
+//   *11008 -> 6144 (137 : 64) 21.42 / 20.10           *28672 -> 4096 (224 : 64) 34.30 / 34.06
+//   *28672 -> 6144 (358 : 64) 44.74 / 45.77           *28672 -> 10240 at 80 % (298 : 72) 35.23 / 35.98
+static inline int gemv_early_class(int pro, int n, int k, int S, int lx) {
+  const long long row = lx * 16, bytes = k / S * row;
+  const int share = (int)((long long)k * 48 / n), cap = gemv_early_cap(lx);
+  const long long early = (share < cap ? share : cap) * 16 * row;  // taken by the workgroup's waves
+  const bool pays = n <= 4096 ? bytes >= 160 * 1024
+                              : bytes >= (early >= 48 * 1024 ? 48 : 72) * 1024 &&
+                                    n / S / 16 * 2 * 1024 <= (pro == AF_PRO_SILUMUL ? 7 : 12) * early;
+  return pays ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
 }
 static_assert(8 * RP_EV * 1024 >= AF_MAX_N, "the widest input fits the largest class");
 
@@ -527,7 +546,7 @@ template <int LX, int U, int NW, bool ROUTED, int MODE = -1>
 __global__ __launch_bounds__(NW * AF_WAVE) void gemv_f16_kernel(GemvParams p) {
   extern __shared__ __align__(16) unsigned short xs[];  // the operator input, when built here
   constexpr int EARLY = gemv_early(MODE, NW, ROUTED);
-  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, (LX == 16 ? 4 : 8) * AF_WAVE / LX>, GemvLds<NW, LX * 8>> lds;
+  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
   const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y};
   if constexpr (MODE >= 0) {
     const GemvParams q = gemv_fix_mode<MODE>(p);
