@@ -307,13 +307,21 @@ def _pattern(kind, n, rng):
     return x.astype(np.float16)
 
 
+@pytest.fixture
+def early_rows(ctx):
+    """Every launch of the test requests rows early; one that could not would be refused."""
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 2)
+    yield
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
+
+
 # width classes of the source (4096 / 16384 / above, and one past each), tile widths 128 / 256 / 512,
 # ragged tiles, ranges that do not divide
 @pytest.mark.parametrize("n,out,share", [(4096, 4096, 0.9), (4096, 12288, 0.5), (4096, 22016, 0.3), (4104, 8184, 0.5),
                                          (4040, 6152, 0.97), (11008, 4096, 0.5), (16384, 2056, 0.4),
                                          (16392, 4096, 0.5), (32768, 1032, 0.99), (8192, 10240, 1.0)])
 @pytest.mark.parametrize("kind", ["random", "equal", "few", "ascending", "descending", "sparse"])
-def test_early_rows_are_exactly_the_kept_ones(ctx, n, out, share, kind):
+def test_early_rows_are_exactly_the_kept_ones(ctx, early_rows, n, out, share, kind):
     rng = np.random.default_rng(n + out)
     x, k = _pattern(kind, n, rng), int(n * share)
     g = torch.Generator(device="cuda")
@@ -432,3 +440,73 @@ def test_early_rows_are_left_out_where_they_cost_time(ctx, n, out, share, pro):
             ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
     off, rule = _median_times(ctx, [lambda e=e: launches(e) for e in (1, 0)])
     assert rule <= 1.03 * off, (off, rule)
+
+
+# Every width class with every producer, forced onto the early rows: one channel group up to the widest
+# input, splits that leave waves without channels, launches of fewer workgroups than list pieces,
+# ragged tiles, padded rows, all three tile widths.
+EARLY_SHAPES = [(8, 8, 0, 0), (136, 264, 3, 0), (1000, 520, 1, 8), (2048, 2048, 0, 0), (4088, 1032, 7, 0), (4096, 12288, 4, 0),
+                (4104, 7176, 0, 24), (11008, 4096, 8, 0), (16384, 520, 16, 0), (16392, 1032, 0, 8), (32768, 520, 5, 0),
+                (28672, 22016, 0, 0)]
+
+
+@pytest.mark.parametrize("n,out,split,pad", EARLY_SHAPES)
+@pytest.mark.parametrize("pro,kind", [(p, k) for p in ("none", "rmsnorm", "silumul") for k in ("random", "few", "half")]
+                         + [("none", "special")])
+def test_early_rows_forced(ctx, n, out, split, pad, pro, kind):
+    rng = np.random.default_rng(n * 7 + out)
+    if kind == "half":
+        v = rng.laplace(size=n) * np.where(np.arange(n) < n // 2, 6, 1)
+    elif kind == "special":
+        v = rng.laplace(size=n)
+        v[rng.random(n) < 0.3] *= 1e-7           # subnormal halves
+        v[rng.integers(0, n, 5)] = np.nan
+        v[rng.integers(0, n, 5)] = np.inf
+        v[rng.integers(0, n, 5)] = -np.inf
+    else:
+        v = _pattern(kind, n, rng).astype(np.float64)
+    v = v.astype(np.float16)
+    kw, src = {}, v
+    if pro == "rmsnorm":
+        kw = {"producer": B.AF_PRO_RMSNORM, "gain": to_dev(np.ones(n, np.float16))}
+    elif pro == "silumul":
+        kw, src = {"producer": B.AF_PRO_SILUMUL}, np.concatenate([np.full(n, 3, np.float16), v])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    Wt = (torch.randn((n, out + pad), generator=g, device="cuda") * 0.02).half()
+    res = to_dev(S.activation(n, S.channel_scales(n, out, "r"), "r", 0))
+    for share in (0.2, 0.7):
+        k = max(1, int(n * share))
+        got = {}
+        for early in (1, 2):
+            ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, early)
+            ctx.set_option(B.AF_OPT_TUNE_SPLIT, split)
+            try:
+                got[early] = _run(ctx, Wt, to_dev(src), n, sel_mode=B.AF_SEL_TOPK, k=k, out=out, residual=res, **kw)
+            finally:
+                ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
+                ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+        (y1, x1, i1, c1), (y2, x2, i2, c2) = got[1], got[2]
+        assert c1 == c2 == k and np.array_equal(x1.view(np.uint16), x2.view(np.uint16))
+        assert np.array_equal(i2, O.select_topk(x2, k)) and np.array_equal(i1, i2)
+        if kind != "special":
+            rows = torch.from_numpy(i2.astype(np.int64)).cuda()
+            xs = torch.from_numpy(x2[i2].astype(np.float64)).cuda()
+            ref = (Wt[rows, :out].double() * xs[:, None]).sum(0) + res.double()
+            assert O.rel_err(y2, ref.cpu().numpy()) <= TOL  # one rounding to fp16
+
+
+def test_early_rows_refused_where_they_cannot_run(ctx):
+    W, x = _wx(264, 2048, 3)
+    Wt = ctx.pack_inmajor_f16(to_dev(W))
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 2)
+    try:
+        ctx.set_option(B.AF_OPT_TUNE_WAVES, 4)
+        with pytest.raises(B.AfError):
+            ctx.select_gemv_f16(Wt, to_dev(x), sel_mode=B.AF_SEL_TOPK, k=1024)
+        ctx.set_option(B.AF_OPT_TUNE_WAVES, 0)
+        ctx.select_gemv_f16(Wt, to_dev(x), sel_mode=B.AF_SEL_THRESHOLD, t=0.5)  # no early rows there
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_WAVES, 0)
+        ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
+    ctx.synchronize()
