@@ -69,14 +69,23 @@ def _exact_topk_property(x16, idx, k):
         assert np.nonzero(sel & (key == lo))[0].max() < np.nonzero(~sel & (key == lo))[0].min()
 
 
-def _sets_close(got, ref, x_ref):
+# How far from the k-th magnitude (in units of the last place) a channel may lie that one side keeps
+# and the other does not.  Behind a norm or attention, a value rounded to fp16 from sums in another
+# order: the neighbouring value, 2 units.  The down projection's input is silu(gate) * up of two such
+# values: one unit of up is at most 2 of the product (significands 1 and 2), one unit of gate at
+# most 2 |d ln silu / d ln g| = 4 (|1 + g (1 - sigma(g))| <= 2 for -3.1 <= g), and the product is
+# rounded once more: 7.
+UNITS = (2, 2, 2, 7)
+
+
+def _sets_close(got, ref, x_ref, units=2):
     """Equal, or differing only in channels whose oracle magnitude sits at the boundary."""
     if np.array_equal(got, ref):
         return True
     key = (np.asarray(x_ref).view(np.uint16) & 0x7FFF).astype(np.int64)
     thr = key[ref].min()
     diff = np.setxor1d(got, ref)
-    return len(got) == len(ref) and np.all(np.abs(key[diff] - thr) <= 2)
+    return len(got) == len(ref) and np.all(np.abs(key[diff] - thr) <= units)
 
 
 TAPS = ("x_qkv", "qkv", "attn", "h_mid", "x_gateup", "gateup", "x_down")
@@ -375,7 +384,7 @@ def test_13b_shape_reuse_pair(ctx):
         same = True
         for p in range(4):
             got = st2.sets[0].fetch(p, ks[p])
-            assert _sets_close(got, traces[0].idx[p], traces[0].x[p]), (sp, p)
+            assert _sets_close(got, traces[0].idx[p], traces[0].x[p], UNITS[p]), (sp, p)
             same &= np.array_equal(got, traces[0].idx[p])
         got_h, ref_h = to_host(out).astype(np.float64), traces[1].hidden.astype(np.float64)
         if same:
