@@ -221,3 +221,25 @@ def test_pack_edges_ties_and_special_values(ctx, out, n, shift, layout):
     got = np.stack([b & 15, b >> 4], axis=2).reshape(n, out).T.astype(np.int64) - 8
     assert np.array_equal(got, q)
     assert np.array_equal(to_host(scales).view(np.uint16), s.T.view(np.uint16))
+
+
+@pytest.mark.parametrize("layout", ["g32", "cl"])
+def test_pack_ties_at_every_kind_of_scale(ctx, layout):
+    """Quotients of exactly k + 1/2 at scales whose reciprocal is inexact, from subnormal ones to the
+    largest: s = m 2^e with m of at most 7 bits, so that (k + 1/2) s and 7 s are fp16 values and 7 s / 7
+    gives s back."""
+    ties = np.concatenate([[7.0, -7.0], np.arange(-6.5, 7, 1), np.arange(-6, 7, 1), [0.5, -0.5, 1.5]])[:32]
+    scales = [m * 2.0 ** e for e in (-23, -22, -20, -16, -12, -6, 0, 6) for m in range(64, 128)]
+    groups = np.stack([ties * s for s in scales])
+    assert np.array_equal(groups.astype(np.float16).astype(np.float64), groups) and len(scales) == 512
+    W = groups.reshape(64, 256).astype(np.float16)          # eight groups in each row
+    if layout == "cl":
+        W = np.ascontiguousarray(W.T)                       # ... in each column of 256 outputs
+    packed, sc = (ctx.pack_q4_cl if layout == "cl" else ctx.pack_q4_g32)(to_dev(W))
+    ctx.synchronize()
+    q, s = _pack_reference(W, 0 if layout == "cl" else 1)
+    out, n = W.shape
+    b = to_host(packed)
+    got = np.stack([b & 15, b >> 4], axis=2).reshape(n, out).T.astype(np.int64) - 8
+    assert np.array_equal(got, q)
+    assert np.array_equal(to_host(sc).view(np.uint16), s.T.view(np.uint16))
