@@ -208,9 +208,8 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     }
   }
   if constexpr (!EARLY) {
-  if (p.use_lds_x() && (!p.range_sel() || routed))
-    RP::produce(r, xs, s_rp, s == 0, vb.bx, vb.gx,
-                r.sel == AF_SEL_TOPK ? s_scratch : nullptr);
+    if (p.use_lds_x() && (!p.range_sel() || routed))
+      RP::produce(r, xs, s_rp, s == 0, vb.bx, vb.gx, r.sel == AF_SEL_TOPK ? s_scratch : nullptr);
   }
   if constexpr (routed) {
     RP::template router_in_lds<RE>(xs, r.n, s_rp, wr, p.router_E, p.router_top);

@@ -72,8 +72,10 @@ struct RowPrologue {
     // RMSNorm of a vector of at most one access per thread (n <= RP_EV * THREADS: 4096 channels
     // for the 1024-thread kernels) takes the copy of the code without the batch of four and its
     // masks: the front end is bound by the instructions its waves issue, and that copy issues
-    // fewer (q|k|v 15.7 -> 15.4 us, gate|up 21.2 -> 20.8 us at the 7B shape).  The other two
-    // producers measured no better with a second copy, so they keep the one.
+    // fewer (4096 -> 12288 15.7 -> 15.4 us, 4096 -> 22016 21.2 -> 20.8 us, when these went through
+    // here; with early rows they take produce_raw, and what is left is short streams, the router's
+    // launches, given rows and the whole-layer kernel).  The other two producers measured no better
+    // with a second copy, so they keep the one.
     if (r.pro == AF_PRO_RMSNORM && r.n <= RP_EV * THREADS)
       produce_batched<1>(r, xs, sm, store_x, store_phase, store_stride, hist);
     else
@@ -636,6 +638,10 @@ struct RowPrologue {
   // the key's exponent and first mantissa bit that at least `want` of the channels reach: one
   // compare, ballot and population count per bit.  want is at most 3/4 of the channels that are
   // kept on average, so that what the cut lets in lies above the k-th magnitude almost always.
+  // The cut resolves half an octave, so more than `want` can reach it, and up to CAP of them are
+  // taken: with magnitudes that are all alike, some that are dropped.  Stopping at `want` instead
+  // saves those 0.1-0.3 us and costs spread magnitudes as much (80 %: 28672 -> 8192 29.8 -> 30.3 us,
+  // 8192 -> 10240 15.8 -> 15.9); so does taking none where the cut lets in twice the average.
   template <int CAP>
   static __device__ __forceinline__ int early_pick(const af_row_src& r, EarlyWave& ew, unsigned* row, half_t a,
                                                    half_t b) {
