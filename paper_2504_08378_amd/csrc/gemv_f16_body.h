@@ -357,6 +357,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     if (early_pending) take_early();
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] += early_acc[c];
+    RP::early_write_list(r, xs, lds.early, early, s * vb.gx + vb.bx, vb.gx * S);
   } else if (p.range_sel()) {
     stream(routed ? RP::threshold_range_of_full(r, xs, s_rp, s_list, S, s)
                   : RP::threshold_range(r, xs, s_rp, s_list, S, s, vb.bx == 0));
@@ -434,7 +435,6 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
         store_out(p, out0 + c, v, res);
       }
     }
-    if constexpr (EARLY) RP::early_write_list(r, xs, early, vb.bx, vb.gx);
     af_prof_end(p.prof);
     return;
   }
@@ -446,9 +446,6 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     for (int w = 0; w < GEMV_WAVES; ++w) v += s_red[w][c];
     af_store_agent(mine + tile0 + c, v);  // out_pad covers whole tiles
   }
-  // Nothing in this launch waits for the index list: it is written while the partial sums are on
-  // their way (7B step 2.218 ms; ahead of the stream 2.222, behind it 2.226, beside the ticket 2.225).
-  if constexpr (EARLY) RP::early_write_list(r, xs, early, s * vb.gx + vb.bx, vb.gx * S);
   af_stores_done();
   __syncthreads();
   if (tid == 0) {

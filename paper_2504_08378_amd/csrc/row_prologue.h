@@ -485,6 +485,8 @@ struct RowPrologue {
   struct Early {
     uint2 tot[WAVES];  // per-wave counts of the selection
     unsigned ties[WAVES];
+    int last_tie;  // the last channel of the whole vector that is kept with the k-th magnitude
+    int done;      // waves that have streamed their rows
   };
   struct EarlyWave {            // uniform over the wave, but for ch
     int cycles, q0, q1;         // of the deal, and the wave's
@@ -492,8 +494,8 @@ struct RowPrologue {
     int ch, ch1;                // this lane's channels of the wave's first 64 and of its next, -1: none
     unsigned long long taken;   // bit l: lane l's channel was taken
     unsigned long long kept;    // bit l: lane l's channel is kept by the selection
-    int T, last_tie;            // kept in this wave's stretch: keys above T, at T up to this channel
-    unsigned pos, ties;         // position of the stretch in the index list, ties that may be kept in it
+    int T;                      // the k-th magnitude's key, and how many channels are kept with it
+    unsigned quota;
   };
   template <int B>
   struct Raw {  // one thread's share of the operator's source: NONE x; RMSNORM hidden, gain; SILUMUL gate, up
@@ -521,14 +523,11 @@ struct RowPrologue {
     ew.taken = ew.kept = 0;
     return ew;
   }
-  // The wave's stretch in groups of 8 channels (n % 8 == 0), and the pieces (of 32
+  // Wave w's stretch in groups of 8 channels (n % 8 == 0), and the pieces (of 32
   // groups) of the longest stretch.
   static constexpr int GROUP = 8;
-  static __device__ __forceinline__ int stretch_begin(const EarlyWave& ew, int n) {
-    return min(ew.q0 * ew.S * (AF_DEAL / GROUP), n / GROUP);
-  }
-  static __device__ __forceinline__ int stretch_end(const EarlyWave& ew, int n) {
-    return min(ew.q1 * ew.S * (AF_DEAL / GROUP), n / GROUP);
+  static __device__ __forceinline__ int stretch_begin(const EarlyWave& ew, int w, int n) {
+    return min(af_dealt_cycle(ew.cycles, w, WAVES) * ew.S * (AF_DEAL / GROUP), n / GROUP);
   }
   static __device__ __forceinline__ int stretch_pieces(const EarlyWave& ew) {
     return ((ew.cycles + WAVES - 1) / WAVES * ew.S * (AF_DEAL / GROUP) + 31) / 32;
@@ -700,7 +699,7 @@ struct RowPrologue {
     // Everything that is looked at comes into registers together: the wave's own channels (up to
     // 128 of them; wider shares go on in loops) and its stretch.
     const int passes = (own_channels(ew) + AF_WAVE - 1) / AF_WAVE;
-    const int g_lo = stretch_begin(ew, r.n), g_hi = stretch_end(ew, r.n);
+    const int g_lo = stretch_begin(ew, wave, r.n), g_hi = stretch_begin(ew, wave + 1, r.n);
     const group_keys* xg = reinterpret_cast<const group_keys*>(xs);
     const unsigned bits0 = xs[max(ew.ch, 0)], bits1 = xs[max(ew.ch1, 0)];
     const group_keys b0 = xg[max(min(g_lo + lane, g_hi - 1), 0)], b1 = xg[max(min(g_lo + AF_WAVE + lane, g_hi - 1), 0)];
@@ -736,6 +735,10 @@ struct RowPrologue {
     for (int g0 = g_lo + 2 * AF_WAVE; g0 < g_hi; g0 += AF_WAVE) all_n += stretch(g0 + lane, xg[min(g0 + lane, g_hi - 1)]);
     all_n = __ballot(all_n != 0) != 0 ? af_wave_sum(all_n) : 0u;
     if (lane == 0) el.tot[wave] = make_uint2(all_n, open_n);
+    if (tid == 0) {
+      el.last_tie = r.n;
+      el.done = 0;
+    }
     __syncthreads();
     // every wave scans the (at most 16) wave counts on its own lanes
     static_assert(WAVES <= 16, "one row of lanes");
@@ -762,6 +765,7 @@ struct RowPrologue {
           for (int c = 0; c < GROUP; ++c)
             if ((int)(b[c / 2] >> (c % 2 * 16) & 0x7FFFu) == T && ++rank == quota) mine = (g0 + lane) * GROUP + c;
           last_tie = __builtin_amdgcn_readlane(mine, (int)__builtin_ctzll(found));
+          if (lane == 0) el.last_tie = last_tie;
         }
         seen += (unsigned)__builtin_amdgcn_readlane((int)up_to, AF_WAVE - 1);
       }
@@ -790,46 +794,52 @@ struct RowPrologue {
     if (j == 0 && r.count_out != nullptr && tid == 0) *r.count_out = r.k;
     __syncthreads();
     ew.T = T;
-    ew.last_tie = last_tie;
-    ew.pos = (all_pre & 0xFFFFu) + min(eq_pre, quota);
-    ew.ties = quota - min(eq_pre, quota);
+    ew.quota = quota;
     const unsigned all_ties = (unsigned)__builtin_amdgcn_readlane(
         (int)af_row_incl_scan(el.ties[lane % WAVES]), WAVES - 1);
     return (int)(n_gt + all_ties);
   }
 
-  // Workgroup j's part of the ascending index list of the whole vector: piece i of stretch w is
-  // written by wave w of workgroup w + i * WAVES of the launch's J (modulo J where there are fewer).
+  // Workgroup j's part of the ascending index list of the whole vector: pieces j, j + J, ... of the
+  // launch's J workgroups, piece p being number p / WAVES of stretch p % WAVES.  Called by every wave
+  // when it has streamed its rows: the first one does it, while it would wait for the others (they end
+  // 2 us apart; 7B step 2.215 ms, 2.222 with every stretch written by its own wave beside the partial
+  // sums or ahead of the rows, 2.203 without the list).
   static __device__ __forceinline__ void early_write_list(const af_row_src& r, const unsigned short* xs,
-                                                          const EarlyWave& ew, int j, int J) {
-    const int g_lo = stretch_begin(ew, r.n), g_hi = stretch_end(ew, r.n);
-    if (!early_lists(r, ew, j) || g_lo >= g_hi) return;
-    const int lane = threadIdx.x & 63, wave = wave_id(), pieces = stretch_pieces(ew);
+                                                          Early& el, const EarlyWave& ew, int j, int J) {
+    if (!early_lists(r, ew, j)) return;
+    int before = 0;
+    if ((threadIdx.x & 63) == 0) before = atomicAdd(&el.done, 1);
+    if (__builtin_amdgcn_readfirstlane(before) != 0) return;
+    const int lane = threadIdx.x & 63, pieces = stretch_pieces(ew) * WAVES;
+    const group_keys* xg = reinterpret_cast<const group_keys*>(xs);
     typedef unsigned short half_group __attribute__((ext_vector_type(GROUP / 2)));
     const half_group* xh = reinterpret_cast<const half_group*>(xs);
-    for (int i = 0; i < pieces; ++i) {
-      int writer = wave + i * WAVES;
-      while (writer >= J) writer -= J;
-      if (writer != j) continue;
-      // the kept channels of the stretch in front of the piece
+    const unsigned all_s = af_row_incl_scan(el.tot[lane % WAVES].x);
+    for (int p = j; p < pieces; p += J) {
+      const int w = p % WAVES, i = p / WAVES;
+      const int g_lo = stretch_begin(ew, w, r.n), g_hi = stretch_begin(ew, w + 1, r.n), g_p = g_lo + i * 32;
+      if (g_p >= g_hi) continue;
+      // the channels in front of the piece, above T | at T << 16
       unsigned front = 0;
-      for (int g0 = g_lo; g0 < g_lo + i * 32; g0 += AF_WAVE) {
-        const int g = g0 + lane;
-        const group_keys b = reinterpret_cast<const group_keys*>(xs)[min(g, g_hi - 1)];
-        const unsigned c = group_above(b, ew.T) + (group_at(b, ew.T) << 16);
-        front += g < min(g_lo + i * 32, g_hi) ? c : 0u;
+      for (int g0 = g_lo; g0 < g_p; g0 += AF_WAVE) {
+        const group_keys b = xg[min(g0 + lane, g_p - 1)];
+        front += g0 + lane < g_p ? group_above(b, ew.T) + (group_at(b, ew.T) << 16) : 0u;
       }
       if (i > 0) front = af_wave_sum(front);
-      const unsigned base = ew.pos + (front & 0xFFFFu) + min(front >> 16, ew.ties);
-      const int h = (g_lo + i * 32) * 2 + lane;  // half a group per lane
+      const unsigned pre = w > 0 ? (unsigned)__builtin_amdgcn_readlane((int)all_s, w - 1) : 0u;
+      front += pre;
+      const int last_tie = (pre >> 16) < ew.quota ? el.last_tie : -1;  // the ties of later stretches are not kept
+      const int h = g_p * 2 + lane;  // half a group per lane
       const half_group b = xh[min(h, g_hi * 2 - 1)];
       unsigned keep = 0;
 #pragma unroll
       for (int c = 0; c < GROUP / 2; ++c) {
         const int key = (int)(b[c] & 0x7FFFu);
-        keep |= (unsigned)(h < g_hi * 2 && (key > ew.T || (key == ew.T && h * (GROUP / 2) + c <= ew.last_tie))) << c;
+        keep |= (unsigned)(h < g_hi * 2 && (key > ew.T || (key == ew.T && h * (GROUP / 2) + c <= last_tie))) << c;
       }
-      unsigned pos = base + af_wave_incl_scan((unsigned)__popc(keep)) - (unsigned)__popc(keep);
+      unsigned pos = (front & 0xFFFFu) + min(front >> 16, ew.quota) + af_wave_incl_scan((unsigned)__popc(keep)) -
+                     (unsigned)__popc(keep);
 #pragma unroll
       for (int c = 0; c < GROUP / 2; ++c)
         if ((keep >> c) & 1u) r.idx_out[pos++] = h * (GROUP / 2) + c;
