@@ -14,8 +14,10 @@ events on the library's stream, and the CPU oracle timed on a bounded sample.
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -26,13 +28,23 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM bytes per launch of the dominant kernel (fused gate|up GEMV, 7B shape, 50 %).  Counters
 # cannot be read from inside this process; the figure comes from the two rocprofv3 --pmc runs
-# of this very command that profiles/gateup_7b_f16_sp50_pmc_traffic.md summarises (file, kernel
-# name and launch shape are repeated in the output so that a stale figure shows):
+# of this very command that profiles/gateup_7b_f16_sp50_pmc_traffic.md summarises:
 # FETCH_SIZE KiB x fetch factor + WRITE_SIZE KiB x write factor, the factors being what the same
-# counters read for a plain 256 MiB device copy of known size.
-TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44360.0, "fetch_factor": 2.000, "write_KiB": 409.8, "write_factor": 1.000,
+# counters read for a plain 256 MiB device copy of known size.  The output repeats file, kernel and
+# launch shape, and says whether the kernel's sources are still those that were counted.
+TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44415.5, "fetch_factor": 2.000, "write_KiB": 410.2, "write_factor": 1.000,
                                "kernel": "gemv_f16_kernel<64, 8, 16, false, 5> grid 43x4",
-                               "source": "profiles/gateup_7b_f16_sp50_pmc_traffic.md"}}
+                               "source": "profiles/gateup_7b_f16_sp50_pmc_traffic.md",
+                               "kernel_sources": "de59ea4c0f32"}}
+
+
+def kernel_sources_digest() -> str:
+    """Digest of the fp16 GEMV's sources without comments and white space."""
+    h = hashlib.sha256()
+    for name in ("af_internal.h", "row_prologue.h", "gemv_f16_body.h", "gemv_f16.hip"):
+        with open(os.path.join(ROOT, "paper_2504_08378_amd", "csrc", name)) as src:
+            h.update(re.sub(r"//[^\n]*|/\*.*?\*/|\s+", "", src.read(), flags=re.S).encode())
+    return h.hexdigest()[:12]
 
 
 def keep_count(n: int, sp: int) -> int:
@@ -759,6 +771,7 @@ def main() -> int:
         roofline["traffic"] = int((tr_["fetch_KiB"] * tr_["fetch_factor"] + tr_["write_KiB"] * tr_["write_factor"]) * 1024)
         roofline["traffic_source"] = {k_: tr_[k_] for k_ in ("source", "kernel", "fetch_KiB", "fetch_factor",
                                                              "write_KiB", "write_factor")}
+        roofline["traffic_source"]["counted_on_these_sources"] = kernel_sources_digest() == tr_["kernel_sources"]
         roofline["traffic_over_algorithmic"] = round(roofline["traffic"] / alg, 4)
 
     # ---- the box's plain streaming-read rate (what an ideal reader of these bytes gets) ----
