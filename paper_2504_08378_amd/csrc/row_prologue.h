@@ -479,7 +479,7 @@ struct RowPrologue {
   // its channels beforehand, so the channels and not the list are cut into splits: they are dealt
   // out in small groups (af_dealt_channel), because what is kept may lie together (whole heads
   // at the o projection).  With one contiguous range per split, half of the vector 6 times the other
-  // took 26.1 us for 4096 -> 22016 and 59.5 for 28672 -> 8192, where even inputs take 21.2 and 50.5.
+  // took 26.1 us for 4096 -> 22016 and 54.6 for 28672 -> 8192, where even inputs take 21.2 and 50.5.
   // Wave w of every split has its groups in the same sixteenth of the vector, its stretch; it counts
   // the ties of all of that for their ranks, so what it took stays in its own registers.
   struct Early {
