@@ -8,8 +8,8 @@
 // instead); per 256 channels, turn the mask words into Xm[j][b] = X[b][j] if
 // token b keeps channel j else 0 (fp16, 8 tokens per row = one 16-byte load in the GEMV) and into
 // the range's part of the ascending union U; move the parts into place behind the lower ranges.
-// Step 2: the gathered GEMV of gemv_f16.hip over U with B accumulator sets per lane; every
-// weight row of the union is read once for all tokens.
+// Step 2: the gathered product over U on the matrix cores; every weight row of the union is read
+// once for all tokens.
 #include "af_internal.h"
 
 #define UB_THREADS 1024
@@ -113,9 +113,8 @@ __global__ __launch_bounds__(UP_THREADS) void union_place_kernel(UnionBuildParam
   if (r == 0 && tid == 0) *p.union_n = s_total;
 }
 
-#define UG_THREADS 256
-#define UG_WAVES (UG_THREADS / AF_WAVE)
-#define UG_CHUNK 512
+#define UG_THREADS 1024
+#define UG_CHUNK 2048  // rows staged at a time
 
 struct UnionGemvParams {
   const half_t* W;
@@ -129,53 +128,41 @@ struct UnionGemvParams {
   int out, ld, nidx_host, y_kind, out_pad, B;
 };
 
-// U rows times NB tokens into the accumulators.  NB >= 4: the rows are taken in pairs through
-// v_dot2_f32_f16 (two products and the add in one instruction; 16 packs + 64 dot instructions per
-// row pair instead of 128 multiply-adds at NB = 8), because at eight tokens the multiply-adds, not
-// the weight stream, were what the kernel waited for (vector ALU busy 59 %; gate|up of the 70B
-// shape 188 -> 172 us; at four tokens the change is neutral).  Zero rows may be
-// passed for the masked end of a list.
-template <int NB, int U>
-__device__ __forceinline__ void union_accumulate(float (&acc)[NB][8], const half8 (&w)[U], const half8 (&xm)[U]) {
-  if constexpr (NB >= 4 && U % 2 == 0) {
-#pragma unroll
-    for (int u = 0; u < U; u += 2) {
-      half2v wp[8];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) wp[c] = half2v{w[u][c], w[u + 1][c]};
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const half2v xp = half2v{xm[u][b], xm[u + 1][b]};
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[b][c] = __builtin_amdgcn_fdot2(wp[c], xp, acc[b][c], false);
-      }
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const float xv = (float)xm[u][b];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) acc[b][c] += (float)w[u][c] * xv;
-      }
-    }
-  }
-}
-
-template <int NB, int LX, int U>
+// Workgroup (tile, split): sixteen waves, CW of them side by side across a tile of 128 * CW columns,
+// the others on different rows.  In a wave 16 lanes span 128 columns (16 bytes each) and its four
+// lane groups take eight rows each, so a step is 32 rows: the lane that has loaded eight rows holds,
+// for each of its eight columns, the eight consecutive contraction elements that a lane supplies to
+// the 16x16x32 matrix instruction, four byte permutations away.  Eight of those (one per column; the
+// tokens in the rows of the result, half of which stay unused) take the place of 64 B multiply-adds
+// per row pair, add up the lane groups on the way and need 32 accumulators where eight tokens
+// needed 64.  The kernel streams the union (4.6 to 6.4 TB/s at the 70B shape).
+// One such workgroup per compute unit: 256-thread workgroups needed 38 to 48 splits to fill the
+// chip, and the last one of a tile then added up 48 x 2048 partial sums on its own.  us with the
+// builder, 50 % of the channels kept, 1 / 4 / 8 tokens, before (vector unit, 256 threads) and now:
+//   8192 -> 10240  32.3 / 49.1 / 56.2   25.7 / 37.7 / 41.2     8192 -> 57344  87.4 / 157.6 / 171.8   79.5 / 137.9 / 147.3
+//   8192 -> 8192   31.1 / 46.5 / 53.9   24.0 / 33.7 / 35.9     28672 -> 8192  52.5 / 96.5 / 105.9    50.5 / 81.3 / 86.6
+//   4096 -> 4096   25.4 / 49.7 / 54.8   18.3 / 18.7 / 19.9     11008 -> 4096  41.3 / 56.0 / 61.3     20.8 / 27.4 / 29.4
+// (the same large workgroups on the vector unit: 8192 -> 57344 80.9 / 139.5 / 155.9, 28672 -> 8192
+// 49.1 / 81.5 / 92.5; two 512-thread workgroups per unit: within 1 % of one of 1024).
+template <int CW>
 __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams p) {
-  constexpr int LY = AF_WAVE / LX;
-  constexpr int TW = LX * 8;
-  constexpr int STEP = UG_WAVES * LY;
-  __shared__ int s_idx[UG_CHUNK];
-  __shared__ half8 s_xm[UG_CHUNK];
-  __shared__ float s_red[UG_WAVES][NB][TW];
+  typedef float float4v __attribute__((ext_vector_type(4)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int THREADS = UG_THREADS;
+  constexpr int TW = 128 * CW, RW = UG_THREADS / AF_WAVE / CW;
+  constexpr int XLD = UG_CHUNK + 8;  // 16 bytes further per token: another bank group
+  constexpr int STAGE_BYTES = 8 * XLD * 2 + UG_CHUNK * 4, RED_BYTES = RW * 4 * TW * 4;
+  __shared__ __align__(16) char s_mem[STAGE_BYTES > RED_BYTES ? STAGE_BYTES : RED_BYTES];
+  half_t* s_x = reinterpret_cast<half_t*>(s_mem);  // [token][staged row]
+  int* s_idx = reinterpret_cast<int*>(s_mem + 8 * XLD * 2);
+  float(*s_red)[4][TW] = reinterpret_cast<float(*)[4][TW]>(s_mem);  // behind the row loop
   __shared__ int s_last;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lx = lane % LX, ly = lane / LX;
-  const int col = blockIdx.x * TW + lx * 8;
+  const int lx = lane & 15, g = lane >> 4;
+  const int cw = wave % CW, rw = wave / CW;
+  const int tile0 = blockIdx.x * TW;
+  const int col = tile0 + cw * 128 + lx * 8;
   const int col_ld = col < p.out ? col : 0;
   const int S = gridDim.y, s = blockIdx.y;
 
@@ -183,65 +170,63 @@ __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams 
   const int R = af_ceil_div_small(nidx, S);
   const int r0 = min(s * R, nidx), r1 = min(r0 + R, nidx);
 
-  float acc[NB][8];
+  float4v acc[8];
 #pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[b][c] = 0.f;
+  for (int c = 0; c < 8; ++c) acc[c] = float4v{0.f, 0.f, 0.f, 0.f};
   const half_t* wcol = p.W + col_ld;
+
+  auto multiply = [&](const u32x4 (&w)[8], int pos) __attribute__((always_inline)) {
+    const half8 a = *reinterpret_cast<const half8*>(s_x + (lane & 7) * XLD + pos);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      u32x4 b;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        b[i] = __builtin_amdgcn_perm(w[2 * i + 1][c / 2], w[2 * i][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
+      // The step's sum starts from zero and joins the others in a rounded addition: with the running
+      // sum as the instruction's addend the error against 64 bits grew with the number of steps
+      // (8192 -> 57344, four tokens: 2.07e-7; 1.25e-7 this way, 1.30e-7 on the vector unit).
+      acc[c] += __builtin_amdgcn_mfma_f32_16x16x32_f16(a, __builtin_bit_cast(half8, b), float4v{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+  };
 
   for (int base = r0; base < r1; base += UG_CHUNK) {
     const int cnt = min(UG_CHUNK, r1 - base);
     __syncthreads();
-    for (int i = tid; i < cnt; i += UG_THREADS) {
-      const int j = p.idx[base + i];
+    for (int i = tid; i < (cnt + 31) / 32 * 32; i += THREADS) {  // whole steps: zeros behind the end
+      const int j = i < cnt ? p.idx[base + i] : 0;
+      half8 x = *reinterpret_cast<const half8*>(p.Xm + (size_t)j * 8);
       s_idx[i] = j;
-      s_xm[i] = *reinterpret_cast<const half8*>(p.Xm + (size_t)j * 8);
+#pragma unroll
+      for (int b = 0; b < 8; ++b) s_x[b * XLD + i] = i < cnt ? x[b] : (half_t)0;
     }
     __syncthreads();
-    int i = wave * LY + ly;
-    half8 zero8;
+    int i = rw * 32;
+    for (; i + 32 <= cnt; i += RW * 32) {
+      u32x4 w[8];
+      int j[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) zero8[c] = (half_t)0;
-    for (; i + (U - 1) * STEP < cnt; i += U * STEP) {
-      half8 w[U], xm[U];
+      for (int u = 0; u < 8; ++u) j[u] = s_idx[i + g * 8 + u];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        w[u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)s_idx[i + u * STEP] * p.ld));
-#pragma unroll
-      for (int u = 0; u < U; ++u) xm[u] = s_xm[i + u * STEP];
-      union_accumulate<NB, U>(acc, w, xm);
+      for (int u = 0; u < 8; ++u)
+        w[u] = af_load_once(reinterpret_cast<const u32x4*>(wcol + (size_t)j[u] * p.ld));
+      __builtin_amdgcn_sched_barrier(0);
+      multiply(w, i + g * 8);
     }
-    // ragged end: one masked batch of the same depth, its loads in flight together
-    if (i < cnt) {
-      half8 w[U], xm[U];
+    if (i < cnt) {  // the last step of the list: its missing rows are zero
+      u32x4 w[8];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool ok = i + u * STEP < cnt;
-        w[u] = ok ? af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)s_idx[i + u * STEP] * p.ld)) : zero8;
-        xm[u] = ok ? s_xm[i + u * STEP] : zero8;
+      for (int u = 0; u < 8; ++u) {
+        w[u] = u32x4{0u, 0u, 0u, 0u};
+        if (i + g * 8 + u < cnt)
+          w[u] = af_load_once(reinterpret_cast<const u32x4*>(wcol + (size_t)s_idx[i + g * 8 + u] * p.ld));
       }
-      union_accumulate<NB, U>(acc, w, xm);
+      multiply(w, i + g * 8);
     }
   }
 
-#pragma unroll
-  for (int off = LX; off < AF_WAVE; off <<= 1)
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[b][c] += __shfl_xor(acc[b][c], off, AF_WAVE);
-  if (ly == 0) {
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) s_red[wave][b][lx * 8 + c] = acc[b][c];
-  }
-  __syncthreads();
-
-  const int tile0 = blockIdx.x * TW;
   auto store = [&](int b, int colg, float v) {
-    if (b < p.B && colg < p.out) {
+    if (colg < p.out) {
       if (p.residual) v += (float)p.residual[(size_t)b * p.out + colg];
       if (p.y_kind == AF_F16)
         reinterpret_cast<half_t*>(p.Y)[(size_t)b * p.out + colg] = (half_t)v;
@@ -249,24 +234,30 @@ __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams 
         reinterpret_cast<float*>(p.Y)[(size_t)b * p.out + colg] = v;
     }
   };
-  if (S == 1) {
-    for (int e = tid; e < NB * TW; e += UG_THREADS) {
+  // Lane group h holds tokens 4 h .. 4 h + 3: added up over the waves one group at a time.
+  float* mine = p.partials + (size_t)s * p.B * p.out_pad;
+  for (int h = 0; h * 4 < p.B; ++h) {
+    __syncthreads();  // the staged rows, or the sums of the tokens before, have been read
+    if (g == h) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) s_red[rw][r][cw * 128 + lx * 8 + c] = acc[c][r];
+    }
+    __syncthreads();
+    const int nb = min(4, p.B - h * 4);
+    for (int e = tid; e < nb * TW; e += THREADS) {
       const int b = e / TW, c = e % TW;
       float v = 0.f;
 #pragma unroll
-      for (int w = 0; w < UG_WAVES; ++w) v += s_red[w][b][c];
-      store(b, tile0 + c, v);
+      for (int w = 0; w < RW; ++w) v += s_red[w][b][c];
+      if (S == 1)
+        store(h * 4 + b, tile0 + c, v);
+      else
+        af_store_agent(mine + (size_t)(h * 4 + b) * p.out_pad + tile0 + c, v);
     }
-    return;
   }
-  float* mine = p.partials + (size_t)s * NB * p.out_pad;
-  for (int e = tid; e < NB * TW; e += UG_THREADS) {
-    const int b = e / TW, c = e % TW;
-    float v = 0.f;
-#pragma unroll
-    for (int w = 0; w < UG_WAVES; ++w) v += s_red[w][b][c];
-    af_store_agent(mine + (size_t)b * p.out_pad + tile0 + c, v);
-  }
+  if (S == 1) return;
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
@@ -275,10 +266,10 @@ __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams 
   }
   __syncthreads();
   if (!s_last) return;
-  for (int e = tid; e < NB * TW; e += UG_THREADS) {
+  for (int e = tid; e < p.B * TW; e += THREADS) {
     const int b = e / TW, c = e % TW;
     store(b, tile0 + c,
-          af_sum_partials(p.partials + (size_t)b * p.out_pad + tile0 + c, (size_t)NB * p.out_pad, S));
+          af_sum_partials(p.partials + (size_t)b * p.out_pad + tile0 + c, (size_t)p.B * p.out_pad, S));
   }
   if (tid == 0) af_ticket_reset(&p.tickets[blockIdx.x]);
 }
@@ -311,19 +302,26 @@ int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
   hipLaunchKernelGGL(union_place_kernel, dim3(bp.ranges), dim3(UP_THREADS), 0, ctx->stream, bp);
   AF_LAUNCH_CHECK();
 
-  const int NB = B == 1 ? 1 : (B == 2 ? 2 : (B <= 4 ? 4 : 8));
-  const int lx = (out <= 2048) ? 16 : 32;
-  const int tw = lx * 8;
+  // Tile width: narrow outputs fill the chip with 128 columns and few splits (8192 -> 8192, eight
+  // tokens: 35.9 us with 128 columns and 4 splits, 38.4 with 256 and 8; 11008 -> 4096 29.4 / 31.0);
+  // from there on longer pieces of a row count for more (8192 -> 10240 41.4 / 41.2, 8192 -> 57344
+  // 164.7 / 147.1; 512 columns 151.9).
+  int cw = out <= 8192 ? 1 : 2;
+  if (ctx->tune_lx == 16) cw = 1;
+  if (ctx->tune_lx == 32) cw = 2;
+  const int tw = cw * 128;
   const int tiles = (out + tw - 1) / tw;
   const int out_pad = tiles * tw;
   if (tiles > AF_TICKET_ATTN) return AF_ESHAPE;
   const int nidx_max = (long long)B * k < in ? B * k : in;
-  int S = (ctx->n_cu * 8 + tiles - 1) / tiles;
+  int S = ctx->n_cu / tiles;  // one workgroup per compute unit
+  if (ctx->tune_split > 0) S = ctx->tune_split;
   int max_s = (nidx_max + 31) / 32;
   if (max_s < 1) max_s = 1;
   if (S > max_s) S = max_s;
   if (S > 256) S = 256;
-  while (S > 1 && (size_t)S * NB * out_pad > ctx->lay.partial_floats) --S;
+  if (S < 1) S = 1;
+  while (S > 1 && (size_t)S * B * out_pad > ctx->lay.partial_floats) --S;
 
   UnionGemvParams p;
   p.W = (const half_t*)u.Wt;
@@ -340,21 +338,11 @@ int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
   p.y_kind = u.y_kind;
   p.out_pad = out_pad;
   p.B = B;
-  dim3 grid(tiles, S), block(UG_THREADS);
-#define UNION_LAUNCH(NBV, LXV, UV) \
-  hipLaunchKernelGGL((gemv_union_kernel<NBV, LXV, UV>), grid, block, 0, ctx->stream, p)
-  if (lx == 16) {
-    if (NB == 1) UNION_LAUNCH(1, 16, 8);
-    else if (NB == 2) UNION_LAUNCH(2, 16, 8);
-    else if (NB == 4) UNION_LAUNCH(4, 16, 4);
-    else UNION_LAUNCH(8, 16, 4);
-  } else {
-    if (NB == 1) UNION_LAUNCH(1, 32, 8);
-    else if (NB == 2) UNION_LAUNCH(2, 32, 8);
-    else if (NB == 4) UNION_LAUNCH(4, 32, 4);
-    else UNION_LAUNCH(8, 32, 4);
-  }
-#undef UNION_LAUNCH
+  dim3 grid(tiles, S);
+  if (cw == 1)
+    hipLaunchKernelGGL(gemv_union_kernel<1>, grid, dim3(UG_THREADS), 0, ctx->stream, p);
+  else
+    hipLaunchKernelGGL(gemv_union_kernel<2>, grid, dim3(UG_THREADS), 0, ctx->stream, p);
   AF_LAUNCH_CHECK();
   return AF_OK;
 }

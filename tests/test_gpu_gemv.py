@@ -209,6 +209,34 @@ def test_union_70b_shapes_sampled(ctx, name, out, n, Bt):
         assert np.array_equal(to_host(got), idx_b[b])
 
 
+@pytest.mark.parametrize("tokens", [1, 4, 5, 8])
+@pytest.mark.parametrize("out,n,k,split,scale", [
+    (8, 8, 1, 0, 1.0),           # one row, one lane's columns
+    (136, 64, 31, 1, 1.0),       # one row short of a step of 32; a tile with one more lane
+    (256, 64, 33, 1, 1.0),       # ... and one more
+    (8200, 300, 257, 0, 1.0),    # 256-column tiles, the last one of 8 columns
+    (264, 4400, 2049, 1, 1.0),   # more rows than are staged at a time
+    (520, 600, 300, 3, 2.0 ** -15),  # most weights below the smallest normal fp16
+])
+def test_union_steps_and_tiles(ctx, tokens, out, n, k, split, scale):
+    """Edges of the matrix-instruction kernel: row lists around its steps of 32 rows and its staging
+    passes, tiles of both widths with a remainder, all three counts of used result rows, subnormal
+    weights.  The bound is that of the other fp32 results (products exact, sums in fp32)."""
+    rng = np.random.default_rng(out + n + tokens)
+    W = (rng.standard_normal((out, n)) * scale).astype(np.float16)
+    X = rng.standard_normal((tokens, n)).astype(np.float16)
+    idx_b = np.stack([np.sort(rng.choice(n, size=k, replace=False)).astype(np.int32) for _ in range(tokens)])
+    ctx.set_option(B.AF_OPT_TUNE_SPLIT, split)
+    try:
+        Y, _, _ = ctx.sparse_gemv_union_f16(ctx.pack_inmajor_f16(to_dev(W)), to_dev(X), to_dev(idx_b), y_kind=B.AF_F32)
+        ctx.synchronize()
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+    ref = O.union_gemv(W, X, list(idx_b))
+    for b in range(tokens):
+        assert O.rel_err(to_host(Y)[b], ref[b]) <= 1e-4, b
+
+
 def test_index_precondition_is_reported_not_followed(ctx):
     """An index list that breaks its precondition never makes a kernel read outside the
     caller's buffers: an entry out of range adds nothing and sets AF_DEVERR_IDX; with
