@@ -184,7 +184,7 @@ struct af_union_args {
   const half_t* residual;   // [B][out] or null
 };
 int af_launch_union_f16(af_ctx* ctx, const af_union_args& u);
-// Rotary embedding, KV append and attention of one token (layer.hip).
+// Rotary embedding, KV append and attention of one token (attention.hip).
 int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv, void* kc, void* vc,
                         int kv_len, int kv_cap, int pos, half_t* out);
 // The same for B tokens in one launch; token b's qkv / out lie b * stride elements further.
@@ -206,6 +206,16 @@ __device__ __forceinline__ void af_store_agent(float* p, float v) {
 }
 __device__ __forceinline__ float af_load_agent(const float* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Two neighbouring floats at once (8-byte aligned).
+typedef float af_float2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void af_store_agent2(float* p, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p),
+                     __builtin_bit_cast(unsigned long long, (af_float2{a, b})), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ af_float2 af_load_agent2(const float* p) {
+  return __builtin_bit_cast(af_float2, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p),
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 // Sum of S partials p[0], p[stride], ... in index order, with up to 16 loads in flight.
 __device__ __forceinline__ float af_sum_partials(const float* p, size_t stride, int S) {

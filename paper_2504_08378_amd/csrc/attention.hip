@@ -1,0 +1,470 @@
+// Decode attention of one token (or of one token each of B sequences): rotary embedding of the new
+// q and k, append to the KV cache, softmax attention over the cache and the new token.
+//
+// Workgroup (key head and up to 8 of the query heads that share it, key split): every key and
+// value row is read once for all of those heads.  A wave takes 32 keys at a time through the matrix
+// cores and keeps a running softmax of its own; nothing is exchanged between the waves before each
+// of them has gone through its keys, so a workgroup has one barrier up to its sums, and the first
+// key / value rows are requested together with q.
+//   scores   D[key][head] = K Q^T, 16 keys x 16 heads per instruction: a lane supplies eight
+//            consecutive dimensions of one key row, which is the load it has made, and gets four
+//            keys of one head, so the softmax of a head runs along the registers of four lanes;
+//   values   D[dim][head] = V^T P^T: a lane supplies eight keys of one dimension.  Which keys is
+//            free as long as both operands agree, so it takes the eight whose probabilities it
+//            has already (no transposition of P), loads those eight rows of V and picks the
+//            columns by byte permutation.
+// q and the probabilities are held in fp32; each enters as two fp16 values (the rounded one and 2^11
+// times what the rounding left, 22 significant bits) in two instructions whose results are added in
+// fp32, so the products lose no more than fp32 ones.
+// What bounds it: latency at short contexts (load, scores, softmax, values, partial sums to the last
+// workgroup of a head), the read of the cache at long ones.  With one workgroup per query head, which
+// read the rows of a key head once for each of its query heads, us per layer (attention and short
+// GEMVs), before / now: 64 heads on 8 key heads, 512 keys 52.5 / 51.0, 2000 keys 61.0 / 52.5, 6001 keys
+// 82.3 / 57.5; 32 on 8, 512 keys 44.0 / 43.0, 4000 keys 53.2 / 47.0; 32 on 32, 512 keys 44.3 / 44.3, 8000
+// keys 63.4 / 62.4.  (A first version that rotated q in every lane, 300 instructions of one wave, was
+// 2 us slower throughout.)  The error of the fp16 result against 64 bits is that of the rounding alone
+// (2.0942e-4 at 32 heads and 512 keys, before and now).
+#include <math.h>
+
+#include "attention.h"
+
+#define ATT_THREADS 256
+#define ATT_WAVES (ATT_THREADS / AF_WAVE)
+#define ATT_HEADS 8        // query heads of one workgroup
+#define ATT_STEP 32        // keys of a wave per step
+#define ATT_MAX_KEYS 2048  // cache keys per key split
+
+typedef float att_f4 __attribute__((ext_vector_type(4)));
+typedef half_t att_h2 __attribute__((ext_vector_type(2)));
+typedef unsigned short att_us2 __attribute__((ext_vector_type(2)));
+typedef half_t att_h4 __attribute__((ext_vector_type(4)));
+
+// The two results of a split factor together.  An infinite key times the zero that a rest may be is NaN:
+// then the other result has the infinity, and the NaN is put aside (the median ignores it).
+__device__ __forceinline__ float att_join(float hi, float lo) {
+  return hi + __builtin_amdgcn_fmed3f(lo, -3.0e38f, 3.0e38f) * (1.0f / 2048.0f);
+}
+
+// a * b + c rounded to fp16 once, the last step of a rotated key.  With a conversion of an fp32
+// fma in its place, which is what the compiler makes of other surroundings, some elements of the cache
+// differ in their last bit.
+__device__ __forceinline__ half_t att_fma_half(half_t a, float b, float c) {
+  unsigned d;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]"
+      : "=v"(d)
+      : "v"((unsigned)__builtin_bit_cast(unsigned short, a)), "v"(b), "v"(c));
+  return __builtin_bit_cast(half_t, (unsigned short)d);
+}
+
+// cs / sn: the rotary table of the token's position.  bx: number of the (key head, head group).
+template <int HD>
+__device__ __forceinline__ void attn_decode_body(const AttnParams& p, const float* cs_tab, const float* sn_tab,
+                                                 const int bx, const int s, const int KS) {
+  constexpr int TT = HD / 32;   // contraction steps of the scores
+  constexpr int VC = HD / 16;   // value columns of a lane
+  constexpr int QLD = HD + 8;
+  typedef half_t vrow __attribute__((ext_vector_type(VC)));
+  typedef unsigned vwords __attribute__((ext_vector_type(VC / 2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
+  __shared__ __align__(16) half_t s_q[2][ATT_HEADS][QLD];  // rotated queries: rounded, and 2^11 times the rest
+  __shared__ __align__(16) half_t s_kn[HD], s_vn[HD];      // the new token's row
+  __shared__ __align__(16) float s_acc[ATT_WAVES][ATT_HEADS][HD + 4];
+  __shared__ float2 s_ml[ATT_WAVES][ATT_HEADS];
+  __shared__ int s_last;
+
+  af_prof_begin(p.prof);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int rep = p.n_heads / p.n_kv, groups = (rep + ATT_HEADS - 1) / ATT_HEADS;
+  const int kvh = groups == 1 ? bx : bx / groups, grp = bx - kvh * groups;
+  const int heads = min(ATT_HEADS, rep - grp * ATT_HEADS), h0 = kvh * rep + grp * ATT_HEADS;
+  const int T = p.kv_len;  // the new token's place
+  // cached keys of a split, in whole steps; the last split has the new token as well
+  const int KP = (af_ceil_div_small(T, KS) + ATT_STEP - 1) / ATT_STEP * ATT_STEP;
+  const bool owns_new = s == KS - 1;
+  const int t0 = min(s * KP, T), t1 = owns_new ? T + 1 : min(t0 + KP, T);
+
+  // Four rotated pairs per thread: of a query head's, or of the new key's, which is the last "head".
+  const int rh = tid / (HD / 8), ri = tid % (HD / 8) * 4;
+  const half_t* vn = p.qkv + (size_t)(p.n_heads + p.n_kv + kvh) * HD;
+  const half_t* rsrc = rh < heads ? p.qkv + (size_t)(h0 + rh) * HD : p.qkv + (size_t)(p.n_heads + kvh) * HD;
+  const att_h4 ra = *reinterpret_cast<const att_h4*>(rsrc + ri), rb = *reinterpret_cast<const att_h4*>(rsrc + ri + HD / 2);
+  att_f4 rc, rs;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    rc[j] = cs_tab[ri + j];
+    rs[j] = sn_tab[ri + j];
+  }
+  const half8 vnew = *reinterpret_cast<const half8*>(vn + tid % (HD / 8) * 8);
+
+  const half_t* Kc = p.k_cache + (size_t)kvh * p.kv_cap * HD;
+  const half_t* Vc = p.v_cache + (size_t)kvh * p.kv_cap * HD;
+  // Rows of a step; what lies behind the cache is read as its last row and replaced or masked.
+  half8 kr[2][TT];
+  vrow vr[8];
+  const int last = max(min(t1, T) - 1, 0);
+  auto fetch = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const unsigned o = (unsigned)min(k0 + i * 16 + n, last) * HD + g * 8;
+#pragma unroll
+      for (int t = 0; t < TT; ++t) kr[i][t] = af_load_once(reinterpret_cast<const half8*>(Kc + o + t * 32));
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const unsigned o = (unsigned)min(k0 + (j >> 2) * 16 + g * 4 + (j & 3), last) * HD + n * VC;
+      vr[j] = af_load_once(reinterpret_cast<const vrow*>(Vc + o));
+    }
+  };
+  int k0 = t0 + wave * ATT_STEP;
+  if (k0 < t1) fetch(k0);
+  __builtin_amdgcn_sched_barrier(0);
+
+  if (rh <= heads) {
+    att_h4 h[2], lo[2];
+    // the exponentials below are powers of two
+    const float scale = 1.44269504088896340736f / sqrtf((float)HD);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float a = (float)ra[j], b = (float)rb[j];
+      const float x[2] = {__builtin_fmaf(a, rc[j], -(b * rs[j])), __builtin_fmaf(b, rc[j], a * rs[j])};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float q = x[e] * scale;
+        h[e][j] = (half_t)q;
+        lo[e][j] = (half_t)((q - (float)h[e][j]) * 2048.0f);
+      }
+      if (rh == heads) {
+        h[0][j] = att_fma_half(ra[j], rc[j], -(b * rs[j]));
+        h[1][j] = att_fma_half(rb[j], rc[j], a * rs[j]);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      if (rh < heads) {
+        *reinterpret_cast<att_h4*>(&s_q[0][rh][ri + e * (HD / 2)]) = h[e];
+        *reinterpret_cast<att_h4*>(&s_q[1][rh][ri + e * (HD / 2)]) = lo[e];
+      } else {
+        *reinterpret_cast<att_h4*>(&s_kn[ri + e * (HD / 2)]) = h[e];  // fp16, as in the cache
+        if (owns_new && grp == 0)
+          *reinterpret_cast<att_h4*>(const_cast<half_t*>(Kc) + (size_t)T * HD + ri + e * (HD / 2)) = h[e];
+      }
+    }
+  }
+  if (tid < HD / 8) {
+    *reinterpret_cast<half8*>(&s_vn[tid * 8]) = vnew;
+    if (owns_new && grp == 0) *reinterpret_cast<half8*>(const_cast<half_t*>(Vc) + (size_t)T * HD + tid * 8) = vnew;
+  }
+  __syncthreads();
+
+  float m = -INFINITY, l = 0.f;  // of head n: maximum (uniform over the lane groups), this lane's sum
+  att_f4 acc[VC];                // dimensions (4 g + r) VC + c of head n
+  const att_f4 zero4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < VC; ++c) acc[c] = zero4;
+  const int hn = min(n, heads - 1);  // the rest of the result's columns repeat the last head
+  while (k0 < t1) {
+    const bool edge = k0 + ATT_STEP > min(t1, T);
+    if (edge) {  // the new token's row
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (k0 + i * 16 + n == T) {
+#pragma unroll
+          for (int t = 0; t < TT; ++t) kr[i][t] = *reinterpret_cast<const half8*>(&s_kn[t * 32 + g * 8]);
+        }
+    }
+    // scores of keys k0 + 16 i + 4 g + r, head n
+    float sc[8];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      att_f4 dh = zero4, dl = zero4;
+#pragma unroll
+      for (int t = 0; t < TT; ++t) {  // added outside the instruction, rounded
+        dh += __builtin_amdgcn_mfma_f32_16x16x32_f16(kr[i][t], *reinterpret_cast<const half8*>(&s_q[0][hn][t * 32 + g * 8]), zero4, 0, 0, 0);
+        dl = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr[i][t], *reinterpret_cast<const half8*>(&s_q[1][hn][t * 32 + g * 8]), dl, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[i * 4 + r] = att_join(dh[r], dl[r]);
+    }
+    vwords vw[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) vw[j] = __builtin_bit_cast(vwords, vr[j]);
+    if (edge) {
+      const vwords vnw = __builtin_bit_cast(vwords, *reinterpret_cast<const vrow*>(&s_vn[n * VC]));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int key = k0 + (j >> 2) * 16 + g * 4 + (j & 3);
+        if (key == T) vw[j] = vnw;
+        if (key >= t1) {  // behind the split's end: no weight, and no value
+          sc[j] = -INFINITY;
+#pragma unroll
+          for (int c = 0; c < VC / 2; ++c) vw[j][c] = 0u;
+        }
+      }
+    }
+    // running softmax
+    float mx = sc[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) mx = fmaxf(mx, sc[j]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, AF_WAVE));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, AF_WAVE));
+    mx = fmaxf(mx, m);
+    const float safe = mx == -INFINITY ? 0.f : mx;  // nothing but keys without weight so far
+    if (__any(m != mx) && k0 >= t0 + ATT_WAVES * ATT_STEP) {
+      const float corr = __builtin_amdgcn_exp2f(m - safe);
+      l *= corr;
+#pragma unroll
+      for (int c = 0; c < VC; ++c) acc[c] *= corr;
+    }
+    m = mx;
+    // Weights times 2^15 (in the range of fp16) as a rounded down value and the rest.  Neither is negative,
+    // and the rest is never zero: an infinite value stays infinite.
+    u32x4 ph, pl;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float e0 = __builtin_amdgcn_exp2f(sc[2 * i] - (safe - 15.f)), e1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - (safe - 15.f));
+      l += e0 + e1;
+      const fp16x2 hi = __builtin_amdgcn_cvt_pkrtz(e0, e1);
+      const att_h2 rest = {(half_t)(e0 - (float)hi[0]), (half_t)(e1 - (float)hi[1])};
+      ph[i] = __builtin_bit_cast(unsigned, hi);
+      pl[i] = __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(att_us2, rest), att_us2{1, 1}));
+    }
+#pragma unroll
+    for (int c = 0; c < VC; ++c) {
+      u32x4 a;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a[i] = __builtin_amdgcn_perm(vw[2 * i + 1][c / 2], vw[2 * i][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
+      const half8 a8 = __builtin_bit_cast(half8, a);
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pl), acc[c], 0, 0, 0);
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, ph), acc[c], 0, 0, 0);
+    }
+    k0 += ATT_WAVES * ATT_STEP;
+    if (k0 < t1) fetch(k0);
+  }
+  l += __shfl_xor(l, 16, AF_WAVE);
+  l += __shfl_xor(l, 32, AF_WAVE);
+
+  // the waves' sums
+  if (n < heads) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int c = 0; c < VC; ++c) s_acc[wave][n][(g * 4 + r) * VC + c] = acc[c][r];
+    if (g == 0) s_ml[wave][n] = make_float2(m, l);
+  }
+  __syncthreads();
+  const int d = lane * 2;  // two dimensions per lane, a head per wave
+  for (int hh = wave; hh < heads; hh += ATT_WAVES) {
+    float M = -INFINITY, L = 0.f, v0 = 0.f, v1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < ATT_WAVES; ++w) M = fmaxf(M, s_ml[w][hh].x);
+    const float safe = M == -INFINITY ? 0.f : M;
+#pragma unroll
+    for (int w = 0; w < ATT_WAVES; ++w) {
+      const float f = __builtin_amdgcn_exp2f(s_ml[w][hh].x - safe);
+      L += f * s_ml[w][hh].y;
+      if (d < HD) {
+        v0 += f * s_acc[w][hh][d];
+        v1 += f * s_acc[w][hh][d + 1];
+      }
+    }
+    float* mine = p.part + ((size_t)(h0 + hh) * KS + s) * (HD + 2);
+    if (d < HD) {
+      if (KS == 1)
+        *reinterpret_cast<half2v*>(p.out + (size_t)(h0 + hh) * HD + d) = half2v{(half_t)(v0 / L), (half_t)(v1 / L)};
+      else
+        af_store_agent2(mine + 2 + d, v0, v1);
+    }
+    if (KS > 1 && lane == 0) af_store_agent2(mine, M, L);
+  }
+  if (KS == 1) {
+    af_prof_end(p.prof);
+    return;
+  }
+  af_stores_done();
+  __syncthreads();
+  if (tid == 0) {
+    int old = af_ticket_take(&p.tickets[bx]);
+    s_last = (old == KS - 1);
+  }
+  __syncthreads();
+  if (!s_last) {
+    af_prof_end(p.prof);
+    return;
+  }
+  // The splits of each head, in split order.  Lane q has the maximum and the weight of split q (KS <= 64); the
+  // partials come from other XCDs, so they are fetched sixteen at a time, the first together with those.
+  for (int hh = wave; hh < heads; hh += ATT_WAVES) {
+    const float* part = p.part + (size_t)(h0 + hh) * KS * (HD + 2);
+    const af_float2 ml = af_load_agent2(part + min(lane, KS - 1) * (HD + 2));
+    float v0 = 0.f, v1 = 0.f, f = 0.f, L = 1.f;
+    for (int q0 = 0; q0 < KS; q0 += 16) {
+      af_float2 av[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        av[u] = af_load_agent2(part + min(q0 + u, KS - 1) * (HD + 2) + 2 + (d < HD ? d : 0));
+      if (q0 == 0) {
+        float M = lane < KS ? ml[0] : -INFINITY;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, AF_WAVE));
+        f = lane < KS ? __builtin_amdgcn_exp2f(ml[0] - (M == -INFINITY ? 0.f : M)) : 0.f;
+        L = af_wave_sum(lane < KS ? f * ml[1] : 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        if (q0 + u < KS) {
+          const float w = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, f), q0 + u));
+          v0 += w * av[u][0];
+          v1 += w * av[u][1];
+        }
+      }
+    }
+    if (d < HD)
+      *reinterpret_cast<half2v*>(p.out + (size_t)(h0 + hh) * HD + d) = half2v{(half_t)(v0 / L), (half_t)(v1 / L)};
+  }
+  if (tid == 0) af_ticket_reset(&p.tickets[bx]);
+  af_prof_end(p.prof);
+}
+
+template <int HD>
+__global__ __launch_bounds__(ATT_THREADS) void attn_decode_kernel(AttnParams p) {
+  attn_decode_body<HD>(p, p.cs, p.sn, blockIdx.x, blockIdx.y, gridDim.y);
+}
+
+// The same for B tokens in one launch (af_decode_layer_batch): grid (key heads x head groups, key splits, tokens);
+// every token has its own caches, length, position and number of key splits.  The rotary table
+// of a token is formed here, in fp64 like the host does for the single-token launch
+// (angle = pos * theta^(-2i/HD) with the host's theta^(-2i/HD)).
+struct AttnBatchParams {
+  AttnParams base;          // token 0's qkv / out, the shared sizes; cs / sn unused
+  half_t* k_caches[AF_MAX_BATCH];
+  half_t* v_caches[AF_MAX_BATCH];
+  int kv_lens[AF_MAX_BATCH];
+  int poss[AF_MAX_BATCH];
+  int splits[AF_MAX_BATCH];  // key splits of each token
+  double inv_freq[64];
+  long long qkv_stride, out_stride, part_stride;  // elements between the tokens
+};
+
+template <int HD>
+__global__ __launch_bounds__(ATT_THREADS) void attn_decode_batch_kernel(AttnBatchParams bp) {
+  __shared__ float s_cs[HD / 2], s_sn[HD / 2];
+  const int b = blockIdx.z;
+  const int KS = bp.splits[b];
+  if ((int)blockIdx.y >= KS) return;  // uniform for the workgroup: this token has fewer splits
+  AttnParams p = bp.base;
+  p.qkv += (size_t)b * bp.qkv_stride;
+  p.out += (size_t)b * bp.out_stride;
+  p.part += (size_t)b * bp.part_stride;
+  p.tickets += b * p.n_heads;
+  p.k_cache = bp.k_caches[b];
+  p.v_cache = bp.v_caches[b];
+  p.kv_len = bp.kv_lens[b];
+  if (threadIdx.x < HD / 2) {
+    const double ang = (double)bp.poss[b] * bp.inv_freq[threadIdx.x];
+    s_cs[threadIdx.x] = (float)cos(ang);
+    s_sn[threadIdx.x] = (float)sin(ang);
+  }
+  __syncthreads();
+  attn_decode_body<HD>(p, s_cs, s_sn, blockIdx.x, blockIdx.y, KS);
+}
+
+static int attn_groups(const af_layer_cfg* cfg) {  // workgroups side by side: key heads x groups of query heads
+  const int rep = cfg->n_heads / cfg->n_kv_heads;
+  return cfg->n_kv_heads * ((rep + ATT_HEADS - 1) / ATT_HEADS);
+}
+
+// Key splits of one token, 0 if the partial results of enough splits do not fit.  One per 64 keys (two
+// waves of 32) up to one workgroup per compute unit and sixteen splits; more only lengthen the sum
+// over them (us per layer, attention and short GEMVs; heads/key heads, keys, at 4 / 8 / 16 / 31 splits):
+//   32/32, 512: 45.2 / 44.1 / 45.3 / 49.8      40/40, 512: 48.5 / 48.0 / 51.4 / 55.5, at 6 splits 47.4
+//   64/8, 2000: 58.9 / 54.1 / 52.3 / 53.9      64/8, 6001: 76.0 / 64.3 / 57.5 / 57.2
+// Where that leaves more than 512 keys to a split, twice as many (32/32, 8000: 8 splits 64.9, 16 62.4).
+static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, size_t floats) {
+  int KS = (kv_len + 63) / 64;
+  int cap = ctx->n_cu / attn_groups(cfg);
+  if (cap > 16) cap = 16;
+  if (cap < 1) cap = 1;
+  if (kv_len > 512 * cap) cap *= 2;
+  if (KS > cap) KS = cap;
+  if (KS < (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS) KS = (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS;  // very long caches
+  if (ctx->tune_attn_splits > 0) KS = ctx->tune_attn_splits;
+  if (KS < 1) KS = 1;
+  if (KS > 64) KS = 64;
+  while (KS > 1 && (size_t)cfg->n_heads * KS * (cfg->head_dim + 2) > floats) --KS;
+  return (kv_len + KS - 1) / KS > ATT_MAX_KEYS ? 0 : KS;
+}
+
+int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv, void* kc, void* vc,
+                        int kv_len, int kv_cap, int pos, half_t* out) {
+  const int KS = attn_splits(ctx, cfg, kv_len, ctx->lay.attn_floats);
+  if (KS == 0) return AF_EINVAL;
+  AttnParams p;
+  p.qkv = qkv;
+  p.k_cache = (half_t*)kc;
+  p.v_cache = (half_t*)vc;
+  p.out = out;
+  p.part = (float*)(ctx->ws + ctx->lay.attn_part);
+  p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
+  p.n_heads = cfg->n_heads;
+  p.n_kv = cfg->n_kv_heads;
+  p.kv_len = kv_len;
+  p.kv_cap = kv_cap;
+  p.head_dim = cfg->head_dim;
+  p.prof = af_prof_take(ctx);
+  for (int i = 0; i < cfg->head_dim / 2; ++i) {
+    const double ang = (double)pos * pow((double)cfg->rope_theta, -2.0 * (double)i / (double)cfg->head_dim);
+    p.cs[i] = (float)cos(ang);
+    p.sn[i] = (float)sin(ang);
+  }
+  dim3 grid(attn_groups(cfg), KS);
+  if (cfg->head_dim == 128)
+    hipLaunchKernelGGL(attn_decode_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, p);
+  else
+    hipLaunchKernelGGL(attn_decode_kernel<64>, grid, dim3(ATT_THREADS), 0, ctx->stream, p);
+  AF_LAUNCH_CHECK();
+  return AF_OK;
+}
+
+int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const half_t* qkv,
+                              long long qkv_stride, void* const* kcs, void* const* vcs, const int* kv_len,
+                              int kv_cap, const int* pos, half_t* out, long long out_stride) {
+  AttnBatchParams bp{};
+  AttnParams& p = bp.base;
+  int ks_max = 1;
+  const size_t per_split = (size_t)cfg->n_heads * (cfg->head_dim + 2);
+  for (int b = 0; b < B; ++b) {
+    const int KS = attn_splits(ctx, cfg, kv_len[b], ctx->lay.attn_floats / B);
+    if (KS == 0) return AF_EINVAL;
+    bp.splits[b] = KS;
+    if (KS > ks_max) ks_max = KS;
+    bp.k_caches[b] = (half_t*)kcs[b];
+    bp.v_caches[b] = (half_t*)vcs[b];
+    bp.kv_lens[b] = kv_len[b];
+    bp.poss[b] = pos[b];
+  }
+  if ((size_t)B * ks_max * per_split > ctx->lay.attn_floats) return AF_EWORKSPACE;
+  p.qkv = qkv;
+  p.out = out;
+  p.part = (float*)(ctx->ws + ctx->lay.attn_part);
+  p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
+  p.n_heads = cfg->n_heads;
+  p.n_kv = cfg->n_kv_heads;
+  p.kv_cap = kv_cap;
+  p.head_dim = cfg->head_dim;
+  p.prof = nullptr;
+  for (int i = 0; i < cfg->head_dim / 2; ++i)
+    bp.inv_freq[i] = pow((double)cfg->rope_theta, -2.0 * (double)i / (double)cfg->head_dim);
+  bp.qkv_stride = qkv_stride;
+  bp.out_stride = out_stride;
+  bp.part_stride = (long long)ks_max * (long long)per_split;
+  dim3 grid(attn_groups(cfg), ks_max, B);
+  if (cfg->head_dim == 128)
+    hipLaunchKernelGGL(attn_decode_batch_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, bp);
+  else
+    hipLaunchKernelGGL(attn_decode_batch_kernel<64>, grid, dim3(ATT_THREADS), 0, ctx->stream, bp);
+  AF_LAUNCH_CHECK();
+  return AF_OK;
+}

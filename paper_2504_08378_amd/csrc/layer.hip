@@ -16,24 +16,9 @@
 #include <stdlib.h>
 
 #include "af_internal.h"
+#include "attention.h"
 #include "row_prologue.h"
 #include "gemv_f16_body.h"
-
-#define ATT_THREADS 256
-#define ATT_WAVES (ATT_THREADS / AF_WAVE)
-#define ATT_MAX_KEYS 2048  // cache keys per (head, split) workgroup
-
-struct AttnParams {
-  const half_t* qkv;   // [q | k | v] of the new token, before rotation
-  half_t* k_cache;     // [n_kv][cap][HD]
-  half_t* v_cache;
-  half_t* out;         // [n_heads*HD]
-  float* part;         // [n_heads][KS][HD+2]
-  int* tickets;        // [n_heads]
-  int n_heads, n_kv, kv_len, kv_cap, head_dim;
-  long long* prof;     // time stamps of this launch (af_profile_set), or null
-  float cs[64], sn[64];  // cos / sin of pos * theta^(-2i/HD), i < HD/2, formed in fp64 on the host
-};
 
 // Output element `c` of one head from the partial results of its KS key splits
 // ([KS][HD + 2]: running maximum, sum of weights, weighted values), summed in split order.  The
@@ -71,343 +56,6 @@ __device__ __forceinline__ float attn_combine(const float* base, const int KS, c
     }
   }
   return v / L;
-}
-
-// One (head, key split) workgroup of the decode attention.  cs / sn: the rotary table of the
-// token's position (kernel arguments for the single-token launch, LDS for the batched one).
-template <int HD>
-__device__ __forceinline__ void attn_decode_body(const AttnParams& p, const float* cs_tab,
-                                                 const float* sn_tab, const int h, const int s,
-                                                 const int KS) {
-  constexpr int LPK = HD / 8;             // lanes per key (8 dims = 16 bytes each)
-  constexpr int KPB = ATT_THREADS / LPK;  // keys per workgroup iteration
-  constexpr int NB = 4;                   // iterations whose loads are issued together
-  __shared__ float s_q[HD];
-  __shared__ float s_knew[HD];
-  __shared__ float s_vnew[HD];
-  __shared__ float s_sc[ATT_MAX_KEYS + 1];
-  __shared__ float s_pv[KPB][HD];
-  __shared__ float s_red[ATT_WAVES];
-  __shared__ int s_last;
-
-  af_prof_begin(p.prof);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int rep = p.n_heads / p.n_kv, kvh = h / rep;
-  const int T = p.kv_len;
-  const int KP = (T + KS - 1) / KS;
-  const int t0 = min(s * KP, T), t1 = min(t0 + KP, T);
-  const int cnt = t1 - t0;
-  const bool owns_new = (s == KS - 1);
-  const int total = cnt + (owns_new ? 1 : 0);
-
-  const half_t* q = p.qkv + (size_t)h * HD;
-  const half_t* kn = p.qkv + (size_t)(p.n_heads + kvh) * HD;
-  const half_t* vn = p.qkv + (size_t)(p.n_heads + p.n_kv + kvh) * HD;
-  half_t* Kc = p.k_cache + (size_t)kvh * p.kv_cap * HD;
-  half_t* Vc = p.v_cache + (size_t)kvh * p.kv_cap * HD;
-  const int lk = tid % LPK, kq = tid / LPK;  // my slice of the head dim, my key slot
-  half8 zero8;
-#pragma unroll
-  for (int c = 0; c < 8; ++c) zero8[c] = (half_t)0;
-
-  // The new token's q (first wave), k (second) and v (third and fourth), its rotation, and behind
-  // them the first NB key / value rows of this thread, all without branches: loads return in order,
-  // so the rotation waits for its own values only and is done when the rows arrive.  With the rows
-  // in front and under masks, they waited for one another and q was rotated 2.3 us into the kernel
-  // (13B stack with reuse 3551 -> 3473 us, 7B with thresholds 2150 -> 2122, Mixtral blocks 232 ->
-  // 225).  Rows past the split are read as its last one (or as the row the new token goes to, if it
-  // has none: kv_len < kv_cap) and not used.
-  const half_t* mine_new = tid < 64 ? q : (tid < 128 ? kn : vn);
-  const int new_i = tid < 128 ? (tid & 63) % (HD / 2) : (tid - 128) % HD;
-  const half_t new_a = mine_new[new_i], new_b = mine_new[tid < 128 ? new_i + HD / 2 : new_i];
-  const float new_cs = cs_tab[(tid & 63) % (HD / 2)], new_sn = sn_tab[(tid & 63) % (HD / 2)];
-  half8 kv[NB], vv[NB];
-#pragma unroll
-  for (int u = 0; u < NB; ++u) {
-    const size_t row = t0 + min(kq + u * KPB, max(cnt - 1, 0));
-    kv[u] = af_load_once(reinterpret_cast<const half8*>(Kc + row * HD + lk * 8));
-    vv[u] = af_load_once(reinterpret_cast<const half8*>(Vc + row * HD + lk * 8));
-  }
-  __builtin_amdgcn_sched_barrier(0);
-
-  if (tid < HD / 2) {
-    const float a = (float)new_a, b = (float)new_b;
-    const float cs = new_cs, sn = new_sn;
-    const float sc = 1.0f / sqrtf((float)HD);
-    s_q[tid] = (a * cs - b * sn) * sc;
-    s_q[tid + HD / 2] = (b * cs + a * sn) * sc;
-  } else if (owns_new && tid >= 64 && tid < 64 + HD / 2) {
-    const int i = tid - 64;
-    const float a = (float)new_a, b = (float)new_b;
-    const float cs = new_cs, sn = new_sn;
-    const half_t ha = (half_t)(a * cs - b * sn), hb = (half_t)(b * cs + a * sn);  // cache is fp16
-    s_knew[i] = (float)ha;
-    s_knew[i + HD / 2] = (float)hb;
-    if (h % rep == 0) {
-      Kc[(size_t)p.kv_len * HD + i] = ha;
-      Kc[(size_t)p.kv_len * HD + i + HD / 2] = hb;
-    }
-  } else if (owns_new && tid >= 128 && tid < 128 + HD) {
-    const int i = tid - 128;
-    const half_t v = new_a;
-    s_vnew[i] = (float)v;
-    if (h % rep == 0) Vc[(size_t)p.kv_len * HD + i] = v;
-  }
-  __syncthreads();
-
-  // ---- scores ------------------------------------------------------------------------
-  float qr[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) qr[c] = s_q[lk * 8 + c];
-  auto score = [&](const half8& k8, int i) {
-    float d = 0.f;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) d += (float)k8[c] * qr[c];
-#pragma unroll
-    for (int off = 1; off < LPK; off <<= 1) d += __shfl_xor(d, off, AF_WAVE);
-    if (lk == 0 && i < cnt) s_sc[i] = d;
-  };
-#pragma unroll
-  for (int u = 0; u < NB; ++u) score(kv[u], kq + u * KPB);
-  for (int i0 = kq + NB * KPB; i0 < cnt; i0 += NB * KPB) {  // long caches: further batches
-    half8 k2[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int i = i0 + u * KPB;
-      k2[u] = i < cnt ? af_load_once(reinterpret_cast<const half8*>(Kc + (size_t)(t0 + i) * HD + lk * 8)) : zero8;
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) score(k2[u], i0 + u * KPB);
-  }
-  if (owns_new && wave == 0) {
-    float d = 0.f;
-    for (int c = lane; c < HD; c += AF_WAVE) d += s_q[c] * s_knew[c];
-    d = af_wave_sum(d);
-    if (lane == 0) s_sc[cnt] = d;
-  }
-  __syncthreads();
-
-  // ---- local softmax -----------------------------------------------------------------
-  float m = -INFINITY;
-  for (int i = tid; i < total; i += ATT_THREADS) m = fmaxf(m, s_sc[i]);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, AF_WAVE));
-  if (lane == 0) s_red[wave] = m;
-  __syncthreads();
-  m = s_red[0];
-#pragma unroll
-  for (int w = 1; w < ATT_WAVES; ++w) m = fmaxf(m, s_red[w]);
-  __syncthreads();
-  float l = 0.f;
-  for (int i = tid; i < total; i += ATT_THREADS) {
-    float e = expf(s_sc[i] - m);
-    s_sc[i] = e;
-    l += e;
-  }
-  l = af_wave_sum(l);
-  if (lane == 0) s_red[wave] = l;
-  __syncthreads();
-  l = 0.f;
-#pragma unroll
-  for (int w = 0; w < ATT_WAVES; ++w) l += s_red[w];
-
-  // ---- weighted values ---------------------------------------------------------------
-  float acc[8];
-#pragma unroll
-  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
-#pragma unroll
-  for (int u = 0; u < NB; ++u) {
-    const int i = kq + u * KPB;
-    if (i < cnt) {
-      const float pw = s_sc[i];
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] += pw * (float)vv[u][c];
-    }
-  }
-  for (int i0 = kq + NB * KPB; i0 < cnt; i0 += NB * KPB) {
-    half8 v2[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int i = i0 + u * KPB;
-      v2[u] = i < cnt ? af_load_once(reinterpret_cast<const half8*>(Vc + (size_t)(t0 + i) * HD + lk * 8)) : zero8;
-    }
-#pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int i = i0 + u * KPB;
-      const float pw = i < cnt ? s_sc[i] : 0.f;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] += pw * (float)v2[u][c];
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 8; ++c) s_pv[kq][lk * 8 + c] = acc[c];
-  __syncthreads();
-  float* mine = p.part + ((size_t)h * KS + s) * (HD + 2);
-  if (tid < HD) {
-    float v = 0.f;
-#pragma unroll 4
-    for (int g = 0; g < KPB; ++g) v += s_pv[g][tid];
-    if (owns_new) v += s_sc[cnt] * s_vnew[tid];
-    if (KS == 1) {
-      p.out[(size_t)h * HD + tid] = (half_t)(v / l);
-    } else {
-      af_store_agent(mine + 2 + tid, v);
-    }
-  }
-  if (KS == 1) {
-    af_prof_end(p.prof);
-    return;
-  }
-  if (tid == 0) {
-    af_store_agent(mine, m);
-    af_store_agent(mine + 1, l);
-  }
-  af_stores_done();
-  __syncthreads();
-  if (tid == 0) {
-    int old = af_ticket_take(&p.tickets[h]);
-    s_last = (old == KS - 1);
-  }
-  __syncthreads();
-  if (!s_last) {
-    af_prof_end(p.prof);
-    return;
-  }
-  const float* base = p.part + (size_t)h * KS * (HD + 2);
-  if (tid < HD) p.out[(size_t)h * HD + tid] = (half_t)attn_combine<HD>(base, KS, tid);
-  if (tid == 0) af_ticket_reset(&p.tickets[h]);
-  af_prof_end(p.prof);
-}
-
-template <int HD>
-__global__ __launch_bounds__(ATT_THREADS) void attn_decode_kernel(AttnParams p) {
-  attn_decode_body<HD>(p, p.cs, p.sn, blockIdx.x, blockIdx.y, gridDim.y);
-}
-
-// The same for B tokens in one launch (af_decode_layer_batch): grid (heads, key splits, tokens);
-// every token has its own caches, length, position and number of key splits.  The rotary table
-// of a token is formed here, in fp64 like the host does for the single-token launch
-// (angle = pos * theta^(-2i/HD) with the host's theta^(-2i/HD)).
-struct AttnBatchParams {
-  AttnParams base;          // token 0's qkv / out, the shared sizes; cs / sn unused
-  half_t* k_caches[AF_MAX_BATCH];
-  half_t* v_caches[AF_MAX_BATCH];
-  int kv_lens[AF_MAX_BATCH];
-  int poss[AF_MAX_BATCH];
-  int splits[AF_MAX_BATCH];  // key splits of each token
-  double inv_freq[64];
-  long long qkv_stride, out_stride, part_stride;  // elements between the tokens
-};
-
-template <int HD>
-__global__ __launch_bounds__(ATT_THREADS) void attn_decode_batch_kernel(AttnBatchParams bp) {
-  __shared__ float s_cs[HD / 2], s_sn[HD / 2];
-  const int b = blockIdx.z;
-  const int KS = bp.splits[b];
-  if ((int)blockIdx.y >= KS) return;  // uniform for the workgroup: this token has fewer splits
-  AttnParams p = bp.base;
-  p.qkv += (size_t)b * bp.qkv_stride;
-  p.out += (size_t)b * bp.out_stride;
-  p.part += (size_t)b * bp.part_stride;
-  p.tickets += b * p.n_heads;
-  p.k_cache = bp.k_caches[b];
-  p.v_cache = bp.v_caches[b];
-  p.kv_len = bp.kv_lens[b];
-  if (threadIdx.x < HD / 2) {
-    const double ang = (double)bp.poss[b] * bp.inv_freq[threadIdx.x];
-    s_cs[threadIdx.x] = (float)cos(ang);
-    s_sn[threadIdx.x] = (float)sin(ang);
-  }
-  __syncthreads();
-  attn_decode_body<HD>(p, s_cs, s_sn, blockIdx.x, blockIdx.y, KS);
-}
-
-int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv, void* kc, void* vc,
-                        int kv_len, int kv_cap, int pos, half_t* out) {
-  // One split per 64 keys up to two workgroups per compute unit over all heads; beyond that
-  // more splits only lengthen the combine (7B shape, 2048 keys: 32 splits 86.4 us per layer,
-  // 16 splits 80.5 us).
-  int KS = (kv_len + 63) / 64;
-  const int ks_cap = 2 * ctx->n_cu / cfg->n_heads > 1 ? 2 * ctx->n_cu / cfg->n_heads : 1;
-  if (KS > ks_cap) KS = ks_cap;
-  if (KS < (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS) KS = (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS;  // very long caches
-  if (ctx->tune_attn_splits > 0) KS = ctx->tune_attn_splits;
-  if (KS < 1) KS = 1;
-  if (KS > 64) KS = 64;
-  while ((size_t)cfg->n_heads * KS * (cfg->head_dim + 2) > ctx->lay.attn_floats && KS > 1) --KS;
-  if ((kv_len + KS - 1) / KS > ATT_MAX_KEYS) return AF_EINVAL;
-  AttnParams p;
-  p.qkv = qkv;
-  p.k_cache = (half_t*)kc;
-  p.v_cache = (half_t*)vc;
-  p.out = out;
-  p.part = (float*)(ctx->ws + ctx->lay.attn_part);
-  p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
-  p.n_heads = cfg->n_heads;
-  p.n_kv = cfg->n_kv_heads;
-  p.kv_len = kv_len;
-  p.kv_cap = kv_cap;
-  p.head_dim = cfg->head_dim;
-  p.prof = af_prof_take(ctx);
-  for (int i = 0; i < cfg->head_dim / 2; ++i) {
-    const double ang = (double)pos * pow((double)cfg->rope_theta, -2.0 * (double)i / (double)cfg->head_dim);
-    p.cs[i] = (float)cos(ang);
-    p.sn[i] = (float)sin(ang);
-  }
-  dim3 grid(cfg->n_heads, KS);
-  if (cfg->head_dim == 128)
-    hipLaunchKernelGGL(attn_decode_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, p);
-  else
-    hipLaunchKernelGGL(attn_decode_kernel<64>, grid, dim3(ATT_THREADS), 0, ctx->stream, p);
-  AF_LAUNCH_CHECK();
-  return AF_OK;
-}
-
-int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const half_t* qkv,
-                              long long qkv_stride, void* const* kcs, void* const* vcs, const int* kv_len,
-                              int kv_cap, const int* pos, half_t* out, long long out_stride) {
-  AttnBatchParams bp{};
-  AttnParams& p = bp.base;
-  int ks_max = 1;
-  const size_t per_split = (size_t)cfg->n_heads * (cfg->head_dim + 2);
-  for (int b = 0; b < B; ++b) {
-    int KS = (kv_len[b] + 63) / 64;
-    const int ks_cap = 2 * ctx->n_cu / cfg->n_heads > 1 ? 2 * ctx->n_cu / cfg->n_heads : 1;
-    if (KS > ks_cap) KS = ks_cap;
-    if (KS < (kv_len[b] + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS) KS = (kv_len[b] + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS;
-    if (KS < 1) KS = 1;
-    if (KS > 64) KS = 64;
-    while (KS > 1 && (size_t)B * KS * per_split > ctx->lay.attn_floats) --KS;
-    if ((kv_len[b] + KS - 1) / KS > ATT_MAX_KEYS) return AF_EINVAL;
-    bp.splits[b] = KS;
-    if (KS > ks_max) ks_max = KS;
-    bp.k_caches[b] = (half_t*)kcs[b];
-    bp.v_caches[b] = (half_t*)vcs[b];
-    bp.kv_lens[b] = kv_len[b];
-    bp.poss[b] = pos[b];
-  }
-  if ((size_t)B * ks_max * per_split > ctx->lay.attn_floats) return AF_EWORKSPACE;
-  p.qkv = qkv;
-  p.out = out;
-  p.part = (float*)(ctx->ws + ctx->lay.attn_part);
-  p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
-  p.n_heads = cfg->n_heads;
-  p.n_kv = cfg->n_kv_heads;
-  p.kv_cap = kv_cap;
-  p.head_dim = cfg->head_dim;
-  p.prof = nullptr;
-  for (int i = 0; i < cfg->head_dim / 2; ++i)
-    bp.inv_freq[i] = pow((double)cfg->rope_theta, -2.0 * (double)i / (double)cfg->head_dim);
-  bp.qkv_stride = qkv_stride;
-  bp.out_stride = out_stride;
-  bp.part_stride = (long long)ks_max * (long long)per_split;
-  dim3 grid(cfg->n_heads, ks_max, B);
-  if (cfg->head_dim == 128)
-    hipLaunchKernelGGL(attn_decode_batch_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, bp);
-  else
-    hipLaunchKernelGGL(attn_decode_batch_kernel<64>, grid, dim3(ATT_THREADS), 0, ctx->stream, bp);
-  AF_LAUNCH_CHECK();
-  return AF_OK;
 }
 
 // ---- whole-layer kernel -------------------------------------------------------------------
@@ -468,7 +116,7 @@ struct AttnLds {
 #define LAYER_ATT_LDS_BYTES (4 * (AttnLds<128>::END > AttnLds<64>::END ? AttnLds<128>::END : AttnLds<64>::END))
 
 // Attention of (head h, key split s) by one 1024-thread workgroup; same arithmetic as
-// attn_decode_kernel.  The cached keys and values of the split are requested first, then the
+// the attention launches (attention.hip).  The cached keys and values of the split are requested first, then the
 // workgroup waits for the qkv projection (counter `ready` reaching `ready_total`).
 template <int HD>
 __device__ __forceinline__ bool attn_phase(const AttnParams& p, int h, int s, int KS, float* lds,
