@@ -286,7 +286,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
-    int old = af_ticket_take(&p.tickets[bx]);
+    int old = af_ticket_take(&p.tickets[af_ticket_of(p.ticket0 + bx)]);
     s_last = (old == KS - 1);
   }
   __syncthreads();
@@ -324,7 +324,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
     if (d < HD)
       *reinterpret_cast<half2v*>(p.out + (size_t)(h0 + hh) * HD + d) = half2v{(half_t)(v0 / L), (half_t)(v1 / L)};
   }
-  if (tid == 0) af_ticket_reset(&p.tickets[bx]);
+  if (tid == 0) af_ticket_reset(&p.tickets[af_ticket_of(p.ticket0 + bx)]);
   af_prof_end(p.prof);
 }
 
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attn_decode_batch_kernel(AttnBatc
   p.qkv += (size_t)b * bp.qkv_stride;
   p.out += (size_t)b * bp.out_stride;
   p.part += (size_t)b * bp.part_stride;
-  p.tickets += b * p.n_heads;
+  p.ticket0 = b * p.n_heads;
   p.k_cache = bp.k_caches[b];
   p.v_cache = bp.v_caches[b];
   p.kv_len = bp.kv_lens[b];
@@ -408,6 +408,7 @@ int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv,
   p.out = out;
   p.part = (float*)(ctx->ws + ctx->lay.attn_part);
   p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
+  p.ticket0 = 0;
   p.n_heads = cfg->n_heads;
   p.n_kv = cfg->n_kv_heads;
   p.kv_len = kv_len;
@@ -450,6 +451,7 @@ int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const
   p.out = out;
   p.part = (float*)(ctx->ws + ctx->lay.attn_part);
   p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
+  p.ticket0 = 0;
   p.n_heads = cfg->n_heads;
   p.n_kv = cfg->n_kv_heads;
   p.kv_cap = kv_cap;

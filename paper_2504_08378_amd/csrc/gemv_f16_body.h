@@ -449,7 +449,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
-    int old = af_ticket_take(&p.tickets[vb.bx]);
+    int old = af_ticket_take(&p.tickets[af_ticket_of(vb.bx)]);
     s_last = (old == S - 1);
   }
   __syncthreads();
@@ -467,7 +467,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S), res);
     }
   }
-  if (tid == 0) af_ticket_reset(&p.tickets[vb.bx]);  // ready for the next launch
+  if (tid == 0) af_ticket_reset(&p.tickets[af_ticket_of(vb.bx)]);  // ready for the next launch
   if constexpr (PHASE) gemv_phase_signal(p);
   af_prof_end(p.prof);
 }

@@ -317,7 +317,7 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
-    int old = af_ticket_take(&p.tickets[blockIdx.x]);
+    int old = af_ticket_take(&p.tickets[af_ticket_of(blockIdx.x)]);
     s_last = (old == S - 1);
   }
   __syncthreads();
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
     const float res = q4_residual_of(p, out0 + c);
     q4_store_out(p, out0 + c, af_sum_partials(p.partials + tile0 + c, p.out_pad, S), res);
   }
-  if (tid == 0) af_ticket_reset(&p.tickets[blockIdx.x]);
+  if (tid == 0) af_ticket_reset(&p.tickets[af_ticket_of(blockIdx.x)]);
   af_prof_end(p.prof);
 }
 

@@ -305,7 +305,7 @@ __device__ __forceinline__ bool attn_phase(const AttnParams& p, int h, int s, in
     af_stores_done();
     __syncthreads();
     if (tid == 0) {
-      int old = af_ticket_take(&p.tickets[h]);
+      int old = af_ticket_take(&p.tickets[af_ticket_of(h)]);
       s_last = (old == KS - 1);
     }
     __syncthreads();
@@ -313,7 +313,7 @@ __device__ __forceinline__ bool attn_phase(const AttnParams& p, int h, int s, in
     if (finisher) {
       const float* base = p.part + (size_t)h * KS * (HD + 2);
       if (tid < HD) s_out[tid] = __builtin_bit_cast(unsigned short, (half_t)attn_combine<HD>(base, KS, tid));
-      if (tid == 0) af_ticket_reset(&p.tickets[h]);
+      if (tid == 0) af_ticket_reset(&p.tickets[af_ticket_of(h)]);
     }
   }
   if (finisher) {  // one finished head: stored through as 8-byte pieces, acknowledged, then counted
@@ -478,6 +478,7 @@ static int launch_layer_kernel(af_ctx* ctx, const af_layer_cfg* cfg, const af_ge
   a.out = attn;
   a.part = (float*)(ctx->ws + ctx->lay.attn_part);
   a.tickets = counters + AF_TICKET_ATTN;
+  a.ticket0 = 0;
   a.n_heads = cfg->n_heads;
   a.n_kv = cfg->n_kv_heads;
   a.kv_len = kv_len;

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams 
   af_stores_done();
   __syncthreads();
   if (tid == 0) {
-    int old = af_ticket_take(&p.tickets[blockIdx.x]);
+    int old = af_ticket_take(&p.tickets[af_ticket_of(blockIdx.x)]);
     s_last = (old == S - 1);
   }
   __syncthreads();
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(UG_THREADS) void gemv_union_kernel(UnionGemvParams 
     store(b, tile0 + c,
           af_sum_partials(p.partials + (size_t)b * p.out_pad + tile0 + c, (size_t)p.B * p.out_pad, S));
   }
-  if (tid == 0) af_ticket_reset(&p.tickets[blockIdx.x]);
+  if (tid == 0) af_ticket_reset(&p.tickets[af_ticket_of(blockIdx.x)]);
 }
 
 int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
