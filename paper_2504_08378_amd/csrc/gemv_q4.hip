@@ -14,6 +14,8 @@
 // of the fp16 constant 1024 gives the pair (1024 + n_a, 1024 + n_b) in one and-or; a packed
 // fp16 subtract of 1032 leaves the exact integers q = n - 8.  Nibbles sitting four bits higher
 // come out as 16*q and are multiplied with x/16 instead.  Accumulation is fp32.
+#include <type_traits>
+
 #include "af_internal.h"
 #include "row_prologue.h"
 
@@ -163,20 +165,6 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
     sbase += (size_t)e_sel * (size_t)p.s_stride;
   }
 
-  auto consume = [&](unsigned e, unsigned w) {
-    const int g = (int)(e >> 21);  // (index >> 5)
-    if (g != cur_g) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        yacc[c] += (float)sc[c] * acc[c];
-        acc[c] = 0.f;
-      }
-      cur_g = g;
-      sc = *reinterpret_cast<const half8*>(sbase + (size_t)g * p.ld + col_ld);
-    }
-    const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e & 0xFFFFu));
-    q4_fma8(acc, w, xv, xv * 0.0625f);
-  };
   // channel-local scales: the row's scale of this lane's column group multiplies x
   const size_t srow = (size_t)(p.ld / 32);
   const half_t* scol = sbase + col_ld / 32;
@@ -190,14 +178,21 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
     const int per = (cnt + NSLOT - 1) / NSLOT;
     int i = min(slot * per, cnt);
     const int iend = min(i + per, cnt);
-    for (; i + U <= iend; i += U) {
+    // A batch of U rows; TAIL: only those in front of the slice's end.  The loads of a batch are in flight
+    // together, and in the group-32 layout those of the scales of the groups that it opens: behind the
+    // end it reads its last row again, which opens none, and drops it.  (A tail that fetched the
+    // scales of a group when it came to it paid one trip to memory per group, and a short slice is nothing but
+    // tail: 7B step at 70 % 1822 -> 1799 us.  Channel-local scales come one to a row; there masked loads
+    // measured better, 7B layers at 70 % 57.1 against 59.4 us.)
+    auto batch = [&](auto tail) __attribute__((always_inline)) {
+      constexpr bool TAIL = decltype(tail)::value;
       unsigned w[U], e[U];
       half_t sr[U];
       half8 sg[U];  // group-32 layout: the scales of a row that opens a new group, fetched with the batch
       int gprev = cur_g;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        e[u] = s_list[i + u];
+        e[u] = s_list[TAIL ? min(i + u, iend - 1) : i + u];
         w[u] = af_load_once(reinterpret_cast<const unsigned*>(wcol + (size_t)(e[u] >> 16) * row_bytes));
         if (CL) {
           sr[u] = scol[(size_t)(e[u] >> 16) * srow];
@@ -209,6 +204,7 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
+        if (TAIL && i + u >= iend) break;
         if (CL) {
           consume_cl(e[u], w[u], sr[u]);
         } else {
@@ -226,27 +222,24 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
           q4_fma8(acc, w[u], xv, xv * 0.0625f);
         }
       }
-    }
-    // Ragged end: one more batch of the same depth with the missing rows masked off, so its
-    // loads are in flight together instead of one memory round trip per row.
+    };
+    for (; i + U <= iend; i += U) batch(std::false_type{});
     if (i < iend) {
-      unsigned w[U], e[U];
-      half_t sr[U];
+      if constexpr (!CL) {
+        batch(std::true_type{});
+      } else {
+        unsigned w[U], e[U];
+        half_t sr[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const bool ok = i + u < iend;
-        e[u] = ok ? s_list[i + u] : 0u;
-        w[u] = ok ? af_load_once(reinterpret_cast<const unsigned*>(wcol + (size_t)(e[u] >> 16) * row_bytes)) : 0u;
-        if (CL) sr[u] = ok ? scol[(size_t)(e[u] >> 16) * srow] : (half_t)0;
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (i + u < iend) {
-          if (CL)
-            consume_cl(e[u], w[u], sr[u]);
-          else
-            consume(e[u], w[u]);
+        for (int u = 0; u < U; ++u) {
+          const bool ok = i + u < iend;
+          e[u] = ok ? s_list[i + u] : 0u;
+          w[u] = ok ? af_load_once(reinterpret_cast<const unsigned*>(wcol + (size_t)(e[u] >> 16) * row_bytes)) : 0u;
+          sr[u] = ok ? scol[(size_t)(e[u] >> 16) * srow] : (half_t)0;
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (i + u < iend) consume_cl(e[u], w[u], sr[u]);
       }
     }
   };
