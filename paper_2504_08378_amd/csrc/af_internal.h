@@ -162,6 +162,13 @@ struct af_gemv_args {
   long long w_stride_scales;  // q4: scale elements per matrix
   int n_slots;
   const float* y_scale;  // device scalar multiplying the product before the residual (null: 1)
+  // A second input in the same launch (fp16 weights, fp16 results, one slot): its matrix is
+  // w_sel[1], its scale y_scale[1], and its product joins the first one's rounded result.
+  bool pair;
+  const half_t* src2;
+  half_t* x_out2;
+  int32_t* idx_out2;
+  int32_t* count_out2;
   // Router run inside this launch (see the kernels): valid for a norm producer, at most 8
   // experts and in <= 8192; the slots then follow the experts found in the kernel (w_sel is
   // not read) and the results are published to the three device arrays.

@@ -132,6 +132,32 @@ static void launch_lx(int nw, int early, dim3 grid, size_t lds, hipStream_t st, 
   }
 }
 
+// The launches with two inputs: the SiLU producer's modes, and the generic kernel.
+template <int LX, int MODE>
+static void launch_pair_one(dim3 grid, size_t lds, hipStream_t st, const GemvPairParams& d) {
+  static bool attr_done = false;
+  if (!attr_done) {
+    attr_done = true;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_f16_pair_kernel<LX, 8, MODE>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, AF_GEMV_LDS_BUDGET);
+  }
+  hipLaunchKernelGGL((gemv_f16_pair_kernel<LX, 8, MODE>), grid, dim3(16 * AF_WAVE), lds, st, d);
+}
+template <int LX>
+static void launch_pair(int early, dim3 grid, size_t lds, hipStream_t st, const GemvPairParams& d) {
+  const int mode = gemv_mode_of(d.p);
+  switch (mode | ((mode >> 2) == 1 ? early << 4 : 0)) {
+#define AF_MODE_CASE(kind) \
+  case GEMV_MODE(AF_PRO_SILUMUL, kind): \
+    launch_pair_one<LX, GEMV_MODE(AF_PRO_SILUMUL, kind)>(grid, lds, st, d); \
+    break;
+    AF_MODE_CASE(1) AF_MODE_CASE(1 | 1 << 2) AF_MODE_CASE(1 | 2 << 2) AF_MODE_CASE(1 | GEMV_EARLY_NONE << 2) AF_MODE_CASE(3)
+#undef AF_MODE_CASE
+    default:
+      launch_pair_one<LX, -1>(grid, lds, st, d);
+  }
+}
+
 int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvPlan* plan) {
   const af_row_src& r = a.rows;
   // the largest index set this launch can meet (the count of a threshold set is only known
@@ -154,13 +180,15 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   const int out_pad = tiles * tw;
   if (tiles > AF_TICKET_ATTN) return AF_ESHAPE;
   S = (int)((long long)S * ((a.out + tw - 1) / tw) / tiles);  // padding adds tiles: keep the grid size
+  if (a.pair) S /= 2;  // the other half of the grid is the second input's
   if (S < 1) S = 1;
   const bool range_sel = r.sel == AF_SEL_THRESHOLD && !r.idx_out && !r.count_out;
   const bool use_lds_x = r.pro != AF_PRO_NONE || r.sel != AF_ROWS_GIVEN;
   size_t xs_bytes;
   int list_cap;
   // the split partial sums have to fit the workspace, the staged rows of a split the LDS
-  while (S > 1 && (size_t)S * out_pad > ctx->lay.partial_floats) --S;
+  const size_t part_floats = ctx->lay.partial_floats / (a.pair ? 2 : 1);
+  while (S > 1 && (size_t)S * out_pad > part_floats) --S;
   if (a.router_Wr && (r.pro != AF_PRO_RMSNORM || a.router_E > 8 || r.n > 8192 || nw != 16 || !use_lds_x))
     return AF_EINVAL;  // the in-kernel router's preconditions (the caller falls back to the router kernel)
   // Early rows split by channel, and a split's channels can be more rows than an even share of the
@@ -181,7 +209,8 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   if (early == GEMV_EARLY_NONE && !af_plan_gemv_lds(r, max_rows, use_lds_x, range_sel, GEMV_LIST, &S, &xs_bytes,
                                                     &list_cap, a.router_Wr != nullptr))
     return AF_EWORKSPACE;
-  if (S > 1 && (size_t)S * out_pad > ctx->lay.partial_floats) return AF_EWORKSPACE;
+  if ((S > 1 || a.pair) && (size_t)S * out_pad > part_floats) return AF_EWORKSPACE;
+  if (a.pair && (nw != 16 || n_slots != 1 || !a.y_scale || a.y_kind != AF_F16)) return AF_EINVAL;
   GemvParams& p = plan->p;
   p = GemvParams{};
   p.W = (const half_t*)a.W;
@@ -222,6 +251,18 @@ int af_launch_gemv_f16(af_ctx* ctx, const af_gemv_args& a) {
   const int rc = af_plan_gemv_f16(ctx, a, false, &plan);
   if (rc) return rc;
   plan.p.prof = af_prof_take(ctx);
+  if (a.pair) {
+    const GemvPairParams d = {plan.p, a.src2, a.x_out2, a.idx_out2, a.count_out2};
+    const dim3 grid(plan.tiles, 2 * plan.S);
+    if (plan.lx == 64)
+      launch_pair<64>(plan.early, grid, plan.lds, ctx->stream, d);
+    else if (plan.lx == 32)
+      launch_pair<32>(plan.early, grid, plan.lds, ctx->stream, d);
+    else
+      launch_pair<16>(plan.early, grid, plan.lds, ctx->stream, d);
+    AF_LAUNCH_CHECK();
+    return AF_OK;
+  }
   dim3 grid(plan.tiles, plan.S);
   if (plan.lx == 64)
     launch_lx<64>(plan.nw, plan.early, grid, plan.lds, ctx->stream, plan.p);

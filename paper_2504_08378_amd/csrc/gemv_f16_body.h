@@ -149,12 +149,16 @@ struct GemvEarlyLds : GemvLds<NW, TWMAX> {
 };
 
 // PHASE: the operator is a phase of the whole-layer kernel (p.done is set).
+// PAIR: the launch multiplies two inputs by two device-picked matrices and adds both products to the
+// residual stream, the first one rounded to fp16 before the second joins it (the down projections
+// of the two experts of a mixture-of-experts block).  Workgroups are (tile, split of input `pair`);
+// the tile's last workgroup adds up both.
 // EARLY (top-k launches of 1024-thread workgroups): the rows whose selection is obvious are
 // requested before the front end runs (RowPrologue, "early rows").  EARLY is the number of
 // vectors of the operator's source that one thread holds (1, 4 or 8; 0: no early rows).
-template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, typename LDS_T>
+template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, bool PAIR = false, typename LDS_T>
 __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos vb,
-                                              unsigned short* xs, LDS_T& lds) {
+                                              unsigned short* xs, LDS_T& lds, const int pair = 0) {
   constexpr int GEMV_THREADS = NW * AF_WAVE;
   constexpr int GEMV_WAVES = NW;
   constexpr int LY = AF_WAVE / LX;
@@ -417,7 +421,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   const int tile0 = vb.bx * TW;                      // in the padded column space
   const int out0 = slot * p.cols_per_slot + tile_in * TW;  // first output column of the tile
   const int valid = min(TW, p.cols_per_slot - tile_in * TW);
-  if (S == 1) {
+  if (S == 1 && !PAIR) {
     if constexpr (PHASE) {
       store_tile_through<GEMV_THREADS>(p, out0, valid, xs, [&](int c) {
         float v = 0.f;
@@ -450,14 +454,24 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   __syncthreads();
   if (tid == 0) {
     int old = af_ticket_take(&p.tickets[af_ticket_of(vb.bx)]);
-    s_last = (old == S - 1);
+    s_last = (old == (PAIR ? 2 * S : S) - 1);
   }
   __syncthreads();
   if (!s_last) {
     af_prof_end(p.prof);
     return;
   }
-  if constexpr (PHASE) {
+  if constexpr (PAIR) {
+    const size_t n = (size_t)S * p.out_pad;
+    const float* first = p.partials - pair * n + tile0;
+    const float* scale = p.y_scale - pair;
+    for (int c = tid; c < valid; c += GEMV_THREADS) {
+      const float res = residual_of(p, out0 + c);
+      const float a = af_sum_partials(first + c, p.out_pad, S), b = af_sum_partials(first + n + c, p.out_pad, S);
+      const half_t h = (half_t)(a * scale[0] + res);
+      reinterpret_cast<half_t*>(p.y)[out0 + c] = (half_t)(b * scale[1] + (float)h);
+    }
+  } else if constexpr (PHASE) {
     store_tile_through<GEMV_THREADS>(p, out0, valid, xs, [&](int c) {
       return af_sum_partials(p.partials + tile0 + c, p.out_pad, S);
     });
@@ -550,4 +564,34 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_f16_kernel(GemvParams p) {
   } else {
     gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(p, vb, xs, lds);
   }
+}
+
+// The second input of a launch with two (see PAIR); everything else is in `p`, whose partials and
+// matrix choices lie in front of the second input's.
+struct GemvPairParams {
+  GemvParams p;
+  const half_t* src;
+  half_t* x_out;
+  int32_t* idx_out;
+  int32_t* count_out;
+};
+template <int LX, int U, int MODE>
+__global__ __launch_bounds__(16 * AF_WAVE) void gemv_f16_pair_kernel(GemvPairParams d) {
+  constexpr int NW = 16;
+  extern __shared__ __align__(16) unsigned short xs[];
+  constexpr int EARLY = gemv_early(MODE, NW, false);
+  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
+  const int S = (int)gridDim.y >> 1, pair = (int)blockIdx.y >= S;
+  const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y - pair * S, (int)gridDim.x, S};
+  GemvParams q = gemv_fix_mode<MODE>(d.p);
+  if (pair) {
+    q.rows.src = d.src;
+    q.rows.x_out = d.x_out;
+    q.rows.idx_out = d.idx_out;
+    q.rows.count_out = d.count_out;
+    q.w_sel += 1;
+    q.y_scale += 1;
+    q.partials += (size_t)S * q.out_pad;
+  }
+  gemv_f16_body<LX, U, NW, false, false, EARLY, true>(q, vb, xs, lds, pair);
 }

@@ -909,6 +909,20 @@ extern "C" int af_decode_moe_layer(af_ctx* ctx, const af_moe_cfg* mcfg, const af
     af_gemv_args a{};
     a.W = w->Wdown; a.scales = (const half_t*)w->Sdown; a.in = f; a.out = d; a.ld = d; a.y = h_out;
     a.residual = s == 0 ? hmid : h_out;
+    // Two experts in one launch: one front end, reduction and launch instead of two around the same
+    // rows (two Mixtral-shape blocks at 50 % 224 -> 208 us).
+    if (!q4 && top == 2 && ctx->tune_nw != 4 && ctx->tune_nw != 8) {
+      a.pair = true;
+      a.src2 = gu + 2 * f;
+      a.x_out2 = x3 + f;
+      a.idx_out2 = write_sets ? sets->idx[4] : nullptr;
+      a.count_out2 = write_sets ? sets->count[4] : nullptr;
+      a.w_sel = route->experts; a.n_slots = 1;
+      bank(a, f, d);
+      a.y_scale = route->weights;
+      if ((rc = gemv(3, 3, a, AF_PRO_SILUMUL, gu, nullptr, x3))) return rc;
+      break;
+    }
     a.w_sel = route->experts + s; a.n_slots = 1;
     bank(a, f, d);
     a.y_scale = route->weights + s;

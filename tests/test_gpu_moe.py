@@ -223,3 +223,60 @@ def test_router_as_its_own_launch_gives_the_same_layer(ctx):
     assert outs[0][0].tolist() == outs[1][0].tolist()
     assert np.allclose(outs[0][1], outs[1][1], rtol=1e-5) and np.allclose(outs[0][2], outs[1][2], rtol=1e-4, atol=1e-5)
     assert O.rel_err(outs[0][3], outs[1][3], 1.0) <= 1e-3
+
+
+@pytest.mark.parametrize("d,ffn,mode,share", [
+    (64, 64, "topk", 0.5),           # one split per expert
+    (136, 1000, "topk", 0.3),        # a remainder in the tile and in the channels
+    (4096, 5504, "topk", 0.5),       # rows requested early
+    (6400, 2048, "topk", 1.0),       # 256-column tiles, every channel
+    (520, 8200, "threshold", 0.4),
+    (520, 8200, "list", 0.4),        # thresholds with the lists written
+    (264, 776, "dense", 1.0),
+    (264, 776, "topk", 0.0),
+])
+def test_both_experts_in_one_launch(ctx, d, ffn, mode, share):
+    """The launch that multiplies both experts' down projections against one call per expert on the
+    inputs the block itself produced: same sets, sums in another order (at most the neighbouring
+    fp16 value twice, once per rounding)."""
+    shape = S.ModelShape("pair", 1, d, 2, 1, 64, ffn, n_experts=4)
+    w = S.device_moe_layer_weights(5, shape, 0)
+    lay = M.DeviceMoeLayer(ctx, shape, w)
+    K, V = (torch.randn((1, 40, 64), device="cuda").half() for _ in range(2))
+    h = to_dev(S.activation(5, S.channel_scales(5, d, "pair"), "h", 0))
+    out = torch.zeros_like(h)
+    widths = (d, 128, d, ffn)
+    k = int(share * ffn)
+    if mode in ("topk", "dense"):
+        sel = M.select_cfg(B.AF_SEL_TOPK if mode == "topk" else B.AF_SEL_DENSE, (d, 128, d, k))
+    else:
+        sel = M.select_cfg(B.AF_SEL_THRESHOLD, t=(-1.0, -1.0, -1.0, 1e-3),
+                           flags=B.AF_SEL_SKIP_SETS if mode == "threshold" else 0)
+    for rep in range(2):        # the second run finds the tickets the first one left
+        lay.run(h, out, K, V, 39, 40, 39, sel)
+    ctx.synchronize()
+    experts, weights = lay.experts.clone(), lay.weights.clone()
+    assert experts[0] != experts[1]
+    hmid = torch.from_numpy(to_host(ctx.layer_tap(3, d))).cuda()
+    gu = torch.from_numpy(to_host(ctx.layer_tap(5, 4 * ffn))).cuda()
+    xd = torch.from_numpy(to_host(ctx.layer_tap(6, 2 * ffn))).cuda()
+    torch.cuda.synchronize()
+    ref = hmid
+    for s in range(2):
+        x = torch.zeros(ffn, dtype=torch.float16, device="cuda")
+        idx = torch.zeros(ffn, dtype=torch.int32, device="cuda")
+        cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        args = dict(sel_mode={"topk": B.AF_SEL_TOPK, "dense": B.AF_SEL_DENSE}.get(mode, B.AF_SEL_THRESHOLD), k=k, t=1e-3)
+        if mode in ("topk", "list"):
+            args.update(idx_out=idx, count_out=cnt)
+        ref = ctx.select_gemv_experts_f16(lay.Wdown, experts[s:s + 1].clone(), 1, gu[s * 2 * ffn:(s + 1) * 2 * ffn].clone(),
+                                          B.AF_PRO_SILUMUL, x_out=x, residual=ref, y_scale=weights[s:s + 1].clone(), **args)
+        ctx.synchronize()
+        assert torch.equal(x, xd[s * ffn:(s + 1) * ffn]), s
+        if mode in ("topk", "list"):
+            n = int(cnt.item())
+            assert n == int(lay.count[3 + s].item()) and torch.equal(idx[:n], lay.idx[3 + s][:n]), s
+    a, b = to_host(out).astype(np.float64), to_host(ref).astype(np.float64)
+    step = np.maximum(np.abs(hmid.cpu().numpy().astype(np.float64)), np.maximum(np.abs(a), np.abs(b))) * 2.0 ** -10
+    assert np.all(np.abs(a - b) <= 2 * step + 1e-7)
