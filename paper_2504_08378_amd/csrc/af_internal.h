@@ -21,13 +21,17 @@ struct af_ws_layout {
   size_t union_x;       // fp16 [max_in][8]: masked, transposed token values of the union GEMV
   size_t union_idx;     // int32 [max_in]: union of the tokens' sets (af_decode_layer_batch)
   size_t union_n;       // int32 [4]: its size per selection point
-  size_t union_ranges;  // int32 [max_in rounded up to 256]: the union builder's per-range lists
-  size_t union_range_cnt; // int32 [AF_MAX_N / 256]
-  size_t union_mask;    // uint32 [max_in]: per-channel token bits of the union builder, zero between calls
+  size_t union_kept;    // [8][af_kept_stride(max_in)]: the tokens' kept channels, four to a byte
   size_t total;
   size_t partial_floats;
   size_t attn_floats;
 };
+// Bytes of one token's kept channels: bit c of byte v is channel 4 v + c; whole 16-byte pieces.
+static inline
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+int af_kept_stride(int n) { return (n + 63) / 64 * 16; }
 enum {
   AF_N_TICKETS = 8256,
   AF_TICKET_ATTN = 4096,  // first ticket used by attention
@@ -195,7 +199,7 @@ struct af_union_args {
   const int32_t* counts;    // device int32[B] or null
   int32_t* union_idx;       // [in]
   int32_t* union_n;         // [1]
-  bool marked;              // the context's channel mask already holds the tokens' bits
+  bool marked;              // the workspace already holds the tokens' kept channels
   void* Y;                  // [B][out]
   int y_kind;
   const half_t* residual;   // [B][out] or null

@@ -7,9 +7,8 @@
 //
 // Per selection point: one launch of B workgroups builds each token's operator input (RMSNorm,
 // copy, or SiLU(gate)*up), selects on it (the front end of row_prologue.h, one workgroup per
-// token) and sets the token's bit in the channel mask for every channel it keeps; one launch
-// turns the mask into the union and the masked token values; one launch streams the union's
-// weight rows for all tokens.  Attention is one launch over (head, key split, token); each token has its own cache,
+// token) and stores a bit per channel; one launch turns the tokens' bits into the union and the masked
+// token values; one launch streams the union's weight rows for all tokens.  Attention is one launch over (head, key split, token); each token has its own cache,
 // length and position.
 #include <math.h>
 
@@ -23,7 +22,7 @@ struct BatchSelectParams {
   long long src_stride;  // elements between the tokens' sources
   long long x_stride;    // ... their produced inputs (x_out)
   long long idx_stride;  // ... their index lists
-  unsigned* mask;        // [n] channel mask of the union builder (bit b: token b keeps the channel)
+  unsigned char* kept;   // [B][af_kept_stride(n)]: the tokens' kept channels, for the union builder
 };
 
 __global__ __launch_bounds__(BS_THREADS) void batch_select_kernel(BatchSelectParams p) {
@@ -40,21 +39,7 @@ __global__ __launch_bounds__(BS_THREADS) void batch_select_kernel(BatchSelectPar
   const bool topk = r.sel == AF_SEL_TOPK;
   RP::produce(r, xs, s_rp, true, 0, 1, topk ? s_scratch : nullptr);
   int nidx;
-  RP::select_split(r, xs, s_scratch, s_rp, nullptr, 1, 0, true, true, &nidx, topk);
-  // the list just written (its stores were waited for at the barrier that ends the selection),
-  // read back past the CU's cache: every kept channel gets this token's bit
-  for (int i0 = threadIdx.x; i0 < nidx; i0 += 8 * BS_THREADS) {
-    int j[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int i = i0 + u * BS_THREADS;
-      j[u] = i < nidx ? __hip_atomic_load(r.idx_out + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if ((unsigned)j[u] < (unsigned)r.n)
-        __hip_atomic_fetch_or(p.mask + j[u], 1u << b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  RP::select_split(r, xs, s_scratch, s_rp, nullptr, 1, 0, true, true, &nidx, topk, p.kept + (size_t)b * af_kept_stride(r.n));
 }
 
 static int launch_batch_select(af_ctx* ctx, int B, int producer, const half_t* src, long long src_stride,
@@ -82,7 +67,7 @@ static int launch_batch_select(af_ctx* ctx, int B, int producer, const half_t* s
   p.src_stride = src_stride;
   p.x_stride = n;
   p.idx_stride = n;
-  p.mask = (unsigned*)(ctx->ws + ctx->lay.union_mask);
+  p.kept = (unsigned char*)(ctx->ws + ctx->lay.union_kept);
   const size_t lds = af_align((size_t)n * 2, 16);
   hipLaunchKernelGGL(batch_select_kernel, dim3(B), dim3(BS_THREADS), lds, ctx->stream, p);
   AF_LAUNCH_CHECK();

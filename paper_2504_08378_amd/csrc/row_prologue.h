@@ -860,10 +860,13 @@ struct RowPrologue {
   // `list` may be null (only idx_out / count_out are wanted).
   // Every thread owns a contiguous run of RP_EV-element vectors, read from LDS one vector at a
   // time in each pass; the thread order is therefore the index order.
+  // `kept_bits`, when given (S == 1 only): bit c of byte v tells whether channel 4 v + c is kept.
   static __device__ __forceinline__ int select_split(const af_row_src& r, const unsigned short* xs,
                                                      unsigned* hist, Smem& sm, unsigned* list,
                                                      int S, int s, bool store_idx, bool store_count,
-                                                     int* nidx_total, bool digit1_counted = false) {
+                                                     int* nidx_total, bool digit1_counted = false,
+                                                     unsigned char* kept_bits = nullptr) {
+    static_assert(RP_EV == 4, "a byte of kept_bits is one vector");
     const int tid = threadIdx.x, lane = tid & 63;
     const int nvec = r.n / RP_EV;
     const int cv = (nvec + THREADS - 1) / THREADS;  // vectors per thread
@@ -930,10 +933,11 @@ struct RowPrologue {
     unsigned eq_seen = pre >> 16;
     // only threads whose run overlaps the split's positions need the second look
     const unsigned my_kept = gt + (min(eq_seen + eq, quota) - min(eq_seen, quota));
-    if ((int)(pos + my_kept) > r0 && (int)pos < r1) {
+    if (((int)(pos + my_kept) > r0 && (int)pos < r1) || kept_bits != nullptr) {
       const bool to_mem = store_idx && r.idx_out != nullptr;
       for (int v = v0; v < v1; ++v) {
         const rp_u16 b = xv[v];
+        unsigned bits_v = 0;
 #pragma unroll
         for (int c = 0; c < RP_EV; ++c) {
           const unsigned bits = b[c];
@@ -947,7 +951,9 @@ struct RowPrologue {
             if (to_mem) r.idx_out[pos] = j;
           }
           pos += keep;
+          bits_v |= (unsigned)keep << c;
         }
+        if (kept_bits != nullptr) kept_bits[v] = (unsigned char)bits_v;
       }
     }
     if (store_count && r.count_out != nullptr && tid == 0) *r.count_out = nidx;
