@@ -104,20 +104,19 @@ static void launch_lx(int nw, int early, dim3 grid, size_t lds, hipStream_t st, 
       launch_one<LX, 16, true, -1>(grid, lds, st, p);
   } else if (nw == 16) {
     const int mode = gemv_mode_of(p);
-    switch (mode | ((mode >> 2) == 1 ? early << 4 : 0)) {
+    switch (mode | ((mode >> 2 & 1) ? early << 4 : 0)) {
 #define AF_MODE_CASE(pro, kind) \
   case GEMV_MODE(pro, kind):    \
     launch_one<LX, 16, false, GEMV_MODE(pro, kind)>(grid, lds, st, p); \
     break;
-#define AF_MODE_CASES(pro) AF_MODE_CASE(pro, 1) AF_MODE_CASE(pro, 1 | 1 << 2) AF_MODE_CASE(pro, 1 | 2 << 2) \
-                           AF_MODE_CASE(pro, 1 | GEMV_EARLY_NONE << 2)
+#define AF_MODE_CLASSES(pro, kind) AF_MODE_CASE(pro, kind) AF_MODE_CASE(pro, kind | 1 << 2) \
+                                   AF_MODE_CASE(pro, kind | 2 << 2) AF_MODE_CASE(pro, kind | GEMV_EARLY_NONE << 2)
+#define AF_MODE_CASES(pro) AF_MODE_CLASSES(pro, 1) AF_MODE_CLASSES(pro, 3)
       AF_MODE_CASES(AF_PRO_RMSNORM)
       AF_MODE_CASES(AF_PRO_NONE)
       AF_MODE_CASES(AF_PRO_SILUMUL)
 #undef AF_MODE_CASES
-      AF_MODE_CASE(AF_PRO_RMSNORM, 3)
-      AF_MODE_CASE(AF_PRO_NONE, 3)
-      AF_MODE_CASE(AF_PRO_SILUMUL, 3)
+#undef AF_MODE_CLASSES
       AF_MODE_CASE(AF_PRO_RMSNORM, 0)
       AF_MODE_CASE(AF_PRO_NONE, 0)
       AF_MODE_CASE(AF_PRO_SILUMUL, 0)
@@ -146,12 +145,13 @@ static void launch_pair_one(dim3 grid, size_t lds, hipStream_t st, const GemvPai
 template <int LX>
 static void launch_pair(int early, dim3 grid, size_t lds, hipStream_t st, const GemvPairParams& d) {
   const int mode = gemv_mode_of(d.p);
-  switch (mode | ((mode >> 2) == 1 ? early << 4 : 0)) {
+  switch (mode | ((mode >> 2 & 1) ? early << 4 : 0)) {
 #define AF_MODE_CASE(kind) \
   case GEMV_MODE(AF_PRO_SILUMUL, kind): \
     launch_pair_one<LX, GEMV_MODE(AF_PRO_SILUMUL, kind)>(grid, lds, st, d); \
     break;
-    AF_MODE_CASE(1) AF_MODE_CASE(1 | 1 << 2) AF_MODE_CASE(1 | 2 << 2) AF_MODE_CASE(1 | GEMV_EARLY_NONE << 2) AF_MODE_CASE(3)
+    AF_MODE_CASE(1) AF_MODE_CASE(1 | 1 << 2) AF_MODE_CASE(1 | 2 << 2) AF_MODE_CASE(1 | GEMV_EARLY_NONE << 2)
+    AF_MODE_CASE(3) AF_MODE_CASE(3 | 1 << 2) AF_MODE_CASE(3 | 2 << 2) AF_MODE_CASE(3 | GEMV_EARLY_NONE << 2)
 #undef AF_MODE_CASE
     default:
       launch_pair_one<LX, -1>(grid, lds, st, d);
@@ -241,6 +241,7 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   plan->lx = lx;
   plan->nw = nw;
   plan->early = early;
+  if (range_sel && nw == 16 && !whole_layer && !a.router_Wr) plan->early = gemv_range_class(r.n, S);
   if (early != GEMV_EARLY_NONE) p.early_cycles = af_dealt_cycles(r.n, S);
   plan->lds = xs_bytes + (size_t)list_cap * 4;
   return AF_OK;

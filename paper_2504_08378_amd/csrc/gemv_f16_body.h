@@ -156,7 +156,10 @@ struct GemvEarlyLds : GemvLds<NW, TWMAX> {
 // EARLY (top-k launches of 1024-thread workgroups): the rows whose selection is obvious are
 // requested before the front end runs (RowPrologue, "early rows").  EARLY is the number of
 // vectors of the operator's source that one thread holds (1, 4 or 8; 0: no early rows).
-template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, bool PAIR = false, typename LDS_T>
+// RANGE (threshold launches of 1024-thread workgroups without an index list): passes of 64 channels
+// that a wave decides in registers (RowPrologue, threshold_wave), requesting its first rows at once; 0: the
+// form that builds x in LDS.
+template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, bool PAIR = false, int RANGE = 0, typename LDS_T>
 __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos vb,
                                               unsigned short* xs, LDS_T& lds, const int pair = 0) {
   constexpr int GEMV_THREADS = NW * AF_WAVE;
@@ -241,7 +244,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   // head the waves stalled on the requests themselves (q|k|v of the 7B shape: the last wave got
   // its eighth request out 2.3 us after its first) and held up the front end.
   // The narrowest tiles (four rows a batch) get by with four.
-  constexpr int UE = EARLY ? (LX == 16 ? 4 : 8) : 1;
+  constexpr int UE = EARLY || RANGE ? (LX == 16 ? 4 : 8) : 1;
   half8 ew[UE];
 #pragma unroll
   for (int u = 0; u < UE; ++u)
@@ -250,6 +253,39 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   int early_n = 0;
   bool early_pending = false;
   typename RP::EarlyWave early;
+  typename RP::template RangeWave<RANGE ? RANGE : 1> range;
+  // Batches U0 .. U0 + 3 of the early rows.  A missing row is read as the wave's last one, or as row 0:
+  // no branch around the loads.
+  auto request_of = [&](auto from, auto channel_of) __attribute__((always_inline)) {
+    if constexpr (EARLY || RANGE) {
+      constexpr int U0 = decltype(from)::value;
+      const unsigned* row = lds.early_row[wave];
+      unsigned e[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) e[u] = row[max(min((U0 + u) * LY + ly, early_n - 1), 0)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const unsigned j = early_n > 0 ? channel_of(e[u]) : 0u;
+        ew[U0 + u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)j * p.ld));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if constexpr (RANGE) {
+    RP::template threshold_wave<RANGE>(r, s_rp, S, s, vb.bx == 0, range);
+    early_n = min(__popcll(range.kept[0]), UE * LY);
+    const int rank = (int)RP::lanes_below(range.kept[0]);
+    if (((range.kept[0] >> lane) & 1ull) && rank < early_n)
+      lds.early_row[wave][rank] = (unsigned)(range.first + lane) << 16 | range.bits[0];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // read by the other lanes of this wave
+    __builtin_amdgcn_wave_barrier();
+    auto channel_of = [](unsigned e) { return e >> 16; };
+    request_of(std::integral_constant<int, 0>{}, channel_of);
+    if constexpr (UE == 8) {
+      if (early_n > 4 * LY) request_of(std::integral_constant<int, 4>{}, channel_of);
+    }
+    early_pending = true;
+  }
   if constexpr (EARLY) {
     early = RP::early_block(r.n, S, s, p.early_cycles);
     half_t ea, eb;
@@ -265,18 +301,8 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     unsigned* row = lds.early_row[wave];
     early_n = RP::template early_pick<UE * LY>(r, early, row, ea, eb);
-    // A missing row is read as the wave's last one, or as row 0: no branch around the loads.
     auto request = [&](auto from) __attribute__((always_inline)) {
-      constexpr int U0 = decltype(from)::value;
-      unsigned e[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) e[u] = row[max(min((U0 + u) * LY + ly, early_n - 1), 0)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const unsigned j = early_n > 0 ? e[u] & 0xFFFFu : 0u;
-        ew[U0 + u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)j * p.ld));
-      }
-      __builtin_amdgcn_sched_barrier(0);
+      request_of(from, [](unsigned e) { return e & 0xFFFFu; });
     };
     request(std::integral_constant<int, 0>{});
     RP::template produce_raw<EARLY>(r, raw, xs, s_rp, s == 0, vb.bx, vb.gx, s_scratch);
@@ -291,6 +317,18 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   // 64 bits, 4096 -> 22016 at 30 %: 1.48e-7 against 1.29e-7 of a sum in index order).
   float early_acc[EARLY ? 8 : 1] = {};
   auto take_early = [&]() __attribute__((always_inline)) {
+    if constexpr (RANGE) {  // the first channels, not the largest: into the running sums
+      early_pending = false;
+#pragma unroll
+      for (int u = 0; u < UE; ++u) {
+        const int i = u * LY + ly;
+        if (i < early_n) {
+          const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(lds.early_row[wave][i] & 0xFFFFu));
+#pragma unroll
+          for (int c = 0; c < 8; ++c) acc[c] += (float)ew[u][c] * xv;
+        }
+      }
+    }
     if constexpr (EARLY) {
       early_pending = false;
 #pragma unroll
@@ -321,7 +359,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       // scheduler has, in some instantiations, paired every load with its own wait (one row in
       // flight instead of U), which halves the streaming rate.
       __builtin_amdgcn_sched_barrier(0);
-      if (EARLY && early_pending) take_early();
+      if ((EARLY || RANGE) && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -346,7 +384,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
           for (int c = 0; c < 8; ++c) w[u][c] = (half_t)0;
         }
       }
-      if (EARLY && early_pending) take_early();
+      if ((EARLY || RANGE) && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -362,6 +400,9 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] += early_acc[c];
     RP::early_write_list(r, xs, lds.early, early, s * vb.gx + vb.bx, vb.gx * S);
+  } else if constexpr (RANGE) {
+    stream(RP::template threshold_list<RANGE>(range, early_n, s_rp, s_list));
+    if (early_pending) take_early();
   } else if (p.range_sel()) {
     stream(routed ? RP::threshold_range_of_full(r, xs, s_rp, s_list, S, s)
                   : RP::threshold_range(r, xs, s_rp, s_list, S, s, vb.bx == 0));
@@ -491,7 +532,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
 // A kernel instantiated for one mode carries none of the other modes' code and branches, which
 // measured 0.4-0.5 us per launch (q|k|v 16.7 -> 16.3 us, gate|up 23.5 -> 23.0 us); mode -1 is
 // the generic kernel that reads both from its arguments.  Top-k modes carry the width class of
-// their input (gemv_early_class) in bits 4 and 5.
+// their input (gemv_early_class) in bits 4 and 5, threshold modes per channel range the class of a wave's share.
 #define GEMV_MODE(pro, kind) ((pro) | ((kind) << 2))
 template <int MODE>
 __device__ __forceinline__ GemvParams gemv_fix_mode(const GemvParams& p) {
@@ -516,6 +557,12 @@ static inline int gemv_mode_of(const GemvParams& p) {
 constexpr int gemv_early(int mode, int nw, bool routed) {
   constexpr int vectors[4] = {1, 4, 8, 0};
   return mode >= 0 && ((mode >> 2) & 3) == 1 && nw == 16 && !routed ? vectors[mode >> 4] : 0;
+}
+// Passes of the threshold launches that decide their channels in registers: shares of up to 64, 128
+// and 256 channels per wave.  Wider ones (class GEMV_EARLY_NONE) build x in LDS.
+constexpr int gemv_range(int mode, int nw, bool routed) {
+  constexpr int passes[4] = {1, 2, 4, 0};
+  return mode >= 0 && ((mode >> 2) & 3) == 3 && nw == 16 && !routed ? passes[mode >> 4] : 0;
 }
 enum { GEMV_EARLY_NONE = 3 };
 // Rows that a wave of a launch with LX lanes across a tile can take.
@@ -555,12 +602,12 @@ static_assert(8 * RP_EV * 1024 >= AF_MAX_N, "the widest input fits the largest c
 template <int LX, int U, int NW, bool ROUTED, int MODE = -1>
 __global__ __launch_bounds__(NW * AF_WAVE) void gemv_f16_kernel(GemvParams p) {
   extern __shared__ __align__(16) unsigned short xs[];  // the operator input, when built here
-  constexpr int EARLY = gemv_early(MODE, NW, ROUTED);
-  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
+  constexpr int EARLY = gemv_early(MODE, NW, ROUTED), RANGE = gemv_range(MODE, NW, ROUTED);
+  __shared__ std::conditional_t<(EARLY + RANGE > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
   const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y};
   if constexpr (MODE >= 0) {
     const GemvParams q = gemv_fix_mode<MODE>(p);
-    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(q, vb, xs, lds);
+    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY, false, RANGE>(q, vb, xs, lds);
   } else {
     gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(p, vb, xs, lds);
   }
@@ -579,8 +626,8 @@ template <int LX, int U, int MODE>
 __global__ __launch_bounds__(16 * AF_WAVE) void gemv_f16_pair_kernel(GemvPairParams d) {
   constexpr int NW = 16;
   extern __shared__ __align__(16) unsigned short xs[];
-  constexpr int EARLY = gemv_early(MODE, NW, false);
-  __shared__ std::conditional_t<(EARLY > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
+  constexpr int EARLY = gemv_early(MODE, NW, false), RANGE = gemv_range(MODE, NW, false);
+  __shared__ std::conditional_t<(EARLY + RANGE > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
   const int S = (int)gridDim.y >> 1, pair = (int)blockIdx.y >= S;
   const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y - pair * S, (int)gridDim.x, S};
   GemvParams q = gemv_fix_mode<MODE>(d.p);
@@ -593,5 +640,5 @@ __global__ __launch_bounds__(16 * AF_WAVE) void gemv_f16_pair_kernel(GemvPairPar
     q.y_scale += 1;
     q.partials += (size_t)S * q.out_pad;
   }
-  gemv_f16_body<LX, U, NW, false, false, EARLY, true>(q, vb, xs, lds, pair);
+  gemv_f16_body<LX, U, NW, false, false, EARLY, true, RANGE>(q, vb, xs, lds, pair);
 }

@@ -91,12 +91,14 @@ template <int LX, int U, int NW, bool CL, bool ROUTED, int MODE = -1>
 __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
   Q4Params p = p_in;
   if constexpr (MODE >= 0) {
-    constexpr int pro = MODE & 3, kind = MODE >> 2;
+    constexpr int pro = MODE & 3, kind = (MODE >> 2) & 3;
     p.rows.pro = pro;
     p.rows.sel = kind == 0 ? (int)AF_ROWS_GIVEN : (kind == 1 ? (int)AF_SEL_TOPK : (int)AF_SEL_THRESHOLD);
     p.use_lds_x = (pro != AF_PRO_NONE || kind != 0) ? 1 : 0;
     p.range_sel = kind == 3 ? 1 : 0;
   }
+  // channels of a threshold launch decided in registers, as in the fp16 kernel (RowPrologue, threshold_wave)
+  constexpr int RANGE = MODE >= 0 && ((MODE >> 2) & 3) == 3 && NW == 16 && !ROUTED && (MODE >> 4) < 3 ? 1 << (MODE >> 4) : 0;
   constexpr int THREADS = NW * AF_WAVE;
   constexpr int LY = AF_WAVE / LX;
   constexpr int TW = LX * 8;
@@ -244,7 +246,11 @@ __global__ __launch_bounds__(NW * AF_WAVE) void gemv_q4_kernel(Q4Params p_in) {
     }
   };
 
-  if (p.range_sel) {
+  if constexpr (RANGE) {
+    typename RP::template RangeWave<RANGE> range;
+    RP::template threshold_wave<RANGE>(r, s_rp, S, s, blockIdx.x == 0, range);
+    stream(RP::template threshold_list<RANGE>(range, 0, s_rp, s_list));
+  } else if (p.range_sel) {
     stream(routed ? RP::threshold_range_of_full(r, xs, s_rp, s_list, S, s)
                   : RP::threshold_range(r, xs, s_rp, s_list, S, s, blockIdx.x == 0));
   } else if (r.sel != AF_ROWS_GIVEN) {
@@ -341,7 +347,7 @@ static void q4_launch_one(dim3 grid, size_t lds, hipStream_t st, const Q4Params&
 template <int LX, bool CL>
 static void q4_launch_mode(dim3 grid, size_t lds, hipStream_t st, const Q4Params& p) {
   const int kind = p.rows.sel == AF_ROWS_GIVEN ? 0 : (p.rows.sel == AF_SEL_TOPK ? 1 : (p.range_sel ? 3 : 2));
-  switch (Q4_MODE(p.rows.pro, kind)) {
+  switch (Q4_MODE(p.rows.pro, kind) | (kind == 3 ? gemv_range_class(p.rows.n, (int)grid.y) << 4 : 0)) {
 #define AF_MODE_CASE(pro, kind_) \
   case Q4_MODE(pro, kind_):      \
     q4_launch_one<LX, 16, CL, false, Q4_MODE(pro, kind_)>(grid, lds, st, p); \
@@ -349,9 +355,12 @@ static void q4_launch_mode(dim3 grid, size_t lds, hipStream_t st, const Q4Params
     AF_MODE_CASE(AF_PRO_RMSNORM, 1)
     AF_MODE_CASE(AF_PRO_NONE, 1)
     AF_MODE_CASE(AF_PRO_SILUMUL, 1)
-    AF_MODE_CASE(AF_PRO_RMSNORM, 3)
-    AF_MODE_CASE(AF_PRO_NONE, 3)
-    AF_MODE_CASE(AF_PRO_SILUMUL, 3)
+#define AF_MODE_CLASSES(pro) AF_MODE_CASE(pro, 3) AF_MODE_CASE(pro, 3 | 1 << 2) AF_MODE_CASE(pro, 3 | 2 << 2) \
+                             AF_MODE_CASE(pro, 3 | 3 << 2)
+    AF_MODE_CLASSES(AF_PRO_RMSNORM)
+    AF_MODE_CLASSES(AF_PRO_NONE)
+    AF_MODE_CLASSES(AF_PRO_SILUMUL)
+#undef AF_MODE_CLASSES
     AF_MODE_CASE(AF_PRO_RMSNORM, 0)
     AF_MODE_CASE(AF_PRO_NONE, 0)
     AF_MODE_CASE(AF_PRO_SILUMUL, 0)

@@ -26,6 +26,12 @@
 typedef _Float16 rp_half __attribute__((ext_vector_type(RP_EV)));
 typedef unsigned short rp_u16 __attribute__((ext_vector_type(RP_EV)));
 
+// Class of a wave's share of a split's channels (1024-thread workgroups): up to 64, 128, 256 channels, more.
+static inline int gemv_range_class(int n, int S) {
+  const int share = ((n / RP_EV + S - 1) / S * RP_EV + 15) / 16;
+  return share <= 64 ? 0 : (share <= 128 ? 1 : (share <= 256 ? 2 : 3));
+}
+
 template <int THREADS>
 struct RowPrologue {
   static constexpr int WAVES = THREADS / AF_WAVE;
@@ -844,6 +850,107 @@ struct RowPrologue {
       for (int c = 0; c < GROUP / 2; ++c)
         if ((keep >> c) & 1u) r.idx_out[pos++] = h * (GROUP / 2) + c;
     }
+  }
+
+  // ---- threshold form, one wave's channels in registers ---------------------------------------
+  // A threshold decides a channel without a look at any other, so a wave can decide its own: lane l has
+  // channels first + l, first + 64 + l, ... of the split's contiguous range (at most 64 P per wave), and what is
+  // kept is a mask per 64 of them.  The rows of the first are requested at once; the others' places in the
+  // split's list follow from population counts.  x goes through LDS nowhere.  (threshold_range, for wider
+  // shares and the in-kernel router, builds x in LDS and counts, scans and lists it there.)  us before / now:
+  //   7B step at 50 % 2056 / 1916, its layers at 30 % 75.7 / 71.4, at 80 % 45.6 / 42.6; 4-bit (the list alone,
+  //   no rows early) 52.0 / 50.5 and at 80 % 43.1 / 41.6; 70B-shape layers at 50 % 165.1 / 159.8
+  //   4096 -> 12288 behind the norm at 40 % 14.39 / 12.85; 11008 -> 4096 behind SiLU 12.17 / 11.42, at 80 %
+  //   7.21 / 6.90; 1000 -> 30000 10.17 / 9.28; 16384 -> 32768 (wide shares, the LDS form) 98.6 / 99.1
+  template <int P>
+  struct RangeWave {
+    int first;                   // the wave's first channel
+    unsigned bits[P];            // fp16 bits of x
+    unsigned long long kept[P];  // and whether the channel passes, per lane
+  };
+  template <int P>
+  static __device__ __forceinline__ void threshold_wave(const af_row_src& r, Smem& sm, int S, int s, bool store_x,
+                                                        RangeWave<P>& rw) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+    const int n = r.n, nvec = n / RP_EV;
+    const int V = af_ceil_div_small(nvec, S);
+    const int c0 = min(s * V, nvec) * RP_EV, c1 = min(min(s * V, nvec) + V, nvec) * RP_EV;
+    const int share = (c1 - c0 + WAVES - 1) / WAVES;
+    rw.first = c0 + wave * share;
+    const int end = min(rw.first + share, c1);
+    half_t a[P], b[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int j = min(rw.first + i * AF_WAVE + lane, n - 1);
+      a[i] = r.src[j];
+      b[i] = r.pro == AF_PRO_NONE ? (half_t)0 : (r.pro == AF_PRO_RMSNORM ? r.gain[j] : r.src[n + j]);
+    }
+    float scale = 1.f;
+    if (r.pro == AF_PRO_RMSNORM) {  // the sum of squares as in threshold_range
+      const rp_half* src = reinterpret_cast<const rp_half*>(r.src);
+      rp_half zero;
+#pragma unroll
+      for (int c = 0; c < RP_EV; ++c) zero[c] = (half_t)0;
+      float ss = 0.f;
+      constexpr int B = 2;
+      for (int v0 = tid; v0 < nvec; v0 += B * THREADS) {
+        rp_half t[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) t[u] = (v0 + u * THREADS < nvec) ? src[v0 + u * THREADS] : zero;
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+#pragma unroll
+          for (int c = 0; c < RP_EV; ++c) ss += (float)t[u][c] * (float)t[u][c];
+      }
+      ss = af_wave_sum(ss);
+      if (lane == 0) sm.red[wave] = ss;
+      __syncthreads();
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) tot += sm.red[w];
+      scale = 1.0f / sqrtf(tot / (float)n + r.eps);
+    }
+    const int T = threshold_key(r.t);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int j = rw.first + i * AF_WAVE + lane;
+      half_t x = a[i];
+      if (r.pro != AF_PRO_NONE) {
+        // The product is rounded to fp32 first, as in the other forms of the front end, which work on vectors:
+        // for one element the compiler would take an instruction that rounds it to fp16 at once.
+        float v = r.pro == AF_PRO_RMSNORM ? (float)x * scale * (float)b[i] : silu_mul((float)x, (float)b[i]);
+        asm("" : "+v"(v));
+        x = (half_t)v;
+      }
+      rw.bits[i] = __builtin_bit_cast(unsigned short, x);
+      const unsigned key = rw.bits[i] & 0x7FFFu;
+      rw.kept[i] = __ballot(j < end && (int)key > T && key <= 0x7C00u);
+      if (store_x && r.x_out != nullptr && j < end) r.x_out[j] = x;
+    }
+  }
+  // The kept channels but the first `taken` of the wave's first 64 into the split's list, ascending; returns
+  // their number.
+  template <int P>
+  static __device__ __forceinline__ int threshold_list(const RangeWave<P>& rw, int taken, Smem& sm, unsigned* list) {
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    static_assert(WAVES <= 16, "one row of lanes");
+    unsigned mine = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) mine += (unsigned)__popcll(rw.kept[i]);
+    mine -= (unsigned)taken;
+    if (lane == 0) sm.wave_tot[wave] = mine;
+    __syncthreads();
+    const unsigned scan = af_row_incl_scan(sm.wave_tot[lane % WAVES]);
+    int pos = __builtin_amdgcn_readlane((int)scan, wave) - (int)mine - taken;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int rank = (int)lanes_below(rw.kept[i]);
+      if (((rw.kept[i] >> lane) & 1ull) && (i > 0 || rank >= taken))
+        list[pos + rank] = (unsigned)(rw.first + i * AF_WAVE + lane) << 16 | rw.bits[i];
+      pos += __popcll(rw.kept[i]);
+    }
+    __syncthreads();
+    return __builtin_amdgcn_readlane((int)scan, WAVES - 1);
   }
 
   static __device__ __forceinline__ unsigned counts(unsigned long long gt, unsigned long long eq) {

@@ -165,6 +165,46 @@ def test_range_threshold_special_values_and_residual(ctx):
     assert np.array_equal(to_host(y), res)            # nothing passes: y is the residual
 
 
+@pytest.mark.parametrize("producer", [B.AF_PRO_NONE, B.AF_PRO_RMSNORM, B.AF_PRO_SILUMUL])
+@pytest.mark.parametrize("n,out,split,share", [
+    (8, 8, 1, 0.5), (1016, 136, 1, 0.5), (1024, 136, 1, 1.0), (1032, 136, 1, 0.02),   # up to 64 channels a wave, one more
+    (2048, 264, 1, 0.5), (2056, 520, 3, 0.9), (4096, 136, 1, 0.4), (4104, 136, 1, 0.4),  # 128, 256, and wider shares
+    (3000, 8200, 7, 0.3), (3000, 14000, 5, 0.0),                                      # wider tiles, ragged splits, none kept
+])
+def test_range_threshold_shares(ctx, n, out, split, share, producer):
+    """Every class of a wave's share against the oracle's product over the channels that pass, with x the
+    GPU's own (the tap); a NaN never passes."""
+    W, h = _wx(out, n, n + split)
+    src, gain = h, None
+    if producer == B.AF_PRO_SILUMUL:
+        src = np.concatenate([h, h[::-1]])
+    elif producer == B.AF_PRO_RMSNORM:
+        gain = S.norm_gain(3, n, "shares")
+    else:
+        src = h.copy()
+        src[n // 2] = np.nan
+    t = 0.0
+    Wt = ctx.pack_inmajor_f16(to_dev(W))
+    ctx.set_option(B.AF_OPT_TUNE_SPLIT, split)
+    try:
+        args = dict(producer=producer, gain=None if gain is None else to_dev(gain), eps=1e-5)
+        _, x = _run_noidx(ctx, Wt, to_dev(src), n, t=1e9, **args)
+        mag = np.sort(np.abs(x[np.isfinite(x)].astype(np.float64)))[::-1]
+        keep = int(share * len(mag))
+        t = -1.0 if share == 1.0 else (float(mag[keep]) if keep < len(mag) else 0.0)
+        if share == 0.0:
+            t = float(mag[0])
+        y, x2 = _run_noidx(ctx, Wt, to_dev(src), n, t=t, **args)
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+    assert np.array_equal(x.view(np.uint16), x2.view(np.uint16))
+    idx = O.select_threshold(x, t)
+    assert len(idx) == 0 if share == 0.0 else len(idx) > 0
+    # the oracle multiplies the masked vector out densely (NaN * 0 = NaN)
+    ref = O.sparse_gemv(W, np.nan_to_num(x, nan=0.0), idx)
+    assert O.rel_err(y, ref) <= 1e-4 if len(idx) else not np.any(y)
+
+
 @pytest.mark.parametrize("n,out", [(256, 264), (4096, 12288), (5120, 1032), (8192, 10240)])
 def test_range_threshold_rmsnorm_producer(ctx, n, out):
     W, h = _wx(out, n, n + 1)
