@@ -104,7 +104,7 @@ static void launch_lx(int nw, int early, dim3 grid, size_t lds, hipStream_t st, 
       launch_one<LX, 16, true, -1>(grid, lds, st, p);
   } else if (nw == 16) {
     const int mode = gemv_mode_of(p);
-    switch (mode | ((mode >> 2 & 1) ? early << 4 : 0)) {
+    switch (mode | ((mode >> 2 & 1) || mode == GEMV_MODE(AF_PRO_RMSNORM, 0) || mode == GEMV_MODE(AF_PRO_SILUMUL, 0) ? early << 4 : 0)) {
 #define AF_MODE_CASE(pro, kind) \
   case GEMV_MODE(pro, kind):    \
     launch_one<LX, 16, false, GEMV_MODE(pro, kind)>(grid, lds, st, p); \
@@ -115,11 +115,11 @@ static void launch_lx(int nw, int early, dim3 grid, size_t lds, hipStream_t st, 
       AF_MODE_CASES(AF_PRO_RMSNORM)
       AF_MODE_CASES(AF_PRO_NONE)
       AF_MODE_CASES(AF_PRO_SILUMUL)
+      AF_MODE_CLASSES(AF_PRO_RMSNORM, 0)
+      AF_MODE_CLASSES(AF_PRO_SILUMUL, 0)
 #undef AF_MODE_CASES
 #undef AF_MODE_CLASSES
-      AF_MODE_CASE(AF_PRO_RMSNORM, 0)
       AF_MODE_CASE(AF_PRO_NONE, 0)
-      AF_MODE_CASE(AF_PRO_SILUMUL, 0)
 #undef AF_MODE_CASE
       default:
         launch_one<LX, 16, false, -1>(grid, lds, st, p);
@@ -242,6 +242,9 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   plan->nw = nw;
   plan->early = early;
   if (range_sel && nw == 16 && !whole_layer && !a.router_Wr) plan->early = gemv_range_class(r.n, S);
+  // Given rows: their number has to be known here.
+  if (r.sel == AF_ROWS_GIVEN && r.pro != AF_PRO_NONE && r.nidx_dev == nullptr && nw == 16 && !whole_layer && !a.router_Wr && !a.pair)
+    plan->early = gemv_given_class(r.n, r.nidx_host, S, lx);
   if (early != GEMV_EARLY_NONE) p.early_cycles = af_dealt_cycles(r.n, S);
   plan->lds = xs_bytes + (size_t)list_cap * 4;
   return AF_OK;

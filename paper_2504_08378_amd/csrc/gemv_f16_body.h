@@ -156,10 +156,13 @@ struct GemvEarlyLds : GemvLds<NW, TWMAX> {
 // EARLY (top-k launches of 1024-thread workgroups): the rows whose selection is obvious are
 // requested before the front end runs (RowPrologue, "early rows").  EARLY is the number of
 // vectors of the operator's source that one thread holds (1, 4 or 8; 0: no early rows).
+// GIVEN (1024-thread launches behind a producer whose rows are known, and their number on the host): the
+// rows of a lane's first U steps are requested before x is built.  GIVEN is the number of source vectors
+// of a thread, as for EARLY.
 // RANGE (threshold launches of 1024-thread workgroups without an index list): passes of 64 channels
 // that a wave decides in registers (RowPrologue, threshold_wave), requesting its first rows at once; 0: the
 // form that builds x in LDS.
-template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, bool PAIR = false, int RANGE = 0, typename LDS_T>
+template <int LX, int U, int NW, bool ROUTED, bool PHASE, int EARLY, bool PAIR = false, int RANGE = 0, int GIVEN = 0, typename LDS_T>
 __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos vb,
                                               unsigned short* xs, LDS_T& lds, const int pair = 0) {
   constexpr int GEMV_THREADS = NW * AF_WAVE;
@@ -214,7 +217,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
         wr[e] = *reinterpret_cast<const half8*>(p.router_Wr + (size_t)e * r.n + (size_t)tid * 8);
     }
   }
-  if constexpr (!EARLY) {
+  if constexpr (!EARLY && !GIVEN) {
     if (p.use_lds_x() && (!p.range_sel() || routed))
       RP::produce(r, xs, s_rp, s == 0, vb.bx, vb.gx, r.sel == AF_SEL_TOPK ? s_scratch : nullptr);
   }
@@ -244,7 +247,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   // head the waves stalled on the requests themselves (q|k|v of the 7B shape: the last wave got
   // its eighth request out 2.3 us after its first) and held up the front end.
   // The narrowest tiles (four rows a batch) get by with four.
-  constexpr int UE = EARLY || RANGE ? (LX == 16 ? 4 : 8) : 1;
+  constexpr int UE = EARLY || RANGE ? (LX == 16 ? 4 : 8) : (GIVEN ? U : 1);
   half8 ew[UE];
 #pragma unroll
   for (int u = 0; u < UE; ++u)
@@ -286,6 +289,32 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     }
     early_pending = true;
   }
+  unsigned given[GIVEN ? UE : 1];  // channels of the rows of the lane's first U steps
+  int given_n = 0;                 // rows of the split's first staging pass
+  if constexpr (GIVEN) {
+    const int R = af_ceil_div_small(r.nidx_host, S), r0 = min(s * R, r.nidx_host);
+    given_n = min(min(r0 + R, r.nidx_host) - r0, GEMV_LIST);
+#pragma unroll
+    for (int u = 0; u < UE; ++u) {  // a missing row is read as the split's last one, or as row 0
+      const int i = r0 + max(min(u * STEP + wave * LY + ly, given_n - 1), 0);
+      given[u] = given_n == 0 ? 0u : (r.idx ? (unsigned)r.idx[i] : (unsigned)i);
+    }
+    typename RP::template Raw<GIVEN> raw;
+    RP::template load_raw<GIVEN>(r, raw);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): see EARLY
+    auto request = [&](int u0, int u1) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = u0; u < u1; ++u) {
+        const unsigned j = given[u] < (unsigned)r.n ? given[u] : 0u;
+        ew[u] = af_load_once(reinterpret_cast<const half8*>(wcol + (size_t)j * p.ld));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    request(0, UE / 2);
+    RP::template produce_raw<GIVEN>(r, raw, xs, s_rp, s == 0, vb.bx, vb.gx, nullptr);
+    request(UE / 2, UE);
+    early_pending = true;
+  }
   if constexpr (EARLY) {
     early = RP::early_block(r.n, S, s, p.early_cycles);
     half_t ea, eb;
@@ -317,6 +346,21 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   // 64 bits, 4096 -> 22016 at 30 %: 1.48e-7 against 1.29e-7 of a sum in index order).
   float early_acc[EARLY ? 8 : 1] = {};
   auto take_early = [&]() __attribute__((always_inline)) {
+    if constexpr (GIVEN) {
+      early_pending = false;
+#pragma unroll
+      for (int u = 0; u < UE; ++u) {
+        if (u * STEP + wave * LY + ly < given_n) {
+          if (given[u] < (unsigned)r.n) {
+            const float xv = (float)__builtin_bit_cast(half_t, xs[given[u]]);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[c] += (float)ew[u][c] * xv;
+          } else if (lx == 0) {  // broken precondition: nothing is added, and the error word
+            af_report_bad_index(p.tickets);
+          }
+        }
+      }
+    }
     if constexpr (RANGE) {  // the first channels, not the largest: into the running sums
       early_pending = false;
 #pragma unroll
@@ -345,8 +389,8 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
   };
 
   // One pass over `cnt` staged rows of s_list.
-  auto stream = [&](int cnt) {
-    int i = wave * LY + ly;
+  auto stream = [&](int cnt, int from = 0) {
+    int i = from + wave * LY + ly;
     for (; i + (U - 1) * STEP < cnt; i += U * STEP) {
       half8 w[U];
       unsigned e[U];
@@ -359,7 +403,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
       // scheduler has, in some instantiations, paired every load with its own wait (one row in
       // flight instead of U), which halves the streaming rate.
       __builtin_amdgcn_sched_barrier(0);
-      if ((EARLY || RANGE) && early_pending) take_early();
+      if ((EARLY || RANGE || GIVEN) && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -384,7 +428,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
           for (int c = 0; c < 8; ++c) w[u][c] = (half_t)0;
         }
       }
-      if ((EARLY || RANGE) && early_pending) take_early();
+      if ((EARLY || RANGE || GIVEN) && early_pending) take_early();
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float xv = (float)__builtin_bit_cast(half_t, (unsigned short)(e[u] & 0xFFFFu));
@@ -419,12 +463,13 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
     const unsigned short* xg = reinterpret_cast<const unsigned short*>(r.src);
     for (int base = r0; base < r1; base += GEMV_LIST) {
       const int cnt = min(GEMV_LIST, r1 - base);
+      const int from = GIVEN && base == r0 ? U * STEP : 0;  // the rows in front have been requested
       __syncthreads();
       if (prefetched && base == r0) {
 #pragma unroll
         for (int u = 0; u < PF; ++u) {
           const int i = tid + u * GEMV_THREADS;
-          if (i < cnt) {
+          if (i < cnt && i >= from) {
             const int j = pre[u];
             if ((unsigned)j < (unsigned)r.n) {
               const unsigned bits = p.use_lds_x() ? xs[j] : xg[j];
@@ -436,7 +481,7 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
           }
         }
       } else {
-        for (int i = tid; i < cnt; i += GEMV_THREADS) {
+        for (int i = from + tid; i < cnt; i += GEMV_THREADS) {
           const int j = r.idx ? r.idx[base + i] : base + i;
           if ((unsigned)j < (unsigned)r.n) {
             const unsigned bits = p.use_lds_x() ? xs[j] : xg[j];
@@ -448,8 +493,9 @@ __device__ __forceinline__ void gemv_f16_body(const GemvParams& p, const GemvPos
         }
       }
       __syncthreads();
-      stream(cnt);
+      stream(cnt, from);
     }
+    if (GIVEN && early_pending) take_early();
   }
   __syncthreads();  // s_scratch changes its role: histograms -> wave sums
 
@@ -564,6 +610,11 @@ constexpr int gemv_range(int mode, int nw, bool routed) {
   constexpr int passes[4] = {1, 2, 4, 0};
   return mode >= 0 && ((mode >> 2) & 3) == 3 && nw == 16 && !routed ? passes[mode >> 4] : 0;
 }
+// Source vectors of a thread in the launches that request given rows ahead of x.
+constexpr int gemv_given(int mode, int nw, bool routed) {
+  constexpr int vectors[4] = {1, 4, 8, 0};
+  return mode >= 0 && ((mode >> 2) & 3) == 0 && (mode & 3) != AF_PRO_NONE && nw == 16 && !routed ? vectors[mode >> 4] : 0;
+}
 enum { GEMV_EARLY_NONE = 3 };
 // Rows that a wave of a launch with LX lanes across a tile can take.
 constexpr int gemv_early_cap(int lx) { return (lx == 16 ? 4 : 8) * AF_WAVE / lx; }
@@ -595,6 +646,16 @@ static inline int gemv_early_class(int pro, int n, int k, int S, int lx) {
                                     n / S / 16 * 2 * 1024 <= (pro == AF_PRO_SILUMUL ? 7 : 12) * early;
   return pays ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
 }
+// Given rows ahead of x.  The list has to be in registers first, which the plain form fetches in the shadow of
+// the norm; that costs short streams more than the rows' head start gives (us per layer, three of four
+// layers reusing two of four lists, plain / ahead; KB of rows per workgroup in q|k|v and gate|up):
+//   4096 channels: 105, 205 KB 51.4 / 52.0    262, 524 KB 67.3 / 67.5    367, 734 KB 78.8 / 77.9
+//   5120: 171, 256 KB 62.4 / 61.8    427, 640 KB 86.3 / 85.3      8192: 341, 2048 KB 168.0 / 166.5
+//   512 channels, 16 KB 34.6 / 36.1
+static inline int gemv_given_class(int n, int nidx, int S, int lx) {
+  const long long bytes = (long long)(nidx / S) * lx * 16;
+  return bytes >= (n <= RP_EV * 1024 ? 320 : 160) * 1024 ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
+}
 static_assert(8 * RP_EV * 1024 >= AF_MAX_N, "the widest input fits the largest class");
 
 // ROUTED: the instantiation that runs a mixture-of-experts router in its front end (kept apart
@@ -603,11 +664,12 @@ template <int LX, int U, int NW, bool ROUTED, int MODE = -1>
 __global__ __launch_bounds__(NW * AF_WAVE) void gemv_f16_kernel(GemvParams p) {
   extern __shared__ __align__(16) unsigned short xs[];  // the operator input, when built here
   constexpr int EARLY = gemv_early(MODE, NW, ROUTED), RANGE = gemv_range(MODE, NW, ROUTED);
+  constexpr int GIVEN = gemv_given(MODE, NW, ROUTED);
   __shared__ std::conditional_t<(EARLY + RANGE > 0), GemvEarlyLds<NW, LX * 8, gemv_early_cap(LX)>, GemvLds<NW, LX * 8>> lds;
   const GemvPos vb = {(int)blockIdx.x, (int)blockIdx.y, (int)gridDim.x, (int)gridDim.y};
   if constexpr (MODE >= 0) {
     const GemvParams q = gemv_fix_mode<MODE>(p);
-    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY, false, RANGE>(q, vb, xs, lds);
+    gemv_f16_body<LX, U, NW, ROUTED, false, EARLY, false, RANGE, GIVEN>(q, vb, xs, lds);
   } else {
     gemv_f16_body<LX, U, NW, ROUTED, false, EARLY>(p, vb, xs, lds);
   }

@@ -583,7 +583,7 @@ struct RowPrologue {
     }
   }
 
-  // x into xs and the first digit's histogram into `hist` (zeroed by the caller), from the loaded
+  // x into xs and (unless null) the first digit's histogram into `hist` (zeroed by the caller), from the loaded
   // source; the arithmetic is produce()'s.  The caller barriers between zeroing and this call.
   template <int B>
   static __device__ __forceinline__ void produce_raw(const af_row_src& r, Raw<B>& raw, unsigned short* xs,
@@ -620,7 +620,7 @@ struct RowPrologue {
           if (r.pro == AF_PRO_SILUMUL) h[c] = (half_t)silu_mul((float)h[c], (float)raw.b[u][c]);
         }
         xv[v] = h;
-        count_digit1(hist, h);
+        if (hist != nullptr) count_digit1(hist, h);
       }
     }
     __syncthreads();

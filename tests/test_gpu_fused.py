@@ -550,3 +550,22 @@ def test_early_rows_refused_where_they_cannot_run(ctx):
         ctx.set_option(B.AF_OPT_TUNE_WAVES, 0)
         ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
     ctx.synchronize()
+
+
+@pytest.mark.parametrize("producer", [B.AF_PRO_RMSNORM, B.AF_PRO_SILUMUL])
+@pytest.mark.parametrize("n,out,split", [(4096, 1032, 1), (4104, 136, 1), (8192, 264, 1), (8200, 6400, 3), (28672, 136, 5)])
+def test_given_rows_ahead_of_x(ctx, n, out, split, producer):
+    """Rows that are known (here all of them) are requested before x is built: one and several staging
+    passes, all three counts of source vectors, both sides of the tile, a ragged split."""
+    W, h = _wx(out, n, n + out)
+    src = np.concatenate([h, h[::-1]]) if producer == B.AF_PRO_SILUMUL else h
+    gain = to_dev(S.norm_gain(3, n, "given")) if producer == B.AF_PRO_RMSNORM else None
+    xo = torch.zeros(n, dtype=torch.float16, device="cuda")
+    Wt, srcd = ctx.pack_inmajor_f16(to_dev(W)), to_dev(src)
+    ctx.set_option(B.AF_OPT_TUNE_SPLIT, split)
+    try:
+        y = ctx.select_gemv_f16(Wt, srcd, producer=producer, gain=gain, x_out=xo, sel_mode=B.AF_SEL_DENSE, y_kind=B.AF_F32)
+        ctx.synchronize()
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+    assert O.rel_err(to_host(y), O.sparse_gemv(W, to_host(xo), np.arange(n))) <= 1e-4

@@ -616,3 +616,37 @@ def test_random_layer_shapes_stage_by_stage(ctx, i, d, nh, n_kv, hd, f, kv_len, 
     for p in range(4):   # the sets are the definition applied to the GPU's own inputs
         assert np.array_equal(got[p], own[p]), p
     assert max(errs.values()) <= TOL, errs
+
+
+@pytest.mark.parametrize("count", [0, 1, 63, 64, 65, 1500, 4600])
+@pytest.mark.parametrize("bad", [False, True])
+def test_reused_lists_requested_ahead_of_the_norm(ctx, count, bad):
+    """A reused list's first rows are requested before x exists: short lists, lists longer than a staging pass,
+    and an entry out of range, which adds nothing and is reported."""
+    if bad and count == 0:
+        pytest.skip("no entry to break")
+    shape = S.ModelShape("given", 1, 4608, 2, 1, 64, 64)
+    w = S.layer_weights(2, shape, 0)
+    h = S.activation(2, S.channel_scales(2, 4608, "given"), "h", 0)
+    K, V = S.kv_cache(2, 1, 8, 64, 4, "given", 0)
+    st = _dev_stack(ctx, shape, [w], [(K, V)], kv_cap=8)
+    rng = np.random.default_rng(count)
+    idx = np.sort(rng.choice(4608, size=count, replace=False)).astype(np.int32)
+    sent = idx.copy()
+    if bad:
+        sent[count // 2] = 4608 + 7
+        idx = np.delete(idx, count // 2)
+    ks = (count, 128, count, 64)
+    st.sets[0].load([sent, None, sent, None])
+    ctx.set_option(B.AF_OPT_TUNE_SPLIT, 2)
+    try:
+        hin = to_dev(h); hout = torch.zeros_like(hin)
+        st.layer(0, hin, hout, 4, 4, M.select_cfg(B.AF_SEL_TOPK, ks, reuse_mask=0b0101))
+        ctx.synchronize()
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+    assert ctx.last_device_error() == (B.AF_DEVERR_IDX if bad else 0)
+    t = _taps(ctx, shape)
+    for x, y, names in (("x_qkv", "qkv", ("Wq", "Wk", "Wv")), ("x_gateup", "gateup", ("Wgate", "Wup"))):
+        ref = np.concatenate([O.sparse_gemv(w[m], t[x], idx) for m in names])
+        assert O.rel_err(t[y], O.round_f16(ref)) <= TOL if len(idx) else not np.any(t[y]), y
