@@ -32,10 +32,10 @@ HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E bandwidth
 # FETCH_SIZE KiB x fetch factor + WRITE_SIZE KiB x write factor, the factors being what the same
 # counters read for a plain 256 MiB device copy of known size.  The output repeats file, kernel and
 # launch shape, and says whether the kernel's sources are still those that were counted.
-TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44415.5, "fetch_factor": 2.000, "write_KiB": 410.2, "write_factor": 1.000,
+TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44423.1, "fetch_factor": 2.000, "write_KiB": 410.2, "write_factor": 1.000,
                                "kernel": "gemv_f16_kernel<64, 8, 16, false, 5> grid 43x4",
                                "source": "profiles/gateup_7b_f16_sp50_pmc_traffic.md",
-                               "kernel_sources": "de59ea4c0f32"}}
+                               "kernel_sources": "15ecd59b021b"}}
 
 
 def kernel_sources_digest() -> str:
@@ -121,7 +121,7 @@ def union_bench(args, S, B, torch, np) -> int:
                    "B": Bt, "union_fraction_of_channels": [round(u, 4) for u in union_frac]},
         "union_weight_bytes_per_step": union_bytes,
         "union_weight_GBps": round(union_bytes * args.steps / dt / 1e9, 1),
-        "roofline": {"bound": "hbm", "kernel": "union_scan_kernel + union_place_kernel + gemv_union_kernel (gate|up)",
+        "roofline": {"bound": "hbm", "kernel": "union_mark_kernel + union_gather_kernel + gemv_union_kernel (gate|up)",
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": None,
                      "bytes_per_launch": alg, "us_per_launch": round(us, 3), "launches": 20},
