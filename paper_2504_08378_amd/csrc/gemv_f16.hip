@@ -37,12 +37,14 @@ static void choose_config(const af_ctx* ctx, int out, int nidx, bool selects, bo
   //  * tile width: 128 columns up to ~6K output columns, 256 up to ~12K, 512 beyond (within
   //    1-2 % of the best of the three for every operator);
   //  * splits: between three quarters of the CUs and all of them, the most that leave every
-  //    workgroup 320 rows (128-column tiles) or 500 rows (wider tiles); below that a workgroup
-  //    is mostly front end and reduction.  13B: o 13.1 against 14.6 us, gate|up 31.0 against
-  //    33.5 us, down 24.4 against 26.4 us for 240 against 160 workgroups; 70B down 54.9 against
-  //    58.9 us; Mixtral gate|up of two experts 43 against 53 us (224 against 112 workgroups);
-  //    7B o: 11.7 us with 6 splits, 12.1 with 8; 7B gate|up inside the stack: 21.8 us with 4
-  //    splits, 22.2 with 5.
+  //    workgroup 320 rows (128-column tiles) or 190 rows (wider tiles); below that a workgroup
+  //    is mostly front end and reduction.  13B: o 13.1 against 14.6 us, down 24.4 against 26.4 us for
+  //    240 against 160 workgroups; 70B down 54.9 against 58.9 us; Mixtral gate|up of two experts 43
+  //    against 53 us (224 against 112 workgroups).  With the tiles' tickets in cache lines of their own
+  //    more splits cost little (us at 500 rows a workgroup / 190): 4096 -> 22016 at 50 % 19.33 / 18.98,
+  //    thresholds 18.14 / 17.27; 4096 -> 12288 at 70 % 12.19 / 11.66; 5120 -> 15360 at 50 % 18.15 / 17.15, at
+  //    70 % 14.30 / 13.54; 8192 -> 8192 at 70 % 13.29 / 12.43; 13B step with reuse 3.475 / 3.442 ms, 7B
+  //    2.227 / 2.210.
   // Plain launches: 128-column tiles up to 16K columns and 512 beyond; with 256-column tiles on
   // a row stride that is a multiple of 1 KB every workgroup stays on one value of address bit 9
   // for all its rows, and the half of the workgroups on one of the two values finished ~2 us
@@ -63,7 +65,7 @@ static void choose_config(const af_ctx* ctx, int out, int nidx, bool selects, bo
     int s_min = ctx->n_cu * 3 / 4 / tiles;
     if (s_min < 1) s_min = 1;
     if (tiles * s_min < ctx->n_cu * 6 / 10 && tiles * (s_min + 1) <= ctx->n_cu) ++s_min;
-    const int rows_min = lx == 16 ? 320 : 500;
+    const int rows_min = lx == 16 ? 320 : 190;
     while (S > s_min && nidx / S < rows_min) --S;
     if (S < s_min) S = s_min;
   }
