@@ -13,17 +13,21 @@
 //            free as long as both operands agree, so it takes the eight whose probabilities it
 //            has already (no transposition of P), loads those eight rows of V and picks the
 //            columns by byte permutation.
-// q and the probabilities are held in fp32; each enters as two fp16 values (the rounded one and 2^11
-// times what the rounding left, 22 significant bits) in two instructions whose results are added in
-// fp32, so the products lose no more than fp32 ones.
+// q and the probabilities are fp32 values.  Each enters the instructions as three fp16 values, the rounded one
+// and two of what that leaves: all 24 bits of q, and of every weight above 2^-16 of the largest (smaller ones
+// to 2^-40 of it).  The sums over instructions and parts are rounded additions outside of them.  Error of the
+// fp32 results (before their rounding) against 64 bits, 32 heads on 32, scores of 0.4 rms, with the vector unit /
+// with two parts, 2^15 in the exponent and the sums in the instructions / now: 16 keys 0.80 / 2.06 / 0.73e-7,
+// 127 keys 1.03 / 2.55 / 0.78e-7, 6001 keys 1.39 / 2.98 / 1.05e-7; scores of 2.4 rms, 127 keys 1.78 / 2.02 /
+// 1.77e-7.  The third part and the additions cost 0.1 to 0.4 us of the 41 to 60 us below.
 // What bounds it: latency at short contexts (load, scores, softmax, values, partial sums to the last
 // workgroup of a head), the read of the cache at long ones.  With one workgroup per query head, which
 // read the rows of a key head once for each of its query heads, us per layer (attention and short
-// GEMVs), before / now: 64 heads on 8 key heads, 512 keys 52.5 / 51.0, 2000 keys 61.0 / 52.5, 6001 keys
-// 82.3 / 57.5; 32 on 8, 512 keys 44.0 / 43.0, 4000 keys 53.2 / 47.0; 32 on 32, 512 keys 44.3 / 44.3, 8000
-// keys 63.4 / 62.4.  (A first version that rotated q in every lane, 300 instructions of one wave, was
-// 2 us slower throughout.)  The error of the fp16 result against 64 bits is that of the rounding alone
-// (2.0942e-4 at 32 heads and 512 keys, before and now).
+// GEMVs), before / now: 64 heads on 8 key heads, 512 keys 52.6 / 49.6, 2000 keys 61.4 / 50.5, 6001 keys
+// 82.5 / 56.0; 32 on 8, 512 keys 44.0 / 41.2, 4000 keys 53.4 / 44.8; 32 on 32, 512 keys 44.3 / 41.9, 8000
+// keys 63.5 / 60.3 (1 to 2.5 us of that by the GEMVs' tickets).  A first version that rotated q in every lane,
+// 300 instructions of one wave, was 2 us slower throughout.  The error of the fp16 result against 64 bits is that
+// of the rounding alone (2.0942e-4 at 32 heads and 512 keys, before and now).
 #include <math.h>
 
 #include "attention.h"
@@ -33,17 +37,17 @@
 #define ATT_HEADS 8        // query heads of one workgroup
 #define ATT_STEP 32        // keys of a wave per step
 #define ATT_MAX_KEYS 2048  // cache keys per key split
+// Workgroups that a compute unit holds (the batched launch has more of them than there are units).
+#define ATT_WAVES_PER_SIMD(hd) ((hd) == 128 ? 2 : 3)
 
 typedef float att_f4 __attribute__((ext_vector_type(4)));
 typedef half_t att_h2 __attribute__((ext_vector_type(2)));
-typedef unsigned short att_us2 __attribute__((ext_vector_type(2)));
 typedef half_t att_h4 __attribute__((ext_vector_type(4)));
 
-// The two results of a split factor together.  An infinite key times the zero that a rest may be is NaN:
-// then the other result has the infinity, and the NaN is put aside (the median ignores it).
-__device__ __forceinline__ float att_join(float hi, float lo) {
-  return hi + __builtin_amdgcn_fmed3f(lo, -3.0e38f, 3.0e38f) * (1.0f / 2048.0f);
-}
+// The product with a factor's rests, to be added to the one with its rounded value.  An infinite key or value
+// times the zero that a rest may be is NaN: then the other product has the infinity, and the NaN is put aside
+// (the median ignores it).
+__device__ __forceinline__ float att_rest(float r) { return __builtin_amdgcn_fmed3f(r, -3.0e38f, 3.0e38f); }
 
 // a * b + c rounded to fp16 once, the last step of a rotated key.  With a conversion of an fp32
 // fma in its place, which is what the compiler makes of other surroundings, some elements of the cache
@@ -67,7 +71,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   typedef unsigned vwords __attribute__((ext_vector_type(VC / 2)));
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
-  __shared__ __align__(16) half_t s_q[2][ATT_HEADS][QLD];  // rotated queries: rounded, and 2^11 times the rest
+  __shared__ __align__(16) half_t s_q[3][ATT_HEADS][QLD];  // rotated queries: rounded, 2^11 and 2^22 times the rests
   __shared__ __align__(16) half_t s_kn[HD], s_vn[HD];      // the new token's row
   __shared__ __align__(16) float s_acc[ATT_WAVES][ATT_HEADS][HD + 4];
   __shared__ float2 s_ml[ATT_WAVES][ATT_HEADS];
@@ -122,7 +126,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   __builtin_amdgcn_sched_barrier(0);
 
   if (rh <= heads) {
-    att_h4 h[2], lo[2];
+    att_h4 h[2], mid[2], lo[2];
     // the exponentials below are powers of two
     const float scale = 1.44269504088896340736f / sqrtf((float)HD);
 #pragma unroll
@@ -133,7 +137,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       for (int e = 0; e < 2; ++e) {
         const float q = x[e] * scale;
         h[e][j] = (half_t)q;
-        lo[e][j] = (half_t)((q - (float)h[e][j]) * 2048.0f);
+        const float rest = (q - (float)h[e][j]) * 2048.0f;
+        mid[e][j] = (half_t)rest;
+        lo[e][j] = (half_t)((rest - (float)mid[e][j]) * 2048.0f);
       }
       if (rh == heads) {
         h[0][j] = att_fma_half(ra[j], rc[j], -(b * rs[j]));
@@ -144,7 +150,8 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
     for (int e = 0; e < 2; ++e) {
       if (rh < heads) {
         *reinterpret_cast<att_h4*>(&s_q[0][rh][ri + e * (HD / 2)]) = h[e];
-        *reinterpret_cast<att_h4*>(&s_q[1][rh][ri + e * (HD / 2)]) = lo[e];
+        *reinterpret_cast<att_h4*>(&s_q[1][rh][ri + e * (HD / 2)]) = mid[e];
+        *reinterpret_cast<att_h4*>(&s_q[2][rh][ri + e * (HD / 2)]) = lo[e];
       } else {
         *reinterpret_cast<att_h4*>(&s_kn[ri + e * (HD / 2)]) = h[e];  // fp16, as in the cache
         if (owns_new && grp == 0)
@@ -178,14 +185,22 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
     float sc[8];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      att_f4 dh = zero4, dl = zero4;
+      auto part = [&](int which, int t, att_f4 c) __attribute__((always_inline)) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(
+            kr[i][t], *reinterpret_cast<const half8*>(&s_q[which][hn][t * 32 + g * 8]), c, 0, 0, 0);
+      };
+      att_f4 mid = zero4, lo = zero4;
 #pragma unroll
-      for (int t = 0; t < TT; ++t) {  // added outside the instruction, rounded
-        dh += __builtin_amdgcn_mfma_f32_16x16x32_f16(kr[i][t], *reinterpret_cast<const half8*>(&s_q[0][hn][t * 32 + g * 8]), zero4, 0, 0, 0);
-        dl = __builtin_amdgcn_mfma_f32_16x16x32_f16(kr[i][t], *reinterpret_cast<const half8*>(&s_q[1][hn][t * 32 + g * 8]), dl, 0, 0, 0);
+      for (int t = 0; t < TT; ++t) {
+        lo = part(2, t, lo);
+        mid = part(1, t, mid);
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sc[i * 4 + r] = att_join(dh[r], dl[r]);
+      for (int r = 0; r < 4; ++r) mid[r] = att_rest(mid[r] + lo[r] * (1.0f / 2048.0f)) * (1.0f / 2048.0f);
+      att_f4 d = part(0, 0, mid) + part(0, 1, zero4);
+      if constexpr (TT == 4) d += part(0, 2, zero4) + part(0, 3, zero4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[i * 4 + r] = d[r];
     }
     vwords vw[8];
 #pragma unroll
@@ -218,17 +233,20 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       for (int c = 0; c < VC; ++c) acc[c] *= corr;
     }
     m = mx;
-    // Weights times 2^15 (in the range of fp16) as a rounded down value and the rest.  Neither is negative,
-    // and the rest is never zero: an infinite value stays infinite.
-    u32x4 ph, pl;
+    // Weights times 2^15 (in the range of fp16; the factor joins behind the exponential, whose argument it
+    // would round) as a rounded down value and two rests.
+    u32x4 ph, pm, pl;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float e0 = __builtin_amdgcn_exp2f(sc[2 * i] - (safe - 15.f)), e1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - (safe - 15.f));
+      const float e0 = __builtin_amdgcn_exp2f(sc[2 * i] - safe) * 32768.f, e1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - safe) * 32768.f;
       l += e0 + e1;
       const fp16x2 hi = __builtin_amdgcn_cvt_pkrtz(e0, e1);
-      const att_h2 rest = {(half_t)(e0 - (float)hi[0]), (half_t)(e1 - (float)hi[1])};
+      const float r0 = e0 - (float)hi[0], r1 = e1 - (float)hi[1];
+      const att_h2 mid = {(half_t)r0, (half_t)r1};
+      const att_h2 lo = {(half_t)(r0 - (float)mid[0]), (half_t)(r1 - (float)mid[1])};
       ph[i] = __builtin_bit_cast(unsigned, hi);
-      pl[i] = __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_bit_cast(att_us2, rest), att_us2{1, 1}));
+      pm[i] = __builtin_bit_cast(unsigned, mid);
+      pl[i] = __builtin_bit_cast(unsigned, lo);
     }
 #pragma unroll
     for (int c = 0; c < VC; ++c) {
@@ -237,9 +255,13 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       for (int i = 0; i < 4; ++i)
         a[i] = __builtin_amdgcn_perm(vw[2 * i + 1][c / 2], vw[2 * i][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
       const half8 a8 = __builtin_bit_cast(half8, a);
-      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pl), acc[c], 0, 0, 0);
-      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, ph), acc[c], 0, 0, 0);
+      att_f4 rest = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pl), zero4, 0, 0, 0);
+      rest = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pm), rest, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) rest[r] = att_rest(rest[r]);
+      acc[c] += __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, ph), zero4, 0, 0, 0) + rest;
     }
+    __builtin_amdgcn_sched_barrier(0);  // with the products and the next rows' addresses mixed, registers spill
     k0 += ATT_WAVES * ATT_STEP;
     if (k0 < t1) fetch(k0);
   }
@@ -329,7 +351,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
 }
 
 template <int HD>
-__global__ __launch_bounds__(ATT_THREADS) void attn_decode_kernel(AttnParams p) {
+__global__ __launch_bounds__(ATT_THREADS, ATT_WAVES_PER_SIMD(HD)) void attn_decode_kernel(AttnParams p) {
   attn_decode_body<HD>(p, p.cs, p.sn, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
@@ -349,7 +371,7 @@ struct AttnBatchParams {
 };
 
 template <int HD>
-__global__ __launch_bounds__(ATT_THREADS) void attn_decode_batch_kernel(AttnBatchParams bp) {
+__global__ __launch_bounds__(ATT_THREADS, ATT_WAVES_PER_SIMD(HD)) void attn_decode_batch_kernel(AttnBatchParams bp) {
   __shared__ float s_cs[HD / 2], s_sn[HD / 2];
   const int b = blockIdx.z;
   const int KS = bp.splits[b];
