@@ -43,10 +43,12 @@
 typedef float att_f4 __attribute__((ext_vector_type(4)));
 typedef half_t att_h2 __attribute__((ext_vector_type(2)));
 typedef half_t att_h4 __attribute__((ext_vector_type(4)));
+typedef unsigned short att_us2 __attribute__((ext_vector_type(2)));
 
 // The product with a factor's rests, to be added to the one with its rounded value.  An infinite key or value
 // times the zero that a rest may be is NaN: then the other product has the infinity, and the NaN is put aside
-// (the median ignores it).
+// (the median ignores it).  The rounded value is zero for a factor of zero only: one that would round to zero
+// takes the smallest fp16 of its sign, and the rests what that is too much.
 __device__ __forceinline__ float att_rest(float r) { return __builtin_amdgcn_fmed3f(r, -3.0e38f, 3.0e38f); }
 
 // a * b + c rounded to fp16 once, the last step of a rotated key.  With a conversion of an fp32
@@ -70,7 +72,6 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   typedef half_t vrow __attribute__((ext_vector_type(VC)));
   typedef unsigned vwords __attribute__((ext_vector_type(VC / 2)));
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  typedef __fp16 fp16x2 __attribute__((ext_vector_type(2)));
   __shared__ __align__(16) half_t s_q[3][ATT_HEADS][QLD];  // rotated queries: rounded, 2^11 and 2^22 times the rests
   __shared__ __align__(16) half_t s_kn[HD], s_vn[HD];      // the new token's row
   __shared__ __align__(16) float s_acc[ATT_WAVES][ATT_HEADS][HD + 4];
@@ -137,6 +138,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       for (int e = 0; e < 2; ++e) {
         const float q = x[e] * scale;
         h[e][j] = (half_t)q;
+        if (h[e][j] == (half_t)0 && q != 0.f) h[e][j] = (half_t)__builtin_copysignf(0x1p-24f, q);
         const float rest = (q - (float)h[e][j]) * 2048.0f;
         mid[e][j] = (half_t)rest;
         lo[e][j] = (half_t)((rest - (float)mid[e][j]) * 2048.0f);
@@ -240,7 +242,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
     for (int i = 0; i < 4; ++i) {
       const float e0 = __builtin_amdgcn_exp2f(sc[2 * i] - safe) * 32768.f, e1 = __builtin_amdgcn_exp2f(sc[2 * i + 1] - safe) * 32768.f;
       l += e0 + e1;
-      const fp16x2 hi = __builtin_amdgcn_cvt_pkrtz(e0, e1);
+      // no zero for a weight that is not: with the bits of a float or 1, whichever is less
+      const att_us2 some = {(unsigned short)min(__builtin_bit_cast(unsigned, e0), 1u), (unsigned short)min(__builtin_bit_cast(unsigned, e1), 1u)};
+      const att_h2 hi = __builtin_bit_cast(att_h2, __builtin_elementwise_max(__builtin_bit_cast(att_us2, __builtin_amdgcn_cvt_pkrtz(e0, e1)), some));
       const float r0 = e0 - (float)hi[0], r1 = e1 - (float)hi[1];
       const att_h2 mid = {(half_t)r0, (half_t)r1};
       const att_h2 lo = {(half_t)(r0 - (float)mid[0]), (half_t)(r1 - (float)mid[1])};

@@ -19,13 +19,15 @@ def _run(ctx, heads, kv_heads, hd, K, V, kv_len, splits=0):
     return attn, lambda: O.attention_decode(O.rope(q, kv_len, 10000.0), Kr, Vr, kv_len + 1).reshape(-1)
 
 
-def _run_parts(ctx, heads, kv_heads, hd, K, V, kv_len, splits=0, q_scale=0.3, seed=0):
+def _run_parts(ctx, heads, kv_heads, hd, K, V, kv_len, splits=0, q_scale=0.3, seed=0, edit=None):
     shape = S.ModelShape("attention", 1, 64, heads, kv_heads, hd, 64)
     rng = np.random.default_rng(heads * 1000 + kv_heads * 10 + kv_len + 7 * seed)
     w = S.layer_weights(3, shape, 0)
     for m in ("Wq", "Wk", "Wv"):
         w[m] = (rng.standard_normal(w[m].shape) * q_scale).astype(np.float16)
     h = rng.standard_normal(64).astype(np.float16)
+    if edit is not None:
+        edit(w, h)
     st = M.DeviceStack(ctx, shape, [M.DeviceLayer(ctx, shape, w)], [(K.copy(), V.copy())], K.shape[1])
     hin = to_dev(h)
     out = to_dev(np.zeros_like(h))
@@ -146,3 +148,44 @@ def test_results_before_rounding_carry_fp32(ctx, heads, kv_heads, hd, kv_len, sp
         err.append(np.linalg.norm(got - exact) / np.linalg.norm(exact))
         plain.append(np.linalg.norm(attend(np.float32) - exact) / np.linalg.norm(exact))
     assert np.mean(err) <= 1.3 * np.mean(plain), (np.mean(err), np.mean(plain))
+
+
+@pytest.mark.parametrize("splits", [1, 4])
+@pytest.mark.parametrize("score,result", [(-25.0, np.inf), (-40.0, np.inf), (-70.0, np.inf), (-200.0, np.nan)])
+def test_infinite_value_of_a_small_weight(ctx, splits, score, result):
+    """However small the weight, an infinite value times it is infinite; times a weight of zero (e^-200 in fp32)
+    it is NaN.  The other dimensions do not see it."""
+    heads, hd, kv_len = 2, 128, 200
+    K, V = _cache(heads, kv_len + 1, hd, kv_len, 6)
+    K[:, :kv_len] = 0
+    plain, q, _, _ = _run_parts(ctx, heads, heads, hd, K, V, kv_len, splits)
+    x = O.rope(q, kv_len, 10000.0)[0]
+    K[0, 77] = x * (score * np.sqrt(hd) / np.dot(x, x))
+    plain, _, _, _ = _run_parts(ctx, heads, heads, hd, K, V, kv_len, splits)
+    V[0, 77, 9] = np.inf
+    got, _, _, _ = _run_parts(ctx, heads, heads, hd, K, V, kv_len, splits)
+    assert np.array_equal(got[9: 10], np.array([result], np.float16), equal_nan=True)
+    keep = np.arange(heads * hd) != 9
+    assert np.array_equal(got[keep], plain[keep])
+
+
+@pytest.mark.parametrize("splits", [1, 4])
+def test_infinite_key_behind_a_small_query(ctx, splits):
+    """A query component far below the smallest fp16, times an infinite key: the score is infinite and not NaN,
+    so the key with -inf has no weight and nothing else changes."""
+    heads, hd, kv_len = 2, 128, 200
+
+    def small(w, h):  # component 3 of head 1 is two or three of the smallest fp16, its partner zero
+        w["Wq"][hd + 3] = 0
+        w["Wq"][hd + 3 + hd // 2] = 0
+        w["Wq"][hd + 3, np.argmax(np.abs(h))] = 2.0 ** -24
+
+    K, V = _cache(heads, kv_len + 1, hd, kv_len, 7)
+    _, q, _, _ = _run_parts(ctx, heads, heads, hd, K, V, kv_len, splits, edit=small)
+    x = O.rope(q, kv_len, 10000.0)[1, 3]
+    assert 0 < abs(x) / np.sqrt(hd) * np.log2(np.e) < 2.0 ** -25
+    K[1, 50, 3] = -np.sign(x) * np.inf
+    got, q, Kr, Vr = _run_parts(ctx, heads, heads, hd, K, V, kv_len, splits, edit=small)
+    ref = O.attention_decode(O.rope(q, kv_len, 10000.0), Kr, Vr, kv_len + 1).reshape(-1)
+    assert np.all(np.isfinite(got.astype(np.float32)))
+    assert O.rel_err(got, O.round_f16(ref)) <= 2e-3
