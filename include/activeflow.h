@@ -78,7 +78,7 @@ const char* af_strerror(int status);
  * detected in validate mode; the GEMV then adds a repeated row twice.
  * AF_OPT_TUNE_*: launch-shape overrides for tuning sweeps, 0 = the built-in choice: lanes across
  * a tile (16, 32, 64), waves per workgroup (4, 8, 16), splits of the row list, workgroups
- * aimed at; AF_OPT_TUNE_ATTN_SPLITS: key splits of the attention launch (0 = one per 64 keys);
+ * aimed at; AF_OPT_TUNE_ATTN_SPLITS: key splits of the attention launch of one token (0 = the built-in choice);
  * AF_OPT_TUNE_EARLY_ROWS: fp16 top-k launches that request weight rows before their selection has
  * run: 0 = where the built-in rule expects a gain, 1 = none, 2 = all of them (a top-k launch that
  * cannot is refused with AF_EINVAL).

@@ -408,7 +408,8 @@ static int attn_groups(const af_layer_cfg* cfg) {  // workgroups side by side: k
 //   32/32, 512: 45.2 / 44.1 / 45.3 / 49.8      40/40, 512: 48.5 / 48.0 / 51.4 / 55.5, at 6 splits 47.4
 //   64/8, 2000: 58.9 / 54.1 / 52.3 / 53.9      64/8, 6001: 76.0 / 64.3 / 57.5 / 57.2
 // Where that leaves more than 512 keys to a split, twice as many (32/32, 8000: 8 splits 64.9, 16 62.4).
-static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, size_t floats) {
+// `tuned`: the number asked for by option (0: none).  The option is the single-token launch's.
+static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, size_t floats, int tuned) {
   int KS = (kv_len + 63) / 64;
   int cap = ctx->n_cu / attn_groups(cfg);
   if (cap > 16) cap = 16;
@@ -416,7 +417,7 @@ static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, s
   if (kv_len > 512 * cap) cap *= 2;
   if (KS > cap) KS = cap;
   if (KS < (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS) KS = (kv_len + ATT_MAX_KEYS - 1) / ATT_MAX_KEYS;  // very long caches
-  if (ctx->tune_attn_splits > 0) KS = ctx->tune_attn_splits;
+  if (tuned > 0) KS = tuned;
   if (KS < 1) KS = 1;
   if (KS > 64) KS = 64;
   while (KS > 1 && (size_t)cfg->n_heads * KS * (cfg->head_dim + 2) > floats) --KS;
@@ -425,7 +426,7 @@ static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, s
 
 int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv, void* kc, void* vc,
                         int kv_len, int kv_cap, int pos, half_t* out) {
-  const int KS = attn_splits(ctx, cfg, kv_len, ctx->lay.attn_floats);
+  const int KS = attn_splits(ctx, cfg, kv_len, ctx->lay.attn_floats, ctx->tune_attn_splits);
   if (KS == 0) return AF_EINVAL;
   AttnParams p;
   p.qkv = qkv;
@@ -463,7 +464,7 @@ int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const
   int ks_max = 1;
   const size_t per_split = (size_t)cfg->n_heads * (cfg->head_dim + 2);
   for (int b = 0; b < B; ++b) {
-    const int KS = attn_splits(ctx, cfg, kv_len[b], ctx->lay.attn_floats / B);
+    const int KS = attn_splits(ctx, cfg, kv_len[b], ctx->lay.attn_floats / B, 0);
     if (KS == 0) return AF_EINVAL;
     bp.splits[b] = KS;
     if (KS > ks_max) ks_max = KS;

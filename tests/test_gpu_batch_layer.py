@@ -157,6 +157,22 @@ def test_batch_layer_rejects_what_it_cannot_run(ctx):
         _run_batch(ctx, shape, w, H, caches, [4, 5], 32, M.select_cfg(B.AF_SEL_TOPK, ks, reuse_mask=1))
 
 
+def test_batch_layer_has_its_own_key_splits(ctx):
+    """The option that sets the single-token launch's key splits (one split holds 2048 keys at most) neither
+    refuses nor changes a batch."""
+    shape = S.MODEL_SHAPES["tiny_gqa"]
+    kv_cap, kv_lens = 2120, [2100, 40]
+    w, H, caches = _inputs(shape, 2, kv_cap, kv_lens)
+    sel = M.select_cfg(B.AF_SEL_TOPK, tuple(O.keep_count(n, 50) for n in _widths(shape)))
+    plain = _run_batch(ctx, shape, w, H, caches, kv_lens, kv_cap, sel)[0]
+    ctx.set_option(B.AF_OPT_TUNE_ATTN_SPLITS, 1)
+    try:
+        tuned = _run_batch(ctx, shape, w, H, caches, kv_lens, kv_cap, sel)[0]
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_ATTN_SPLITS, 0)
+    assert np.array_equal(plain, tuned)
+
+
 @pytest.mark.parametrize("Bt", [4])
 def test_batch_layer_70b_shape(ctx, Bt):
     """BASELINE config 4 as a whole layer: 70B shape (64 query / 8 key-value heads), B tokens, each
