@@ -303,10 +303,18 @@ int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
   // Tile width: narrow outputs fill the chip with 128 columns and few splits (8192 -> 8192, eight
   // tokens: 35.9 us with 128 columns and 4 splits, 38.4 with 256 and 8; 11008 -> 4096 29.4 / 31.0);
   // from there on longer pieces of a row count for more (8192 -> 10240 41.4 / 41.2, 8192 -> 57344
-  // 164.7 / 147.1; 512 columns 151.9).
+  // 164.7 / 147.1; 512 columns 151.9).  512 columns where the 256-column tiles leave compute units without
+  // one and the wider ones fill a third more (129 to 170 tiles of 256; us for 1 / 4 / 8 tokens on the vector unit,
+  // 256 and 512 columns): 8192 -> 33024 56.5 / 101.1 / 111.6, 61.2 / 107.0 / 114.9 and 50.9 / 87.6 / 94.8;
+  // 4096 -> 40960 38.4 / 69.0 / 75.9, 36.4 / 60.1 / 64.9 and 34.8 / 57.5 / 64.0.  On the other side of the line
+  // 4096 -> 24576 (192 and 240 workgroups) 29.2 / 49.1 / 54.7, 25.7 / 39.7 / 43.5 and 25.3 / 39.6 / 44.8, and with
+  // as many of either 8192 -> 49152 77.1 / 139.7 / 144.9, 70.0 / 121.1 / 129.5 and 70.0 / 122.9 / 133.8.
   int cw = out <= 8192 ? 1 : 2;
+  auto workgroups = [&](int width) { const int t = (out + width - 1) / width; return t >= ctx->n_cu ? t : ctx->n_cu / t * t; };
+  if (cw == 2 && workgroups(512) <= ctx->n_cu && 3 * workgroups(512) >= 4 * workgroups(256)) cw = 4;
   if (ctx->tune_lx == 16) cw = 1;
   if (ctx->tune_lx == 32) cw = 2;
+  if (ctx->tune_lx == 64) cw = 4;
   const int tw = cw * 128;
   const int tiles = (out + tw - 1) / tw;
   const int out_pad = tiles * tw;
@@ -339,6 +347,8 @@ int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
   dim3 grid(tiles, S);
   if (cw == 1)
     hipLaunchKernelGGL(gemv_union_kernel<1>, grid, dim3(UG_THREADS), 0, ctx->stream, p);
+  else if (cw == 4)
+    hipLaunchKernelGGL(gemv_union_kernel<4>, grid, dim3(UG_THREADS), 0, ctx->stream, p);
   else
     hipLaunchKernelGGL(gemv_union_kernel<2>, grid, dim3(UG_THREADS), 0, ctx->stream, p);
   AF_LAUNCH_CHECK();

@@ -217,6 +217,7 @@ def test_union_70b_shapes_sampled(ctx, name, out, n, Bt):
     (8200, 300, 257, 0, 1.0),    # 256-column tiles, the last one of 8 columns
     (264, 4400, 2049, 1, 1.0),   # more rows than are staged at a time
     (520, 600, 300, 3, 2.0 ** -15),  # most weights below the smallest normal fp16
+    (33032, 100, 70, 0, 1.0),    # 512-column tiles, the last one of 264 columns, several splits
 ])
 def test_union_steps_and_tiles(ctx, tokens, out, n, k, split, scale):
     """Edges of the matrix-instruction kernel: row lists around its steps of 32 rows and its staging
