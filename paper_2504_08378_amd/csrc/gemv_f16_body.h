@@ -621,11 +621,15 @@ constexpr int gemv_early_cap(int lx) { return (lx == 16 ? 4 : 8) * AF_WAVE / lx;
 // Which of them: inputs of up to 4096, 16384 and AF_MAX_N channels.
 static inline int gemv_width_class(int n) { return n <= RP_EV * 1024 ? 0 : (n <= 4 * RP_EV * 1024 ? 1 : 2); }
 // ... and whether at all: not where early rows cost more than they hide.  The look for the rows is
-// 0.5-1 us of front end.  Up to 4096 channels it pays from a stream of 160 KB a workgroup on (us
-// without / with, index list written; 50 % unless stated):
-//   2048 -> 12288 (128 KB) 10.54 / 11.59    4096 -> 4096 (85 KB) 9.89 / 10.41    2048 -> 16384 (170 KB) 12.31 / 12.37
-//   4096 -> 8192 (170 KB) 12.61 / 12.19     4096 -> 12288 (256 KB) 15.24 / 14.35, at 80 % (102 KB) 10.75 / 12.01
-//   3072 -> 12288 (192 KB) 13.00 / 12.63    4096 -> 22016 (512 KB) 22.13 / 21.68, at 80 % (205 KB) 14.68 / 14.84
+// 0.5-1 us of front end.  Up to 4096 channels it pays from a stream of 100, 132 and 150 KB a workgroup on, by
+// the width of the tile (us without / with, index list written; 50 % unless stated):
+//   128 columns: 4096 -> 4096 (85 KB) 10.45 / 10.67         2048 -> 6144 at 30 % (90 KB) 10.10 / 10.32
+//                4096 -> 6144 (102 KB) 11.57 / 11.40        4096 -> 6144 at 30 % (143 KB) 13.62 / 12.70
+//   256 columns: 2048 -> 12288 (102 KB) 10.71 / 11.23       4096 -> 8192 (128 KB) 12.44 / 12.96, behind SiLU 12.18 / 12.45
+//                3072 -> 8192 at 30 % (134 KB) 12.38 / 11.86    2048 -> 12288 at 30 % (143 KB) 12.67 / 11.96
+//                4096 -> 6400 at 30 % (143 KB) 13.61 / 12.46    3072 -> 12288 (154 KB) 13.22 / 12.34
+//   512 columns: 4096 -> 14336 at 80 % (136 KB) 11.38 / 11.85   3072 -> 14336 at 70 % (153 KB) 12.00 / 11.67
+//                3072 -> 22016 at 80 % (153 KB) 11.98 / 12.03   4096 -> 22016 (409 KB) 21.28 / 19.69
 // Wider inputs have a longer front end to hide behind: from 48 KB on, or from 72 KB where few
 // channels are kept and so less than 48 KB can be taken early,
 //   10672 -> 920 (55 KB) 12.82 / 12.36      12632 -> 616 at 30 % (58 KB) 15.33 / 14.36    14456 -> 1536 at 70 % (67 KB) 13.83 / 12.89
@@ -634,14 +638,15 @@ static inline int gemv_width_class(int n) { return n <= RP_EV * 1024 ? 0 : (n <=
 // 64 only, so what is taken has to be worth it: 1 KB for the workgroup to 6 of a wave's channels, to
 // 3.5 behind the SiLU producer (channels : KB; * SiLU):
 //   17856 -> 3408 at 80 % (124 : 36) 18.91 / 16.87    28304 -> 3152 at 80 % (177 : 36) 23.50 / 21.87
-//   19888 -> 6472 at 90 % (178 : 32) 19.36 / 18.80    28672 -> 8192 at 90 % (298 : 32) 24.11 / 24.46
+//   19888 -> 6472 at 90 % (138 : 32) 18.05 / 17.29    28672 -> 8192 at 90 % (224 : 32) 22.43 / 21.66
 //   *11008 -> 6144 (137 : 64) 21.42 / 20.10           *28672 -> 4096 (224 : 64) 34.30 / 34.06
-//   *28672 -> 6144 (358 : 64) 44.74 / 45.77           *28672 -> 10240 at 80 % (298 : 72) 35.23 / 35.98
+//   *28672 -> 6144 (358 : 64) 44.74 / 45.77           *28672 -> 10240 at 80 % (299 : 72) 32.53 / 31.92
 static inline int gemv_early_class(int pro, int n, int k, int S, int lx) {
   const long long row = lx * 16, bytes = k / S * row;
   const int share = (int)((long long)k * 48 / n), cap = gemv_early_cap(lx);
   const long long early = (share < cap ? share : cap) * 16 * row;  // taken by the workgroup's waves
-  const bool pays = n <= 4096 ? bytes >= 160 * 1024
+  const int line = lx == 16 ? 100 : (lx == 32 ? 132 : 150);
+  const bool pays = n <= 4096 ? bytes >= line * 1024
                               : bytes >= (early >= 48 * 1024 ? 48 : 72) * 1024 &&
                                     n / S / 16 * 2 * 1024 <= (pro == AF_PRO_SILUMUL ? 7 : 12) * early;
   return pays ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
