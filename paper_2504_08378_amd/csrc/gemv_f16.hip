@@ -26,7 +26,7 @@
 
 // Tile width, waves per workgroup and split count for a shape.  The AF_OPT_TUNE_* options of
 // the context override the heuristic (tuning sweeps).
-static void choose_config(const af_ctx* ctx, int out, int nidx, bool selects, bool whole_layer,
+static void choose_config(const af_ctx* ctx, int n, int out, int nidx, int sel, bool selects, bool whole_layer,
                           int* lx_out, int* nw_out, int* s_out) {
   // A kernel that selects for itself (or builds its input vector) repeats that work in every
   // workgroup, so it runs few, large workgroups (one 1024-thread workgroup per CU); a plain
@@ -37,14 +37,23 @@ static void choose_config(const af_ctx* ctx, int out, int nidx, bool selects, bo
   //  * tile width: 128 columns up to ~6K output columns, 256 up to ~12K, 512 beyond (within
   //    1-2 % of the best of the three for every operator);
   //  * splits: between three quarters of the CUs and all of them, the most that leave every
-  //    workgroup 320 rows (128-column tiles) or 190 rows (wider tiles); below that a workgroup
+  //    workgroup 320 rows (128-column tiles), 190 rows (wider tiles), or 300 (256-column tiles whose rows are
+  //    given, which have no selection to repeat but wait on x with them); below that a workgroup
   //    is mostly front end and reduction.  13B: o 13.1 against 14.6 us, down 24.4 against 26.4 us for
   //    240 against 160 workgroups; 70B down 54.9 against 58.9 us; Mixtral gate|up of two experts 43
   //    against 53 us (224 against 112 workgroups).  With the tiles' tickets in cache lines of their own
   //    more splits cost little (us at 500 rows a workgroup / 190): 4096 -> 22016 at 50 % 19.33 / 18.98,
   //    thresholds 18.14 / 17.27; 4096 -> 12288 at 70 % 12.19 / 11.66; 5120 -> 15360 at 50 % 18.15 / 17.15, at
   //    70 % 14.30 / 13.54; 8192 -> 8192 at 70 % 13.29 / 12.43; 13B step with reuse 3.475 / 3.442 ms, 7B
-  //    2.227 / 2.210.
+  //    2.227 / 2.210.  Given rows behind the norm, with the most splits that leave 190 / 300: 2048 -> 8192
+  //    11.75 / 10.98, 2304 -> 8192 12.07 / 11.51, 2048 -> 8704 11.66 / 11.11, but 2048 -> 6400 9.67 / 10.26 (500
+  //    rows, before the tickets had lines of their own: 11.02, 11.95, 11.34 and 10.78);
+  //  * a wave looks for the obvious rows of its selection among the first 64 of its channels.  256-column launches of
+  //    more than 4096 channels and fewer than 300 rows a workgroup, which are little more than those rows, take the
+  //    splits with which a wave has 64, where the rules above leave that open (at 70 %, without / with):
+  //    5120 -> 9216 12.66 / 12.01, 6144 -> 8192 12.62 / 12.27, 8192 -> 6400 13.36 / 12.86, behind SiLU 12.62 / 12.72.
+  //    With more rows more splits are better (5120 -> 9216 at 50 %, 7 and 5 splits: 13.67 / 14.62), and without early
+  //    rows (4096 -> 10240 at 70 %, 6 and 4: 11.26 / 12.13).
   // Plain launches: 128-column tiles up to 16K columns and 512 beyond; with 256-column tiles on
   // a row stride that is a multiple of 1 KB every workgroup stays on one value of address bit 9
   // for all its rows, and the half of the workgroups on one of the two values finished ~2 us
@@ -65,9 +74,11 @@ static void choose_config(const af_ctx* ctx, int out, int nidx, bool selects, bo
     int s_min = ctx->n_cu * 3 / 4 / tiles;
     if (s_min < 1) s_min = 1;
     if (tiles * s_min < ctx->n_cu * 6 / 10 && tiles * (s_min + 1) <= ctx->n_cu) ++s_min;
-    const int rows_min = lx == 16 ? 320 : 190;
+    const int rows_min = lx == 16 ? 320 : (lx == 32 && sel == AF_ROWS_GIVEN ? 300 : 190);
     while (S > s_min && nidx / S < rows_min) --S;
     if (S < s_min) S = s_min;
+    const int s64 = (n + 1023) / 1024;
+    if (sel == AF_SEL_TOPK && lx == 32 && n > 4096 && nidx / S < 300 && s64 >= s_min && s64 < S) S = s64;
   }
   if (ctx->tune_split > 0) S = ctx->tune_split;
   const int min_rows = 32;  // a split shorter than this is mostly reduction overhead
@@ -169,7 +180,7 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   // inside the whole-layer kernel every operator runs on the kernel's 1024-thread workgroups,
   // one per compute unit
   // a threshold keeps an unknown number of rows: plan the launch for half of them
-  choose_config(ctx, a.out, r.sel == AF_SEL_THRESHOLD ? (r.n + 1) / 2 : max_rows,
+  choose_config(ctx, r.n, a.out, r.sel == AF_SEL_THRESHOLD ? (r.n + 1) / 2 : max_rows, r.sel,
                 whole_layer || r.sel != AF_ROWS_GIVEN || r.pro != AF_PRO_NONE, whole_layer, &lx, &nw, &S);
   const int tw = lx * 8;
   // output slots (one per device-selected matrix; a single one otherwise), whole tiles each
