@@ -79,9 +79,9 @@ const char* af_strerror(int status);
  * AF_OPT_TUNE_*: launch-shape overrides for tuning sweeps, 0 = the built-in choice: lanes across
  * a tile (16, 32, 64), waves per workgroup (4, 8, 16), splits of the row list, workgroups
  * aimed at; AF_OPT_TUNE_ATTN_SPLITS: key splits of the attention launch of one token (0 = the built-in choice);
- * AF_OPT_TUNE_EARLY_ROWS: fp16 top-k launches that request weight rows before their selection has
- * run: 0 = where the built-in rule expects a gain, 1 = none, 2 = all of them (a top-k launch that
- * cannot is refused with AF_EINVAL).
+ * AF_OPT_TUNE_EARLY_ROWS: fp16 launches that request weight rows before their selection has
+ * run (top-k), or before their input is built (rows given): 0 = where the built-in rule expects a gain,
+ * 1 = none, 2 = all of them that can (a top-k launch that cannot is refused with AF_EINVAL).
  * AF_OPT_MOE_ROUTER_KERNEL: 1 runs the router of af_decode_moe_layer as a launch of
  * its own instead of inside the gate|up launch. */
 enum {

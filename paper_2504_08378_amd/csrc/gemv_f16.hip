@@ -255,9 +255,11 @@ int af_plan_gemv_f16(af_ctx* ctx, const af_gemv_args& a, bool whole_layer, GemvP
   plan->nw = nw;
   plan->early = early;
   if (range_sel && nw == 16 && !whole_layer && !a.router_Wr) plan->early = gemv_range_class(r.n, S);
-  // Given rows: their number has to be known here.
+  // Given rows: their number has to be known here.  (The option forces or forbids it as it does early rows.)
   if (r.sel == AF_ROWS_GIVEN && r.pro != AF_PRO_NONE && r.nidx_dev == nullptr && nw == 16 && !whole_layer && !a.router_Wr && !a.pair)
-    plan->early = gemv_given_class(r.n, r.nidx_host, S, lx);
+    plan->early = ctx->tune_early_rows == 1   ? (int)GEMV_EARLY_NONE
+                  : ctx->tune_early_rows == 2 ? gemv_width_class(r.n)
+                                              : gemv_given_class(r.pro, r.idx == nullptr, r.n, r.nidx_host, S, lx);
   if (early != GEMV_EARLY_NONE) p.early_cycles = af_dealt_cycles(r.n, S);
   plan->lds = xs_bytes + (size_t)list_cap * 4;
   return AF_OK;

@@ -651,15 +651,22 @@ static inline int gemv_early_class(int pro, int n, int k, int S, int lx) {
                                     n / S / 16 * 2 * 1024 <= (pro == AF_PRO_SILUMUL ? 7 : 12) * early;
   return pays ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
 }
-// Given rows ahead of x.  The list has to be in registers first, which the plain form fetches in the shadow of
+// Given rows ahead of x.  A list has to be in registers first, which the plain form fetches in the shadow of
 // the norm; that costs short streams more than the rows' head start gives (us per layer, three of four
 // layers reusing two of four lists, plain / ahead; KB of rows per workgroup in q|k|v and gate|up):
-//   4096 channels: 105, 205 KB 51.4 / 52.0    262, 524 KB 67.3 / 67.5    367, 734 KB 78.8 / 77.9
-//   5120: 171, 256 KB 62.4 / 61.8    427, 640 KB 86.3 / 85.3      8192: 341, 2048 KB 168.0 / 166.5
-//   512 channels, 16 KB 34.6 / 36.1
-static inline int gemv_given_class(int n, int nidx, int S, int lx) {
+//   4096 channels, tiles of 256 and 512 columns: 102, 205 KB 51.6 / 52.1    205, 409 KB 67.9 / 67.2    286, 573 KB 78.9 / 78.1
+//   3072, 128 and 512: 90, 268 KB 57.3 / 57.4    2048, 128 and 256: 45, 179 KB 45.6 / 46.3    512, 128: 4, 8 KB 34.4 / 36.1
+//   5120: 170, 256 KB 61.1 / 60.4    320, 640 KB 86.2 / 84.8      8192: 341, 2048 KB 168.6 / 167.4
+// All rows (no list): 2048 -> 8192 (128 KB) 11.74 / 11.46 but 2048 -> 7936 (127 KB) 10.59 / 10.77, 3072 -> 6400 (154 KB)
+// 12.16 / 11.96, 2048 -> 10240 (170 KB) 12.02 / 11.71; 512 columns: 1024 -> 16384 (170 KB) 10.71 / 10.69, 2048 -> 14336
+// (227 KB) 14.36 / 13.73; 128 columns: 4096 -> 4096 (128 KB) 11.69 / 11.66, behind SiLU 11.27 / 11.52; 256, behind SiLU:
+// 4096 -> 6400 (204 KB) 13.47 / 13.38.  Behind SiLU, beyond 24576 channels, both halves of the source fill the registers:
+// 24000 -> 4096 36.67 / 36.45, 25000 -> 4096 38.20 / 38.32, 28672 -> 5120 52.9 / 53.6.
+static inline int gemv_given_class(int pro, bool dense, int n, int nidx, int S, int lx) {
   const long long bytes = (long long)(nidx / S) * lx * 16;
-  return bytes >= (n <= RP_EV * 1024 ? 320 : 160) * 1024 ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
+  if (pro == AF_PRO_SILUMUL && n > 24576) return GEMV_EARLY_NONE;
+  const int narrow = lx == 16 || (lx == 64 && !dense) ? 320 : (lx == 32 && dense && pro == AF_PRO_RMSNORM ? 150 : 200);
+  return bytes >= (n <= RP_EV * 1024 ? narrow : 160) * 1024 ? gemv_width_class(n) : (int)GEMV_EARLY_NONE;
 }
 static_assert(8 * RP_EV * 1024 >= AF_MAX_N, "the widest input fits the largest class");
 

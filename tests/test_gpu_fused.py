@@ -569,3 +569,49 @@ def test_given_rows_ahead_of_x(ctx, n, out, split, producer):
     finally:
         ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
     assert O.rel_err(to_host(y), O.sparse_gemv(W, to_host(xo), np.arange(n))) <= 1e-4
+
+
+@pytest.mark.parametrize("producer", [B.AF_PRO_RMSNORM, B.AF_PRO_SILUMUL])
+@pytest.mark.parametrize("lx", [16, 32, 64])
+@pytest.mark.parametrize("n,out,split", [(8, 8, 1), (136, 264, 1), (504, 136, 3), (520, 520, 1), (1032, 1032, 2), (5000, 264, 40)])
+def test_few_given_rows_ahead_of_x(ctx, n, out, split, lx, producer):
+    """The same where the rule would not: workgroups with fewer rows than are requested ahead, or a few more."""
+    W, h = _wx(out, n, n + out)
+    src = np.concatenate([h, h[::-1]]) if producer == B.AF_PRO_SILUMUL else h
+    gain = to_dev(S.norm_gain(3, n, "given")) if producer == B.AF_PRO_RMSNORM else None
+    xo = torch.zeros(n, dtype=torch.float16, device="cuda")
+    Wt, srcd = ctx.pack_inmajor_f16(to_dev(W)), to_dev(src)
+    ctx.set_option(B.AF_OPT_TUNE_SPLIT, split)
+    ctx.set_option(B.AF_OPT_TUNE_LX, lx)
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 2)
+    try:
+        y = ctx.select_gemv_f16(Wt, srcd, producer=producer, gain=gain, x_out=xo, sel_mode=B.AF_SEL_DENSE, y_kind=B.AF_F32)
+        ctx.synchronize()
+    finally:
+        for opt in (B.AF_OPT_TUNE_SPLIT, B.AF_OPT_TUNE_LX, B.AF_OPT_TUNE_EARLY_ROWS):
+            ctx.set_option(opt, 0)
+    assert O.rel_err(to_host(y), O.sparse_gemv(W, to_host(xo), np.arange(n))) <= 1e-4
+
+
+@pytest.mark.parametrize("lx", [16, 64])
+def test_given_rows_ahead_of_x_of_matrices_picked_on_the_device(ctx, lx):
+    """Two output slots, each with the matrix that a device array names."""
+    n, out, picked = 1032, 264, (2, 0)
+    cases = [_wx(out, n, 50 + e) for e in range(3)]
+    bank = torch.stack([ctx.pack_inmajor_f16(to_dev(W)) for W, _ in cases])
+    x = cases[0][1]
+    xo = torch.zeros(n, dtype=torch.float16, device="cuda")
+    gain, srcd = to_dev(S.norm_gain(3, n, "given")), to_dev(x)
+    sel = torch.tensor(picked, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    ctx.set_option(B.AF_OPT_TUNE_LX, lx)
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 2)
+    try:
+        y = ctx.select_gemv_experts_f16(bank, sel, 2, srcd, B.AF_PRO_RMSNORM, gain=gain, x_out=xo, sel_mode=B.AF_SEL_DENSE,
+                                        y_kind=B.AF_F32)
+        ctx.synchronize()
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_LX, 0)
+        ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 0)
+    ref = np.concatenate([O.sparse_gemv(cases[e][0], to_host(xo), np.arange(n)) for e in picked])
+    assert O.rel_err(to_host(y).reshape(-1), ref) <= 1e-4

@@ -618,11 +618,13 @@ def test_random_layer_shapes_stage_by_stage(ctx, i, d, nh, n_kv, hd, f, kv_len, 
     assert max(errs.values()) <= TOL, errs
 
 
-@pytest.mark.parametrize("count", [0, 1, 63, 64, 65, 1500, 4600])
+@pytest.mark.parametrize("lx", [16, 32, 64])
+@pytest.mark.parametrize("count", [0, 1, 63, 64, 65, 255, 258, 511, 514, 1023, 1026, 1500, 4600])
 @pytest.mark.parametrize("bad", [False, True])
-def test_reused_lists_requested_ahead_of_the_norm(ctx, count, bad):
-    """A reused list's first rows are requested before x exists: short lists, lists longer than a staging pass,
-    and an entry out of range, which adds nothing and is reported."""
+def test_reused_lists_requested_ahead_of_the_norm(ctx, count, bad, lx):
+    """A reused list's first rows (512, 256 or 128 of a workgroup's, by the tile's width) are requested before x
+    exists, here whatever the built-in rule says: lists that end within them, at their end and behind it,
+    lists longer than a staging pass, and an entry out of range, which adds nothing and is reported."""
     if bad and count == 0:
         pytest.skip("no entry to break")
     shape = S.ModelShape("given", 1, 4608, 2, 1, 64, 64)
@@ -639,12 +641,15 @@ def test_reused_lists_requested_ahead_of_the_norm(ctx, count, bad):
     ks = (count, 128, count, 64)
     st.sets[0].load([sent, None, sent, None])
     ctx.set_option(B.AF_OPT_TUNE_SPLIT, 2)
+    ctx.set_option(B.AF_OPT_TUNE_LX, lx)
+    ctx.set_option(B.AF_OPT_TUNE_EARLY_ROWS, 2)
     try:
         hin = to_dev(h); hout = torch.zeros_like(hin)
         st.layer(0, hin, hout, 4, 4, M.select_cfg(B.AF_SEL_TOPK, ks, reuse_mask=0b0101))
         ctx.synchronize()
     finally:
-        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+        for opt in (B.AF_OPT_TUNE_SPLIT, B.AF_OPT_TUNE_LX, B.AF_OPT_TUNE_EARLY_ROWS):
+            ctx.set_option(opt, 0)
     assert ctx.last_device_error() == (B.AF_DEVERR_IDX if bad else 0)
     t = _taps(ctx, shape)
     for x, y, names in (("x_qkv", "qkv", ("Wq", "Wk", "Wv")), ("x_gateup", "gateup", ("Wgate", "Wup"))):
