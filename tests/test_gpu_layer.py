@@ -655,3 +655,38 @@ def test_reused_lists_requested_ahead_of_the_norm(ctx, count, bad, lx):
     for x, y, names in (("x_qkv", "qkv", ("Wq", "Wk", "Wv")), ("x_gateup", "gateup", ("Wgate", "Wup"))):
         ref = np.concatenate([O.sparse_gemv(w[m], t[x], idx) for m in names])
         assert O.rel_err(t[y], O.round_f16(ref)) <= TOL if len(idx) else not np.any(t[y]), y
+
+
+@pytest.mark.parametrize("kind", [B.AF_W_Q4G32, B.AF_W_Q4CL])
+@pytest.mark.parametrize("d,nh,f", [
+    (1024, 2, 64), (1056, 2, 64), (2048, 2, 64), (2080, 2, 64), (4096, 2, 64), (4128, 2, 64),   # behind the norm
+    (64, 16, 1056), (64, 17, 1024), (64, 32, 2080), (64, 33, 2048), (64, 64, 4128), (64, 65, 4096),  # no producer, SiLU
+])
+def test_q4_thresholds_in_registers_every_share(ctx, kind, d, nh, f):
+    """4-bit threshold launches without sets decide up to 64, 128 or 256 channels a wave in registers, more
+    of them through the LDS.  One workgroup per tile, so that a wave has a sixteenth of the input: at and behind
+    each line, for each producer, against the oracle's product over what passes of the GPU's own x."""
+    shape = S.ModelShape("shares", 1, d, nh, 1, 64, f)
+    w = S.layer_weights(12, shape, 0)
+    h = S.activation(12, S.channel_scales(12, d, "shares"), "h", 0)
+    K, V = S.kv_cache(12, 1, 12, 64, 9, "shares", 0)
+    st = _dev_stack(ctx, shape, [w], [(K, V)], kv_cap=12, kind=kind)
+    hin = to_dev(h); hout = torch.zeros_like(hin)
+    ctx.set_option(B.AF_OPT_TUNE_WORKGROUPS, 1)
+    try:
+        st.layer(0, hin, hout, 9, 9, M.select_cfg(B.AF_SEL_TOPK, _ks(shape, 50)))
+        ctx.synchronize()
+        names = ("x_qkv", "attn", "x_gateup", "x_down")
+        ts = tuple(float(np.float32(np.median(np.abs(_taps(ctx, shape)[n].astype(np.float64))))) for n in names)
+        st.layer(0, hin, hout, 9, 9, M.select_cfg(B.AF_SEL_THRESHOLD, t=ts, flags=B.AF_SEL_SKIP_SETS))
+        ctx.synchronize()
+    finally:
+        ctx.set_option(B.AF_OPT_TUNE_WORKGROUPS, 0)
+    quantise = O.quantize_q4_cl if kind == B.AF_W_Q4CL else O.quantize_q4_g32
+    wo = {k: quantise(v) if k.startswith("W") else v for k, v in w.items()}
+    t = _taps(ctx, shape)
+    idx = [O.select_threshold(t[n], v) for n, v in zip(names, ts)]
+    assert all(0 < len(i) < len(t[n]) for i, n in zip(idx, names))
+    errs, _ = teacher_forced_layer_errors(O, _ocfg(shape), wo, h, K, V, 9, 9, t, to_host(hout), idx,
+                                          O.SelectCfg(O.SEL_THRESHOLD, t=ts), "cl" if kind == B.AF_W_Q4CL else True)
+    assert max(errs.values()) <= TOL, errs

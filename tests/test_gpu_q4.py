@@ -47,19 +47,20 @@ def test_q4_gemv(ctx, out, n, k):
 
 @pytest.mark.parametrize("k", [1, 5, 64, 65, 7 * 64, 8 * 64, 8 * 64 + 1, 9 * 64 + 63, 17 * 64])
 def test_q4_slice_ends(ctx, k):
-    """Slices of one row to two batches and one more, whose rows open none to all of their groups."""
+    """Slices of one row to two batches and one more (k / 64 rows, rounded up), whose rows open none to all of
+    their groups: both tiles have one workgroup of 64 slices."""
     n, out = 2048, 136
     W, x = _case(out, n, 41)
     nib, s = O.quantize_q4_g32(W)
     packed, scales = ctx.pack_q4_g32(to_dev(W))
-    ctx.set_option(B.AF_OPT_TUNE_SPLIT, 1)      # one workgroup of 64 slices per tile
+    ctx.set_option(B.AF_OPT_TUNE_WORKGROUPS, 2)
     try:
         for idx in (np.arange(k, dtype=np.int32), np.linspace(0, n - 1, k).astype(np.int32)):
             y = ctx.sparse_gemv_q4(packed, scales, to_dev(x), to_dev(idx), y_kind=B.AF_F32)
             ctx.synchronize()
             assert O.rel_err(to_host(y), O.sparse_gemv_q4(nib, s, x, idx)) <= 1e-4
     finally:
-        ctx.set_option(B.AF_OPT_TUNE_SPLIT, 0)
+        ctx.set_option(B.AF_OPT_TUNE_WORKGROUPS, 0)
 
 
 def test_q4_dense_empty_residual(ctx):
