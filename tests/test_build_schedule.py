@@ -13,7 +13,7 @@ import pytest
 
 from paper_2504_08378_amd import build
 
-SOURCES = ["gemv_f16.hip", "gemv_q4.hip", "union.hip", "layer.hip"]
+SOURCES = ["gemv_f16.hip", "gemv_q4.hip", "union.hip", "attention.hip", "layer.hip"]
 
 
 def _assembly(src, tmp):

@@ -173,6 +173,20 @@ def test_batch_layer_has_its_own_key_splits(ctx):
     assert np.array_equal(plain, tuned)
 
 
+@pytest.mark.parametrize("heads,kv_heads,Bt", [(18, 2, 3), (16, 1, 8)])
+def test_batch_layer_more_than_eight_query_heads_of_a_key_head(ctx, heads, kv_heads, Bt):
+    """Two workgroups share a key head (eight query heads each at most): every token's tickets and partial
+    results are its own, with several key splits."""
+    shape = S.ModelShape("wide_groups", 1, 64, heads, kv_heads, 64, 128)
+    kv_cap = 400
+    kv_lens = [390 - 41 * b for b in range(Bt)]
+    w, H, caches = _inputs(shape, Bt, kv_cap, kv_lens, seed=3)
+    ks = tuple(O.keep_count(n, 50) for n in _widths(shape))
+    for rep in range(2):   # the second run finds the tickets the first one left
+        res = _run_batch(ctx, shape, w, H, caches, kv_lens, kv_cap, M.select_cfg(B.AF_SEL_TOPK, ks))
+        _check_tokens(ctx, shape, w, H, caches, kv_lens, O.SelectCfg(O.SEL_TOPK, ks), *res, free_running=False)
+
+
 @pytest.mark.parametrize("Bt", [4])
 def test_batch_layer_70b_shape(ctx, Bt):
     """BASELINE config 4 as a whole layer: 70B shape (64 query / 8 key-value heads), B tokens, each
