@@ -195,8 +195,7 @@ struct af_union_args {
   const half_t* X;          // [B][in]
   int B;
   const int32_t* idx_b;     // [B][idx_stride]
-  int idx_stride, k;        // k entries per list, or counts[b] <= k of them
-  const int32_t* counts;    // device int32[B] or null
+  int idx_stride, k;        // entries per list (marked: at most that many are kept)
   int32_t* union_idx;       // [in]
   int32_t* union_n;         // [1]
   bool marked;              // the workspace already holds the tokens' kept channels
@@ -386,8 +385,7 @@ __device__ __forceinline__ float af_wave_sum(float v) {
 // sixteen waves of a workgroup want at the same moment: the step took 0.95 us with 16 of them
 // (selecting launches 2048 -> 2048: 9.81 -> 9.27 us, 4096 -> 4096: 10.44 -> 9.83 us).  Afterwards
 // v[0 .. LX / 8) are the sums of the columns from the returned one on; the order of the additions
-// is the butterfly's.  (The union GEMV keeps the plain butterfly: four tokens measured 3 % slower
-// this way.)
+// is the butterfly's.
 template <int OFF, int N>
 __device__ __forceinline__ int af_sum_lane_step(float (&v)[8]) {  // 2 N columns become N
   const bool up = (threadIdx.x & OFF) != 0;

@@ -8,8 +8,9 @@
 // Per selection point: one launch of B workgroups builds each token's operator input (RMSNorm,
 // copy, or SiLU(gate)*up), selects on it (the front end of row_prologue.h, one workgroup per
 // token) and stores a bit per channel; one launch turns the tokens' bits into the union and the masked
-// token values; one launch streams the union's weight rows for all tokens.  Attention is one launch over (head, key split, token); each token has its own cache,
-// length and position.
+// token values; one launch streams the union's weight rows for all tokens.  Attention is one launch
+// over (key head with up to eight of its query heads, key split, token); each token has its own
+// cache, length and position.
 #include <math.h>
 
 #include "af_internal.h"
@@ -134,7 +135,6 @@ extern "C" int af_decode_layer_batch(af_ctx* ctx, const af_layer_cfg* cfg, const
     u.idx_b = sets->idx[p];
     u.idx_stride = in;
     u.k = sel->mode == AF_SEL_TOPK ? sel->k[p] : in;
-    u.counts = sel->mode == AF_SEL_TOPK ? nullptr : sets->count[p];
     u.union_idx = un_idx;
     u.union_n = un_n + p;
     u.marked = true;        // by the selection launch

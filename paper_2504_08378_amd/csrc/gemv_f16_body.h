@@ -120,7 +120,7 @@ __device__ __forceinline__ void store_out(const GemvParams& p, int col, float v,
 struct GemvPlan {
   GemvParams p;
   int tiles, S, lx, nw;
-  int early;  // gemv_early_class of the launch
+  int early;  // gemv_early_class (top-k), gemv_range_class (thresholds) or gemv_given_class (rows given) of the launch
   size_t lds;
 };
 // whole_layer: the operator runs as a phase of the whole-layer kernel (1024-thread workgroups,

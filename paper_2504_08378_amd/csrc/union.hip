@@ -16,8 +16,7 @@
 
 struct UnionBuildParams {
   const half_t* X;         // [B][in]
-  const int32_t* idx_b;    // [B][idx_stride], k entries used (or counts[b] of them)
-  const int32_t* counts;   // per-token list lengths on the device, or null: k for every token
+  const int32_t* idx_b;    // [B][idx_stride], k entries used
   unsigned char* kept;     // [B][af_kept_stride(in)]
   int32_t* union_idx;      // [in]
   int32_t* union_n;        // [1]
@@ -31,7 +30,7 @@ struct UnionBuildParams {
 __global__ __launch_bounds__(UB_THREADS) void union_mark_kernel(UnionBuildParams p) {
   extern __shared__ __align__(16) unsigned s_kept[];  // af_kept_stride(in) bytes
   const int b = blockIdx.x, words = af_kept_stride(p.in) / 4;
-  const int kb = p.counts ? min(max(p.counts[b], 0), p.k) : p.k;
+  const int kb = p.k;
   const int32_t* list = p.idx_b + (size_t)b * p.idx_stride;
   int j[4];
   auto fetch = [&](int t0) {
@@ -283,7 +282,6 @@ int af_launch_union_f16(af_ctx* ctx, const af_union_args& u) {
   UnionBuildParams bp;
   bp.X = u.X;
   bp.idx_b = u.idx_b;
-  bp.counts = u.counts;
   bp.union_idx = u.union_idx;
   bp.union_n = u.union_n;
   bp.Xm = (half_t*)(ctx->ws + ctx->lay.union_x);
