@@ -15,11 +15,11 @@
 //            columns by byte permutation.
 // q and the probabilities are fp32 values.  Each enters the instructions as three fp16 values, the rounded one
 // and two of what that leaves: all 24 bits of q, and of every weight above 2^-16 of the largest (smaller ones
-// to 2^-40 of it).  The sums over instructions and parts are rounded additions outside of them.  Error of the
-// fp32 results (before their rounding) against 64 bits, 32 heads on 32, scores of 0.4 rms, with the vector unit /
-// with two parts, 2^15 in the exponent and the sums in the instructions / now: 16 keys 0.80 / 2.06 / 0.73e-7,
-// 127 keys 1.03 / 2.55 / 0.78e-7, 6001 keys 1.39 / 2.98 / 1.05e-7; scores of 2.4 rms, 127 keys 1.78 / 2.02 /
-// 1.77e-7.  The third part and the additions cost 0.1 to 0.4 us of the 41 to 60 us below.
+// to 2^-40 of it).  The products of the parts are added outside of the instructions, and those of a score's
+// dimensions as well.  Error of the fp32 results (before their rounding) against 64 bits, 32 heads on 32, scores of
+// 0.4 rms, with the vector unit / with two parts, 2^15 in the exponent and all parts in one running sum / now:
+// 16 keys 0.80 / 2.06 / 0.73e-7, 64 keys 1.01 / 2.48 / 0.75e-7, 6001 keys 1.38 / 2.98 / 1.11e-7; scores of 2.4 rms,
+// 64 keys 1.67 / 1.85 / 1.53e-7.
 // What bounds it: latency at short contexts (load, scores, softmax, values, partial sums to the last
 // workgroup of a head), the read of the cache at long ones.  With one workgroup per query head, which
 // read the rows of a key head once for each of its query heads, us per layer (attention and short
@@ -34,7 +34,7 @@
 
 #define ATT_THREADS 256
 #define ATT_WAVES (ATT_THREADS / AF_WAVE)
-#define ATT_HEADS 8        // query heads of one workgroup
+#define ATT_HEADS 8        // query heads of one workgroup, at most
 #define ATT_STEP 32        // keys of a wave per step
 #define ATT_MAX_KEYS 2048  // cache keys per key split
 // Workgroups that a compute unit holds (the batched launch has more of them than there are units).
@@ -81,9 +81,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   af_prof_begin(p.prof);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
-  const int rep = p.n_heads / p.n_kv, groups = (rep + ATT_HEADS - 1) / ATT_HEADS;
+  const int rep = p.n_heads / p.n_kv, gh = p.group_heads, groups = (rep + gh - 1) / gh;
   const int kvh = groups == 1 ? bx : bx / groups, grp = bx - kvh * groups;
-  const int heads = min(ATT_HEADS, rep - grp * ATT_HEADS), h0 = kvh * rep + grp * ATT_HEADS;
+  const int heads = min(gh, rep - grp * gh), h0 = kvh * rep + grp * gh;
   const int T = p.kv_len;  // the new token's place
   // cached keys of a split, in whole steps; the last split has the new token as well
   const int KP = (af_ceil_div_small(T, KS) + ATT_STEP - 1) / ATT_STEP * ATT_STEP;
@@ -168,10 +168,13 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
   __syncthreads();
 
   float m = -INFINITY, l = 0.f;  // of head n: maximum (uniform over the lane groups), this lane's sum
-  att_f4 acc[VC];                // dimensions (4 g + r) VC + c of head n
+  // Dimensions (4 g + r) VC + c of head n: with the weights' rounded values, and with their rests.  These sums run
+  // through the instructions (at most sixteen steps; 2000 keys a split: 1.37e-7, additions outside 1.15e-7,
+  // fp32 on the vector unit 1.82e-7; the additions cost 0.2 us).
+  att_f4 acc[VC], low[VC];
   const att_f4 zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < VC; ++c) acc[c] = zero4;
+  for (int c = 0; c < VC; ++c) acc[c] = low[c] = zero4;
   const int hn = min(n, heads - 1);  // the rest of the result's columns repeat the last head
   while (k0 < t1) {
     const bool edge = k0 + ATT_STEP > min(t1, T);
@@ -232,7 +235,10 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       const float corr = __builtin_amdgcn_exp2f(m - safe);
       l *= corr;
 #pragma unroll
-      for (int c = 0; c < VC; ++c) acc[c] *= corr;
+      for (int c = 0; c < VC; ++c) {
+        acc[c] *= corr;
+        low[c] *= corr;
+      }
     }
     m = mx;
     // Weights times 2^15 (in the range of fp16; the factor joins behind the exponential, whose argument it
@@ -259,11 +265,9 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
       for (int i = 0; i < 4; ++i)
         a[i] = __builtin_amdgcn_perm(vw[2 * i + 1][c / 2], vw[2 * i][c / 2], c % 2 ? 0x07060302u : 0x05040100u);
       const half8 a8 = __builtin_bit_cast(half8, a);
-      att_f4 rest = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pl), zero4, 0, 0, 0);
-      rest = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pm), rest, 0, 0, 0);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) rest[r] = att_rest(rest[r]);
-      acc[c] += __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, ph), zero4, 0, 0, 0) + rest;
+      low[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pl), low[c], 0, 0, 0);
+      low[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, pm), low[c], 0, 0, 0);
+      acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a8, __builtin_bit_cast(half8, ph), acc[c], 0, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);  // with the products and the next rows' addresses mixed, registers spill
     k0 += ATT_WAVES * ATT_STEP;
@@ -277,7 +281,7 @@ __device__ __forceinline__ void attn_decode_body(const AttnParams& p, const floa
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int c = 0; c < VC; ++c) s_acc[wave][n][(g * 4 + r) * VC + c] = acc[c][r];
+      for (int c = 0; c < VC; ++c) s_acc[wave][n][(g * 4 + r) * VC + c] = acc[c][r] + att_rest(low[c][r]);
     if (g == 0) s_ml[wave][n] = make_float2(m, l);
   }
   __syncthreads();
@@ -397,21 +401,34 @@ __global__ __launch_bounds__(ATT_THREADS, ATT_WAVES_PER_SIMD(HD)) void attn_deco
   attn_decode_body<HD>(p, s_cs, s_sn, blockIdx.x, blockIdx.y, KS);
 }
 
-static int attn_groups(const af_layer_cfg* cfg) {  // workgroups side by side: key heads x groups of query heads
+static int attn_groups(const af_layer_cfg* cfg, int gh) {  // workgroups side by side: key heads x groups of query heads
   const int rep = cfg->n_heads / cfg->n_kv_heads;
-  return cfg->n_kv_heads * ((rep + ATT_HEADS - 1) / ATT_HEADS);
+  return cfg->n_kv_heads * ((rep + gh - 1) / gh);
 }
 
-// Key splits of one token, 0 if the partial results of enough splits do not fit.  One per 64 keys (two
-// waves of 32) up to one workgroup per compute unit and sixteen splits; more only lengthen the sum
-// over them (us per layer, attention and short GEMVs; heads/key heads, keys, at 4 / 8 / 16 / 31 splits):
-//   32/32, 512: 45.2 / 44.1 / 45.3 / 49.8      40/40, 512: 48.5 / 48.0 / 51.4 / 55.5, at 6 splits 47.4
-//   64/8, 2000: 58.9 / 54.1 / 52.3 / 53.9      64/8, 6001: 76.0 / 64.3 / 57.5 / 57.2
-// Where that leaves more than 512 keys to a split, twice as many (32/32, 8000: 8 splits 64.9, 16 62.4).
+// Query heads of a workgroup, for one token.  With four, a wave has one head's splits to add up and not two, one
+// after the other; with eight the rows of eight query heads are read once and not twice, which only
+// caches of more than 3 M key elements notice (us per layer, attention and short GEMVs, 8 / 4; heads/key heads,
+// keys): 8/1, 300 35.4 / 34.4; 64/8, 300 40.0 / 39.6; 64/8, 3000 43.5 / 43.6; 64/8, 6001 47.5 / 47.9.  Batches
+// fill the chip and take eight (64/8, eight tokens of 512 keys, a layer with short GEMVs 133.7 / 142.4).
+static int attn_group_heads(const af_layer_cfg* cfg, int kv_len) {
+  return (long long)cfg->n_kv_heads * kv_len * cfg->head_dim <= 3 << 20 ? ATT_HEADS / 2 : ATT_HEADS;
+}
+
+// Key splits of one token, 0 if the partial results of enough splits do not fit.  One while the four waves take the
+// keys in one step, or in two with a head width of 64, where the step is half as long: no partial results, no ticket
+// (one per 64 keys / one; 32/32, 100: 37.1 / 36.1; 64/8, 100: 40.1 / 38.2; 8/1, 100: 35.8 / 33.8; width 64, 16/4,
+// 200: 34.2 / 33.5, and 256: 34.6 / 35.0).  Beyond that one per 32 keys, a wave's step, and one for the new token,
+// up to one workgroup per compute unit and sixteen splits; more only lengthen the sum over them (one per 64 keys /
+// this; 16/4, 128: 35.8 / 35.1; 32/32, 200: 37.1 / 36.8; 8/1, 400: 35.8 / 35.5; at 8 / 16 / 32 splits 32/32,
+// 695: 38.4 / 39.7 / 43.0; 16/1, 1500: 39.8 / 37.4 / 38.5).  Where that leaves more than 512 keys to a split, twice as
+// many (32/32, 3000: 8 splits 45.2, 16 44.2).  Batches: one per 64 keys (64/8, eight tokens of 512 keys 129.8, one
+// per 32 133.7).
 // `tuned`: the number asked for by option (0: none).  The option is the single-token launch's.
-static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, size_t floats, int tuned) {
-  int KS = (kv_len + 63) / 64;
-  int cap = ctx->n_cu / attn_groups(cfg);
+static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int gh, bool batch, int kv_len, size_t floats, int tuned) {
+  int KS = batch ? (kv_len + 63) / 64 : (kv_len + ATT_STEP - 1) / ATT_STEP + 1;
+  if (kv_len < (cfg->head_dim == 64 ? 2 : 1) * ATT_WAVES * ATT_STEP) KS = 1;
+  int cap = ctx->n_cu / attn_groups(cfg, gh);
   if (cap > 16) cap = 16;
   if (cap < 1) cap = 1;
   if (kv_len > 512 * cap) cap *= 2;
@@ -426,7 +443,8 @@ static int attn_splits(const af_ctx* ctx, const af_layer_cfg* cfg, int kv_len, s
 
 int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv, void* kc, void* vc,
                         int kv_len, int kv_cap, int pos, half_t* out) {
-  const int KS = attn_splits(ctx, cfg, kv_len, ctx->lay.attn_floats, ctx->tune_attn_splits);
+  const int gh = attn_group_heads(cfg, kv_len);
+  const int KS = attn_splits(ctx, cfg, gh, false, kv_len, ctx->lay.attn_floats, ctx->tune_attn_splits);
   if (KS == 0) return AF_EINVAL;
   AttnParams p;
   p.qkv = qkv;
@@ -436,6 +454,7 @@ int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv,
   p.part = (float*)(ctx->ws + ctx->lay.attn_part);
   p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
   p.ticket0 = 0;
+  p.group_heads = gh;
   p.n_heads = cfg->n_heads;
   p.n_kv = cfg->n_kv_heads;
   p.kv_len = kv_len;
@@ -447,7 +466,7 @@ int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv,
     p.cs[i] = (float)cos(ang);
     p.sn[i] = (float)sin(ang);
   }
-  dim3 grid(attn_groups(cfg), KS);
+  dim3 grid(attn_groups(cfg, p.group_heads), KS);
   if (cfg->head_dim == 128)
     hipLaunchKernelGGL(attn_decode_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, p);
   else
@@ -464,7 +483,7 @@ int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const
   int ks_max = 1;
   const size_t per_split = (size_t)cfg->n_heads * (cfg->head_dim + 2);
   for (int b = 0; b < B; ++b) {
-    const int KS = attn_splits(ctx, cfg, kv_len[b], ctx->lay.attn_floats / B, 0);
+    const int KS = attn_splits(ctx, cfg, ATT_HEADS, true, kv_len[b], ctx->lay.attn_floats / B, 0);
     if (KS == 0) return AF_EINVAL;
     bp.splits[b] = KS;
     if (KS > ks_max) ks_max = KS;
@@ -479,6 +498,7 @@ int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const
   p.part = (float*)(ctx->ws + ctx->lay.attn_part);
   p.tickets = (int*)(ctx->ws + ctx->lay.tickets) + AF_TICKET_ATTN;
   p.ticket0 = 0;
+  p.group_heads = ATT_HEADS;
   p.n_heads = cfg->n_heads;
   p.n_kv = cfg->n_kv_heads;
   p.kv_cap = kv_cap;
@@ -489,7 +509,7 @@ int af_launch_attention_batch(af_ctx* ctx, const af_layer_cfg* cfg, int B, const
   bp.qkv_stride = qkv_stride;
   bp.out_stride = out_stride;
   bp.part_stride = (long long)ks_max * (long long)per_split;
-  dim3 grid(attn_groups(cfg), ks_max, B);
+  dim3 grid(attn_groups(cfg, p.group_heads), ks_max, B);
   if (cfg->head_dim == 128)
     hipLaunchKernelGGL(attn_decode_batch_kernel<128>, grid, dim3(ATT_THREADS), 0, ctx->stream, bp);
   else

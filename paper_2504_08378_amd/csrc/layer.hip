@@ -481,6 +481,7 @@ static int launch_layer_kernel(af_ctx* ctx, const af_layer_cfg* cfg, const af_ge
   a.part = (float*)(ctx->ws + ctx->lay.attn_part);
   a.tickets = counters + AF_TICKET_ATTN;
   a.ticket0 = 0;
+  a.group_heads = 1;
   a.n_heads = cfg->n_heads;
   a.n_kv = cfg->n_kv_heads;
   a.kv_len = kv_len;

@@ -71,6 +71,14 @@ def test_heads_keys_and_splits(ctx, heads, kv_heads, hd, kv_len, splits):
     assert O.rel_err(got, O.round_f16(ref())) <= 2e-3
 
 
+@pytest.mark.parametrize("heads,kv_heads,hd,kv_len", [(72, 8, 128, 3100), (16, 16, 64, 3100), (16, 16, 64, 3000)])
+def test_long_caches_share_rows_among_eight_heads(ctx, heads, kv_heads, hd, kv_len):
+    """Caches on both sides of the line from which a workgroup takes eight query heads and not four."""
+    K, V = _cache(kv_heads, kv_len + 5, hd, kv_len, kv_len + hd)
+    got, ref = _run(ctx, heads, kv_heads, hd, K, V, kv_len)
+    assert O.rel_err(got, O.round_f16(ref())) <= 2e-3
+
+
 @pytest.mark.parametrize("splits", [1, 4])
 def test_infinities_stay_where_they_are(ctx, splits):
     """An infinite value reaches its own dimension only; a key with an infinite component takes all the
