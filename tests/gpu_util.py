@@ -19,7 +19,10 @@ def to_host(t):
 def ctx():
     from paper_2504_08378_amd import binding as B
     c = B.Context(0)
-    yield c
+    # What a test fills or copies with torch lies on the context's stream too: on the default stream a fill could
+    # come after the kernel whose output it prepares.
+    with torch.cuda.stream(c.stream):
+        yield c
     c.close()
 
 

@@ -29,7 +29,8 @@ def ctx(request):
     c = B.Context(0)
     if request.param == "launch_per_layer":
         c.set_option(B.AF_OPT_LAYER_KERNEL, 1)
-    yield c
+    with torch.cuda.stream(c.stream):  # as in gpu_util.ctx
+        yield c
     assert c.last_device_error() == 0
     c.close()
 

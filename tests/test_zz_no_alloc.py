@@ -45,6 +45,7 @@ def test_noalloc_matches_workspace_entry_point_twice():
             dt = torch.float16 if kind == B.AF_F16 else torch.float32
             y_ref = torch.zeros(out, dtype=dt, device="cuda")
             y_new = torch.full((out,), 7.0, dtype=dt, device="cuda")   # made before the call
+            torch.cuda.synchronize()   # the contexts' streams do not wait for these fills
             ref_ctx.sparse_gemv_f16(Wt, xd, idxd, nidx=k, y=y_ref, y_kind=kind, residual=resd, out=out)
             ref_ctx.synchronize()
             # torch's allocator counts every device allocation it makes: the call must add none
