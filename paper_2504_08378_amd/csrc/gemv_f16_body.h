@@ -621,12 +621,15 @@ constexpr int gemv_early_cap(int lx) { return (lx == 16 ? 4 : 8) * AF_WAVE / lx;
 // Which of them: inputs of up to 4096, 16384 and AF_MAX_N channels.
 static inline int gemv_width_class(int n) { return n <= RP_EV * 1024 ? 0 : (n <= 4 * RP_EV * 1024 ? 1 : 2); }
 // ... and whether at all: not where early rows cost more than they hide.  The look for the rows is
-// 0.5-1 us of front end.  Up to 4096 channels it pays from a stream of 100, 132 and 150 KB a workgroup on, by
-// the width of the tile (us without / with, index list written; 50 % unless stated):
+// 0.5-1 us of front end.  Up to 4096 channels it pays from a stream of 100, 132 (up to 3584 channels 120) and 150 KB
+// a workgroup on, by the width of the tile (us without / with, index list written; 50 % unless stated):
 //   128 columns: 4096 -> 4096 (85 KB) 10.45 / 10.67         2048 -> 6144 at 30 % (90 KB) 10.10 / 10.32
 //                4096 -> 6144 (102 KB) 11.57 / 11.40        4096 -> 6144 at 30 % (143 KB) 13.62 / 12.70
 //   256 columns: 2048 -> 12288 (102 KB) 10.71 / 11.23       4096 -> 8192 (128 KB) 12.44 / 12.96, behind SiLU 12.18 / 12.45
 //                3072 -> 8192 at 30 % (134 KB) 12.38 / 11.86    2048 -> 12288 at 30 % (143 KB) 12.67 / 11.96
+//                2200 -> 10128 at 30 % (128 KB) 13.20 / 11.79   3056 -> 10128 (127 KB) 13.19 / 12.36
+//                3496 -> 9208 (124 KB) 13.21 / 12.94            2800 -> 8136 at 30 % (122 KB) 12.79 / 12.15
+//                2800 -> 10128 (116 KB) 12.15 / 11.94, behind SiLU 11.88 / 12.16    4000 -> 8136 (125 KB) 13.17 / 13.71
 //                4096 -> 6400 at 30 % (143 KB) 13.61 / 12.46    3072 -> 12288 (154 KB) 13.22 / 12.34
 //   512 columns: 4096 -> 14336 at 80 % (136 KB) 11.38 / 11.85   3072 -> 14336 at 70 % (153 KB) 12.00 / 11.67
 //                3072 -> 22016 at 80 % (153 KB) 11.98 / 12.03   4096 -> 22016 (409 KB) 21.28 / 19.69
@@ -645,7 +648,7 @@ static inline int gemv_early_class(int pro, int n, int k, int S, int lx) {
   const long long row = lx * 16, bytes = k / S * row;
   const int share = (int)((long long)k * 48 / n), cap = gemv_early_cap(lx);
   const long long early = (share < cap ? share : cap) * 16 * row;  // taken by the workgroup's waves
-  const int line = lx == 16 ? 100 : (lx == 32 ? 132 : 150);
+  const int line = lx == 16 ? 100 : (lx == 32 ? (n <= 3584 ? 120 : 132) : 150);
   const bool pays = n <= 4096 ? bytes >= line * 1024
                               : bytes >= (early >= 48 * 1024 ? 48 : 72) * 1024 &&
                                     n / S / 16 * 2 * 1024 <= (pro == AF_PRO_SILUMUL ? 7 : 12) * early;
