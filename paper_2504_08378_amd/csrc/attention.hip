@@ -23,10 +23,10 @@
 // What bounds it: latency at short contexts (load, scores, softmax, values, partial sums to the last
 // workgroup of a head), the read of the cache at long ones.  With one workgroup per query head, which
 // read the rows of a key head once for each of its query heads, us per layer (attention and short
-// GEMVs), before / now: 64 heads on 8 key heads, 512 keys 52.6 / 49.6, 2000 keys 61.4 / 50.5, 6001 keys
-// 82.5 / 56.0; 32 on 8, 512 keys 44.0 / 41.2, 4000 keys 53.4 / 44.8; 32 on 32, 512 keys 44.3 / 41.9, 8000
-// keys 63.5 / 60.3 (1 to 2.5 us of that by the GEMVs' tickets).  A first version that rotated q in every lane,
-// 300 instructions of one wave, was 2 us slower throughout.  The error of the fp16 result against 64 bits is that
+// GEMVs: 512 channels), before / now: 64 heads on 8 key heads, 512 keys 45.3 / 41.6, 2000 keys 54.1 / 43.3, 6001 keys
+// 76.1 / 49.6; 32 on 8, 512 keys 41.9 / 39.3, 4000 keys 51.7 / 43.5; 32 on 32, 512 keys 42.2 / 40.4, 3000 keys 49.2 / 47.8,
+// 8000 keys 61.5 / 58.8 (1 to 2 us of that by the GEMVs' tickets).  Caches of fewer than 128 keys: attn_short_kernel.
+// A first version that rotated q in every lane, 300 instructions of one wave, was 2 us slower throughout.  The error of the fp16 result against 64 bits is that
 // of the rounding alone (2.0942e-4 at 32 heads and 512 keys, before and now).
 #include <math.h>
 
@@ -363,6 +363,128 @@ __global__ __launch_bounds__(ATT_THREADS, ATT_WAVES_PER_SIMD(HD)) void attn_deco
   attn_decode_body<HD>(p, p.cs, p.sn, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
+// Caches of fewer than 128 keys, one token: a workgroup per query head on the vector unit, in fp32.  All keys and
+// values are requested at once, a wave holds every score (one or two per lane) and forms the softmax for itself, and
+// nothing is split over workgroups.  At this size the launch is a chain of dependent steps, and that of the matrix-core
+// form is longer whatever the number of keys (us per layer of 512 channels, heads/key heads, keys, matrix cores / this;
+// head width 128): 4/2, 17 33.6 / 32.2; 4/2, 90 34.2 / 33.5; 32/32, 60 38.1 / 36.4; 32/32, 64 38.3 / 37.4; 64/8, 64 39.9 /
+// 39.6; 64/8, 100 40.2 / 39.7; width 64, 16/4, 64 34.3 / 33.3.  The launch itself: 4/2, 17 5.1 / 4.2.  From 64 keys on the
+// second eight rows a lane and the second score cost 0.6 to 1 us (32/32, 63 and 64: 36.4, 37.4).
+// KEYS: at most, with the new token's.
+template <int HD, int KEYS>
+__global__ __launch_bounds__(ATT_THREADS) void attn_short_kernel(AttnParams p) {
+  constexpr int LPK = HD / 8;                  // lanes per key (16 bytes each)
+  constexpr int KPB = ATT_THREADS / LPK;       // keys of the workgroup at a time
+  constexpr int NB = KEYS / KPB, P = KEYS / AF_WAVE;
+  __shared__ __align__(16) float s_q[HD], s_kn[HD], s_vn[HD];
+  __shared__ float s_sc[KEYS];
+  __shared__ __align__(16) float s_pv[KPB][HD];
+
+  af_prof_begin(p.prof);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = blockIdx.x, rep = p.n_heads / p.n_kv, kvh = h / rep, T = p.kv_len;
+  const half_t* q = p.qkv + (size_t)h * HD;
+  const half_t* kn = p.qkv + (size_t)(p.n_heads + kvh) * HD;
+  const half_t* vn = p.qkv + (size_t)(p.n_heads + p.n_kv + kvh) * HD;
+  half_t* Kc = p.k_cache + (size_t)kvh * p.kv_cap * HD;
+  half_t* Vc = p.v_cache + (size_t)kvh * p.kv_cap * HD;
+  const int lk = tid % LPK, kq = tid / LPK;
+
+  // q (first wave), the new k (second) and v (the others), and behind them the rows: loads return in order.  A row
+  // behind the cache is read as the last one (or as the one that the new token goes to) and not used.
+  const half_t* src = wave == 0 ? q : (wave == 1 ? kn : vn);
+  const int i = wave < 2 ? lane % (HD / 2) : (tid - 128) % HD;
+  const half_t a = src[i], b = src[wave < 2 ? i + HD / 2 : i];
+  const float cs = p.cs[lane % (HD / 2)], sn = p.sn[lane % (HD / 2)];
+  half8 kr[NB], vr[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const unsigned o = (unsigned)min(kq + u * KPB, max(T - 1, 0)) * HD + lk * 8;
+    kr[u] = af_load_once(reinterpret_cast<const half8*>(Kc + o));
+    vr[u] = af_load_once(reinterpret_cast<const half8*>(Vc + o));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  if (wave == 0) {
+    if (lane < HD / 2) {
+      const float scale = 1.0f / sqrtf((float)HD);
+      s_q[i] = __builtin_fmaf((float)a, cs, -((float)b * sn)) * scale;
+      s_q[i + HD / 2] = __builtin_fmaf((float)b, cs, (float)a * sn) * scale;
+    }
+  } else if (wave == 1) {
+    if (lane < HD / 2) {
+      const half_t ha = att_fma_half(a, cs, -((float)b * sn)), hb = att_fma_half(b, cs, (float)a * sn);
+      s_kn[i] = (float)ha;  // fp16, as in the cache
+      s_kn[i + HD / 2] = (float)hb;
+      if (h % rep == 0) {
+        Kc[(size_t)T * HD + i] = ha;
+        Kc[(size_t)T * HD + i + HD / 2] = hb;
+      }
+    }
+  } else if (tid - 128 < HD) {
+    s_vn[i] = (float)a;
+    if (h % rep == 0) Vc[(size_t)T * HD + i] = a;
+  }
+  __syncthreads();
+
+  float qr[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) qr[c] = s_q[lk * 8 + c];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int key = kq + u * KPB;
+    float d = 0.f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) d += (float)kr[u][c] * qr[c];
+    if (key == T) {
+      d = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) d += s_kn[lk * 8 + c] * qr[c];
+    }
+#pragma unroll
+    for (int off = 1; off < LPK; off <<= 1) d += __shfl_xor(d, off, AF_WAVE);
+    if (lk == 0) s_sc[key] = key <= T ? d : -INFINITY;
+  }
+  __syncthreads();
+
+  float e[P], m = -INFINITY, l = 0.f;  // of keys lane, lane + 64
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    e[j] = s_sc[j * AF_WAVE + lane];
+    m = fmaxf(m, e[j]);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, AF_WAVE));
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    e[j] = j * AF_WAVE + lane <= T ? expf(e[j] - m) : 0.f;
+    l += e[j];
+  }
+  l = af_wave_sum(l);
+  float acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int key = kq + u * KPB;
+    const float w = __shfl(e[u * KPB / AF_WAVE], key % AF_WAVE, AF_WAVE);
+    if (key < T) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] += w * (float)vr[u][c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) s_pv[kq][lk * 8 + c] = acc[c];
+  __syncthreads();
+  if (tid < HD) {
+    float v[4] = {__shfl(P > 1 && T >= AF_WAVE ? e[P - 1] : e[0], T % AF_WAVE, AF_WAVE) * s_vn[tid], 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < KPB; ++g) v[g & 3] += s_pv[g][tid];
+    p.out[(size_t)h * HD + tid] = (half_t)(((v[0] + v[1]) + (v[2] + v[3])) / l);
+  }
+  af_prof_end(p.prof);
+}
+
 // The same for B tokens in one launch (af_decode_layer_batch): grid (key heads x head groups, key splits, tokens);
 // every token has its own caches, length, position and number of key splits.  The rotary table
 // of a token is formed here, in fp64 like the host does for the single-token launch
@@ -416,8 +538,9 @@ static int attn_group_heads(const af_layer_cfg* cfg, int kv_len) {
 }
 
 // Key splits of one token, 0 if the partial results of enough splits do not fit.  One while the four waves take the
-// keys in one step, or in two with a head width of 64, where the step is half as long: no partial results, no ticket
-// (one per 64 keys / one; 32/32, 100: 37.1 / 36.1; 64/8, 100: 40.1 / 38.2; 8/1, 100: 35.8 / 33.8; width 64, 16/4,
+// keys in one step (batches), or in two with a head width of 64, where the step is half as long: no partial results, no
+// ticket (one token, when it took this form at any length; one per 64 keys / one; 32/32, 100: 37.1 / 36.1; 64/8, 100:
+// 40.1 / 38.2; 8/1, 100: 35.8 / 33.8; width 64, 16/4,
 // 200: 34.2 / 33.5, and 256: 34.6 / 35.0).  Beyond that one per 32 keys, a wave's step, and one for the new token,
 // up to one workgroup per compute unit and sixteen splits; more only lengthen the sum over them (one per 64 keys /
 // this; 16/4, 128: 35.8 / 35.1; 32/32, 200: 37.1 / 36.8; 8/1, 400: 35.8 / 35.5; at 8 / 16 / 32 splits 32/32,
@@ -465,6 +588,19 @@ int af_launch_attention(af_ctx* ctx, const af_layer_cfg* cfg, const half_t* qkv,
     const double ang = (double)pos * pow((double)cfg->rope_theta, -2.0 * (double)i / (double)cfg->head_dim);
     p.cs[i] = (float)cos(ang);
     p.sn[i] = (float)sin(ang);
+  }
+  if (kv_len < 128 && ctx->tune_attn_splits == 0) {
+    const dim3 grid(cfg->n_heads), threads(ATT_THREADS);
+    if (cfg->head_dim == 128 && kv_len < 64)
+      hipLaunchKernelGGL((attn_short_kernel<128, 64>), grid, threads, 0, ctx->stream, p);
+    else if (cfg->head_dim == 128)
+      hipLaunchKernelGGL((attn_short_kernel<128, 128>), grid, threads, 0, ctx->stream, p);
+    else if (kv_len < 64)
+      hipLaunchKernelGGL((attn_short_kernel<64, 64>), grid, threads, 0, ctx->stream, p);
+    else
+      hipLaunchKernelGGL((attn_short_kernel<64, 128>), grid, threads, 0, ctx->stream, p);
+    AF_LAUNCH_CHECK();
+    return AF_OK;
   }
   dim3 grid(attn_groups(cfg, p.group_heads), KS);
   if (cfg->head_dim == 128)

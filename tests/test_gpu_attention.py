@@ -197,3 +197,42 @@ def test_infinite_key_behind_a_small_query(ctx, splits):
     ref = O.attention_decode(O.rope(q, kv_len, 10000.0), Kr, Vr, kv_len + 1).reshape(-1)
     assert np.all(np.isfinite(got.astype(np.float32)))
     assert O.rel_err(got, O.round_f16(ref)) <= 2e-3
+
+
+@pytest.mark.parametrize("heads,kv_heads,hd", [(4, 2, 128), (6, 1, 128), (3, 3, 64), (16, 2, 64)])
+@pytest.mark.parametrize("kv_len", [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 80, 97, 126, 127, 128])
+def test_short_caches(ctx, heads, kv_heads, hd, kv_len):
+    """Fewer than 128 cached keys go to a kernel of their own (up to 63 in one form, from 64 in another): against the oracle, and against
+    the other kernel (one split asked for), both within half a unit in the last place plus fp32's error of
+    the same result, so at most the neighbouring fp16 value apart."""
+    K, V = _cache(kv_heads, kv_len + 3, hd, kv_len, kv_len + hd)
+    got, ref = _run(ctx, heads, kv_heads, hd, K, V, kv_len)
+    assert O.rel_err(got, O.round_f16(ref())) <= 2e-3
+    other, _ = _run(ctx, heads, kv_heads, hd, K, V, kv_len, 1)
+    a, b = got.astype(np.float64), other.astype(np.float64)
+    assert np.all(np.abs(a - b) <= 2.0 ** -10 * np.maximum(np.abs(b), 2.0 ** -14) + 1e-6)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("kv_len", [17, 63, 64, 127])
+def test_short_caches_special_values(ctx, hd, kv_len):
+    """An infinite value reaches its own dimension only; a key of -inf has no weight; a NaN key makes its head NaN;
+    rows behind the cache are read and not used."""
+    heads, rep = 4, 2
+    K, V = _cache(heads // rep, kv_len + 2, hd, kv_len, 11)
+    K[:, kv_len:] = np.nan
+    V[:, kv_len:] = np.nan
+    plain, q, Kr, Vr = _run_parts(ctx, heads, heads // rep, hd, K, V, kv_len)
+    assert np.all(np.isfinite(plain.astype(np.float32)))
+    V1 = V.copy(); V1[0, 5, 3] = np.inf
+    got = _run_parts(ctx, heads, heads // rep, hd, K, V1, kv_len)[0].reshape(heads, hd)
+    keep = np.ones((heads, hd), bool); keep[:rep, 3] = False
+    assert np.all(got[:rep, 3] == np.inf) and np.array_equal(got[keep], plain.reshape(heads, hd)[keep])
+    K1 = K.copy(); K1[1, 7, 2] = np.nan
+    got = _run_parts(ctx, heads, heads // rep, hd, K1, V, kv_len)[0].reshape(heads, hd)
+    assert np.all(np.isnan(got[rep:].astype(np.float32))) and np.array_equal(got[:rep], plain.reshape(heads, hd)[:rep])
+    x = O.rope(q, kv_len, 10000.0)[0]
+    K2 = K.copy(); K2[0, 9, 4] = -np.sign(x[4]) * np.inf
+    got, q, Kr, Vr = _run_parts(ctx, heads, heads // rep, hd, K2, V, kv_len)
+    one = O.attention_decode(O.rope(q, kv_len, 10000.0), Kr, Vr, kv_len + 1)[0]
+    assert np.all(np.isfinite(got[:hd].astype(np.float32))) and O.rel_err(got[:hd], O.round_f16(one)) <= 2e-3
