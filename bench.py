@@ -32,10 +32,10 @@ HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E bandwidth
 # FETCH_SIZE KiB x fetch factor + WRITE_SIZE KiB x write factor, the factors being what the same
 # counters read for a plain 256 MiB device copy of known size.  The output repeats file, kernel and
 # launch shape, and says whether the kernel's sources are still those that were counted.
-TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44466.0, "fetch_factor": 2.000, "write_KiB": 497.5, "write_factor": 1.000,
+TRAFFIC = {("7b", "f16", 50): {"fetch_KiB": 44465.8, "fetch_factor": 2.000, "write_KiB": 497.5, "write_factor": 1.000,
                                "kernel": "gemv_f16_kernel<64, 8, 16, false, 5> grid 43x5",
                                "source": "profiles/gateup_7b_f16_sp50_pmc_traffic.md",
-                               "kernel_sources": "8f625a4a3c83"}}
+                               "kernel_sources": "f4b430cae8ed"}}
 
 
 def kernel_sources_digest() -> str:
