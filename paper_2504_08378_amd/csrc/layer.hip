@@ -116,9 +116,10 @@ struct AttnLds {
 #define LAYER_ATT_LDS_BYTES (4 * (AttnLds<128>::END > AttnLds<64>::END ? AttnLds<128>::END : AttnLds<64>::END))
 
 // Attention of (head h, key split s) by one 1024-thread workgroup, in fp32 on the vector unit: fp32 q, dot
-// products and weights (expf), one softmax over the split.  The attention launches (attention.hip) take a key
-// head's queries together through the matrix cores, with a running softmax in powers of two; both are as
-// close to 64 bits as fp32 sums are, and agree to the fp16 rounding of the result.  The cached keys and values of the split are requested first, then the
+// products and weights (expf), one softmax over the split.  The attention launches (attention.hip) do so for caches
+// of fewer than 128 keys; beyond that they take a key head's queries together through the matrix cores, with a
+// running softmax in powers of two.  All are as close to 64 bits as fp32 sums are, and agree to the fp16 rounding of
+// the result.  The cached keys and values of the split are requested first, then the
 // workgroup waits for the qkv projection (counter `ready` reaching `ready_total`).
 template <int HD>
 __device__ __forceinline__ bool attn_phase(const AttnParams& p, int h, int s, int KS, float* lds,
